@@ -3,6 +3,7 @@
 // contract of every function.
 #include "../../include/fingpt_hpc.h"
 #include "gemm_bf16.h"
+#include "gemm_f32.h"
 #include "kernels_misc.h"
 #include "merge.h"
 #include "qskinny.h"
@@ -349,6 +350,35 @@ bool stream_dx(int64_t M, int64_t K, int64_t r, int64_t N)
     return qskinny_dx_supports(M, K, r, N, FHPC_Q_INT4_BLOCK) && qskinny_dx_supports(M, K, r, N, FHPC_Q_INT8_PER_CHANNEL);
 }
 
+// ---- fp32 products: plan, and the slabs a plan needs
+GemmF32Plan plan_f32(int64_t M, int64_t N, int64_t Kred) { return plan_gemm_f32(1, &M, &N, &Kred, num_cu(), nullptr); }
+// dA (K x r) and dB (r x N), both reductions over the M tokens, in one launch
+void plan_f32_grads(int64_t M, int64_t K, int64_t r, int64_t N, GemmF32Plan* each)
+{
+    const int64_t ms[2] = {K, r}, ns[2] = {r, N}, ks[2] = {M, M};
+    plan_gemm_f32(2, ms, ns, ks, num_cu(), each);
+}
+int64_t plan_f32_bytes(const GemmF32Plan& p, int64_t M, int64_t N) { return p.splits > 1 ? p.splits * gemm_f32_slab(M, N) * 4 : 0; }
+
+int64_t f32_part_bytes(bool bwd, int64_t M, int64_t K, int64_t r, int64_t N)
+{
+    int64_t part = 0;
+    auto upto = [&part](int64_t b) { if (b > part) part = b; };
+    if (!lowrank_chain_f32_pays(M, K, r)) {
+        upto(plan_f32_bytes(plan_f32(M, r, K), M, r));                                          // H = X A
+        if (!bwd) upto(plan_f32_bytes(plan_f32(M, N, r), M, N));                                // Y = H B
+    }
+    if (!bwd) return part;
+    if (!lowrank_chain_f32_pays(M, N, r)) {
+        upto(plan_f32_bytes(plan_f32(M, r, N), M, r));                                          // dH = dY B^T
+        upto(plan_f32_bytes(plan_f32(M, K, r), M, K));                                          // dX = dH A^T
+    }
+    GemmF32Plan both[2];
+    plan_f32_grads(M, K, r, N, both);                                                           // dA and dB
+    upto(plan_f32_bytes(both[0], K, r) + plan_f32_bytes(both[1], r, N));
+    return part;
+}
+
 Scratch carve(Carver& c, int op, int64_t M, int64_t K, int64_t r, int64_t N, int dtype, bool quantised = true,
               bool premerged = false)
 {
@@ -358,6 +388,8 @@ Scratch carve(Carver& c, int op, int64_t M, int64_t K, int64_t r, int64_t N, int
         // fp32 path: H and dH in fp32, no padding
         s.H = c.take(M * r * 4);
         if (op == FHPC_OP_LOWRANK_BWD) s.dH = c.take(M * r * 4);
+        s.part_bytes = f32_part_bytes(op == FHPC_OP_LOWRANK_BWD, M, K, r, N);
+        s.part = static_cast<float*>(c.take(s.part_bytes));
         return s;
     }
     if (op == FHPC_OP_QLINEAR_FWD && quantised && qskinny_supports(M, K, r, N, FHPC_Q_INT4_BLOCK)) {
@@ -742,20 +774,63 @@ int check_workspace(int op, void* ws, size_t ws_bytes, int64_t M, int64_t K, int
 }
 
 // ---------------- fp32 path of the factorised layer ----------------
+GemmF32Job job_f32(const float* a, int64_t lda, const float* b, int64_t ldb, int64_t M, int64_t N, int64_t Kred, const GemmF32Plan& p)
+{
+    GemmF32Job j = {};
+    j.a = a; j.lda = lda; j.b = b; j.ldb = ldb;
+    j.M = (int)M; j.N = (int)N; j.K = (int)Kred;
+    j.ldc = N; j.slab = gemm_f32_slab(M, N);
+    j.splits = p.splits; j.k_chunk = p.k_chunk;
+    return j;
+}
+
+// Dense outputs C[i][M][N] of `count` products (same layouts, same tile): one launch, and one more for the slab sums
+// of those whose reduction is cut into slices.
+hipError_t products_f32(F32Layout al, F32Layout bl, GemmF32Job* jobs, float* const* C, int count, int tile, float* part, Run& run)
+{
+    int64_t need = 0;
+    for (int i = 0; i < count; i++) need += jobs[i].splits > 1 ? jobs[i].splits * jobs[i].slab * 4 : 0;
+    if (!run.claim(need)) return hipErrorOutOfMemory;
+    if (run.dry) return hipSuccess;
+    SumF32Job sums[2] = {};
+    int n = 0;
+    for (int i = 0; i < count; i++) {
+        if (jobs[i].splits == 1) {
+            jobs[i].c = C[i];
+            continue;
+        }
+        jobs[i].c = part;
+        sums[n].slabs = part; sums[n].out = C[i];
+        sums[n].n = (int64_t)jobs[i].M * jobs[i].N; sums[n].slab = jobs[i].slab; sums[n].nslab = jobs[i].splits;
+        part += jobs[i].splits * jobs[i].slab;
+        n++;
+    }
+    hipError_t e = launch_gemm_f32(al, bl, jobs, count, tile, run.st);
+    if (e != hipSuccess || n == 0) return e;
+    return launch_sum_f32(sums, n, run.st);
+}
+
+// C[M][N] = a * b, one product
+hipError_t product_f32(F32Layout al, F32Layout bl, const float* a, int64_t lda, const float* b, int64_t ldb, float* C,
+                       int64_t M, int64_t N, int64_t Kred, const Scratch& s, Run& run)
+{
+    const GemmF32Plan p = plan_f32(M, N, Kred);
+    GemmF32Job j = job_f32(a, lda, b, ldb, M, N, Kred, p);
+    return products_f32(al, bl, &j, &C, 1, p.tile, s.part, run);
+}
+
 int lowrank_fwd_f32(const float* X, const float* A, const float* B, float* Y, float* H_out,
                     int64_t M, int64_t K, int64_t r, int64_t N, const Scratch& s, Run& run)
 {
-    if (run.dry) return FHPC_OK;
-    hipStream_t st = run.st;
-    if (lowrank_chain_f32_supports(r)) {
-        // a rank that fits a workgroup's LDS: H = X A never leaves the chip on its way into Y = H B (one launch;
-        // H is stored only if the caller asked for it)
-        FHPC_HIP(launch_lowrank_chain_f32(X, K, A, r, 1, B, N, 1, Y, N, H_out, (int)M, (int)K, (int)r, (int)N, st));
+    if (lowrank_chain_f32_pays(M, K, r)) {
+        // few tokens and a rank that fits a workgroup's LDS: H = X A never leaves the chip on its way into Y = H B (one
+        // launch; H is stored only if the caller asked for it)
+        FHPC_LAUNCH(run, launch_lowrank_chain_f32(X, K, A, r, F32_XC, B, N, F32_XC, Y, N, H_out, (int)M, (int)K, (int)r, (int)N, num_cu(), run.st));
         return FHPC_OK;
     }
     float* H = H_out ? H_out : static_cast<float*>(s.H);
-    FHPC_HIP(launch_gemm_f32(X, K, 1, A, r, 1, H, r, (int)M, (int)r, (int)K, 1.f, st));
-    FHPC_HIP(launch_gemm_f32(H, r, 1, B, N, 1, Y, N, (int)M, (int)N, (int)r, 1.f, st));
+    FHPC_HIP(product_f32(F32_KC, F32_XC, X, K, A, r, H, M, r, K, s, run));
+    FHPC_HIP(product_f32(F32_KC, F32_XC, H, r, B, N, Y, M, N, r, s, run));
     return FHPC_OK;
 }
 
@@ -763,28 +838,39 @@ int lowrank_bwd_f32(const float* X, const float* A, const float* B, const float*
                     float* dX, float* dA, float* dB, int64_t M, int64_t K, int64_t r, int64_t N,
                     const Scratch& s, Run& run)
 {
-    if (run.dry) return FHPC_OK;
-    hipStream_t st = run.st;
     const float* H = H_saved;
     if (!H && dB) {
+        // (the way the forward call forms it, so that saved and recomputed H have the same bits)
         float* Hw = static_cast<float*>(s.H);
-        FHPC_HIP(launch_gemm_f32(X, K, 1, A, r, 1, Hw, r, (int)M, (int)r, (int)K, 1.f, st));
+        if (lowrank_chain_f32_pays(M, K, r))
+            FHPC_LAUNCH(run, launch_lowrank_chain_f32(X, K, A, r, F32_XC, B, N, F32_XC, nullptr, N, Hw, (int)M, (int)K, (int)r, 0, num_cu(), run.st));
+        else
+            FHPC_HIP(product_f32(F32_KC, F32_XC, X, K, A, r, Hw, M, r, K, s, run));
         H = Hw;
     }
     float* dH = static_cast<float*>(s.dH);
-    if (dX && lowrank_chain_f32_supports(r)) {
+    if ((dX || dA) && lowrank_chain_f32_pays(M, N, r)) {
         // dH = dY B^T stays in LDS on its way into dX = dH A^T (and is stored for dA)
-        FHPC_HIP(launch_lowrank_chain_f32(dY, N, B, 1, N, A, 1, r, dX, K, dA ? dH : nullptr, (int)M, (int)N, (int)r, (int)K, st));
+        FHPC_LAUNCH(run, launch_lowrank_chain_f32(dY, N, B, N, F32_KC, A, r, F32_KC, dX, K, dA ? dH : nullptr, (int)M, (int)N, (int)r, dX ? (int)K : 0,
+                                                  num_cu(), run.st));
     } else {
         if (dX || dA)   // dH[m][j] = sum_n dY[m][n] B[j][n]
-            FHPC_HIP(launch_gemm_f32(dY, N, 1, B, 1, N, dH, r, (int)M, (int)r, (int)N, 1.f, st));
+            FHPC_HIP(product_f32(F32_KC, F32_KC, dY, N, B, N, dH, M, r, N, s, run));
         if (dX)         // dX[m][k] = sum_j dH[m][j] A[k][j]
-            FHPC_HIP(launch_gemm_f32(dH, r, 1, A, 1, r, dX, K, (int)M, (int)K, (int)r, 1.f, st));
+            FHPC_HIP(product_f32(F32_KC, F32_KC, dH, r, A, r, dX, M, K, r, s, run));
     }
-    if (dA)         // dA[k][j] = sum_m X[m][k] dH[m][j]
-        FHPC_HIP(launch_gemm_f32(X, 1, K, dH, r, 1, dA, r, (int)K, (int)r, (int)M, 1.f, st));
-    if (dB)         // dB[j][n] = sum_m H[m][j] dY[m][n]
-        FHPC_HIP(launch_gemm_f32(H, 1, r, dY, N, 1, dB, N, (int)r, (int)N, (int)M, 1.f, st));
+    // dA[k][j] = sum_m X[m][k] dH[m][j],  dB[j][n] = sum_m H[m][j] dY[m][n]; planned together also when only one of them
+    // is wanted, so that each has the same bits either way
+    if (dA || dB) {
+        GemmF32Plan p[2];
+        plan_f32_grads(M, K, r, N, p);
+        GemmF32Job jobs[2] = {};
+        float* C[2];
+        int n = 0;
+        if (dA) { jobs[n] = job_f32(X, K, dH, r, K, r, M, p[0]); C[n++] = dA; }
+        if (dB) { jobs[n] = job_f32(H, r, dY, N, r, N, M, p[1]); C[n++] = dB; }
+        FHPC_HIP(products_f32(F32_XC, F32_XC, jobs, C, n, p[0].tile, s.part, run));
+    }
     return FHPC_OK;
 }
 

@@ -1,0 +1,49 @@
+// The fp32 products of the factorised layer, on the fp32 matrix instructions.  Internal; not part of the C ABI.
+#pragma once
+#include <hip/hip_runtime.h>
+#include <stdint.h>
+
+namespace fhpc {
+
+// How an operand element (row, k) is stored: ptr[row * ld + k] (F32_KC) or ptr[k * ld + row] (F32_XC).
+enum F32Layout { F32_KC = 0, F32_XC = 1 };
+
+struct GemmF32Plan {
+    int tile;        // 64 or 32: the edge of the square output tile
+    int splits;      // slices of the reduction; more than one: each stores a slab, launch_sum_f32 adds them
+    int k_chunk;     // reduction length of a slice, a multiple of 32
+};
+
+// C[M][N] (row stride ldc, or slab s of `slab` floats when the plan has slices) = sum_k a(m, k) b(n, k)
+struct GemmF32Job {
+    const float* a;
+    const float* b;
+    float* c;
+    int64_t lda, ldb, ldc, slab;
+    int M, N, K;
+    int splits, k_chunk;
+    int a_vec, b_vec;      // 16-byte loads along the contiguous index
+    int tiles_n, items;    // (set by launch_gemm_f32)
+};
+
+// Up to two products of the same operand layouts share a launch; `jobs` products of these sizes are planned together.
+GemmF32Plan plan_gemm_f32(int jobs, const int64_t* M, const int64_t* N, const int64_t* K, int units, GemmF32Plan* each);
+int64_t gemm_f32_slab(int64_t M, int64_t N);      // floats of one slab of an M x N output
+hipError_t launch_gemm_f32(F32Layout al, F32Layout bl, const GemmF32Job* jobs, int count, int tile, hipStream_t s);
+
+struct SumF32Job {
+    const float* slabs;
+    float* out;
+    int64_t n, slab;
+    int nslab, blocks;
+};
+hipError_t launch_sum_f32(const SumF32Job* jobs, int count, hipStream_t s);
+
+// Two chained products with the rank-r intermediate kept in LDS (r <= 64), see gemm_f32.hip:
+// P = L R (M x r, also stored to P_out when given), Out = P S (M x C; C = 0: P alone, with the same bits).
+bool lowrank_chain_f32_pays(int64_t M, int64_t T, int64_t r);
+hipError_t launch_lowrank_chain_f32(const float* L, int64_t ldl, const float* R, int64_t ldr, F32Layout rl,
+                                    const float* S, int64_t lds, F32Layout sl, float* Out, int64_t ldo, float* P_out,
+                                    int M, int T, int r, int C, int units, hipStream_t s);
+
+}  // namespace fhpc

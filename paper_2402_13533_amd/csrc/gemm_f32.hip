@@ -1,0 +1,468 @@
+// fp32 products of the factorised layer (fp32 operands, fp32 accumulation; no reduced-precision path).
+#include "gemm_f32.h"
+
+namespace fhpc {
+
+typedef __attribute__((ext_vector_type(4))) float f32x4;
+typedef __attribute__((ext_vector_type(16))) float f32x16;
+
+// ---------------------------------------------------------------------------------
+// C[m][n] = sum_k a(m, k) b(n, k) on v_mfma_f32_32x32x2_f32: 256 flop per clock and compute unit, twice what separate
+// fp32 fused multiply-adds reach, and an operand word read from LDS feeds 32 products instead of 4.
+// A workgroup of four waves covers a T x T tile (64: 32 x 32 per wave; 32: the four waves share the tile and take a
+// quarter of every step each, their sums meet in LDS).  Bound by the matrix pipes, which reach 132 .. 142 TFLOP/s
+// from registers alone on this chip: the instruction takes 64 clocks, so L2 -> registers -> LDS keeps up, and what
+// counts is how evenly tiles x slices of the reduction fall on the compute units (plan_gemm_f32) with enough
+// workgroups per unit to hide a step's latency.  (A 128 x 128 tile, 64 x 64 per wave, never came first: two
+// workgroups per unit instead of four; 192 x 3072 over 8192: 136 against 108 microseconds.)
+// 8192 x 192 x 768: 334 microseconds on the vector ALU -> 35; 8192 x 3072 x 192: 149 -> 104 (93 TFLOP/s);
+// 768 x 192 x 8192: 895 -> 41, mostly from cutting the reduction into slices.
+// 32-deep steps; a lane takes four consecutive k at a time (lanes 0 .. 31 the first four of eight, lanes 32 .. 63 the
+// other four), so an operand with k contiguous is one 16-byte LDS read per four instructions.
+// PD steps are in flight in registers ahead of the LDS tile (two LDS buffers, one barrier per step).
+// ---------------------------------------------------------------------------------
+constexpr int F32_BK = 32, F32_PAD_K = 4, F32_PAD_X = 8;
+
+struct GemmF32Args {
+    GemmF32Job job[2];
+};
+
+template <F32Layout L, int T> struct F32Tile {
+    // words of the LDS tile: [row][k] with rows 4 words apart beyond 32, or [k][row] with rows of k 8 words apart
+    // beyond T: neither the 16-byte reads of the one nor the 4-byte reads of the other meet on a bank
+    static constexpr int LD = (L == F32_KC) ? F32_BK + F32_PAD_K : T + F32_PAD_X;
+    static constexpr int WORDS = (L == F32_KC) ? T * LD : F32_BK * LD;
+    static constexpr int PIECES = T * F32_BK / 4 / 256;      // 16-byte pieces per thread and step
+};
+
+template <F32Layout L, int T>
+__device__ __forceinline__ void f32_fetch(f32x4* reg, const float* __restrict__ p, int64_t ld, int x0, int X, int k0, int k_end, bool vec)
+{
+    const int tid = threadIdx.x;
+#pragma unroll
+    for (int i = 0; i < F32Tile<L, T>::PIECES; i++) {
+        const int e = tid + 256 * i;
+        const int x = x0 + (L == F32_KC ? e / (F32_BK / 4) : (e % (T / 4)) * 4);
+        const int k = k0 + (L == F32_KC ? (e % (F32_BK / 4)) * 4 : e / (T / 4));
+        const int64_t at = (L == F32_KC) ? (int64_t)x * ld + k : (int64_t)k * ld + x;
+        f32x4 v = {0.f, 0.f, 0.f, 0.f};
+        if (vec) {
+            // (the contiguous extent is a multiple of four: a piece is inside or outside as a whole)
+            if (x < X && k < k_end) v = *reinterpret_cast<const f32x4*>(p + at);
+        } else {
+#pragma unroll
+            for (int q = 0; q < 4; q++) {
+                const bool in = (L == F32_KC) ? (x < X && k + q < k_end) : (x + q < X && k < k_end);
+                if (in) v[q] = p[at + q];
+            }
+        }
+        reg[i] = v;
+    }
+}
+
+template <F32Layout L, int T>
+__device__ __forceinline__ void f32_put(float* tile, const f32x4* reg)
+{
+    const int tid = threadIdx.x;
+#pragma unroll
+    for (int i = 0; i < F32Tile<L, T>::PIECES; i++) {
+        const int e = tid + 256 * i;
+        const int at = (L == F32_KC) ? (e / (F32_BK / 4)) * F32Tile<L, T>::LD + (e % (F32_BK / 4)) * 4
+                                     : (e / (T / 4)) * F32Tile<L, T>::LD + (e % (T / 4)) * 4;
+        *reinterpret_cast<f32x4*>(tile + at) = reg[i];
+    }
+}
+
+// the lane's four k of eight (chunk c of the step) for row x of the tile
+template <F32Layout L, int T>
+__device__ __forceinline__ f32x4 f32_frag(const float* tile, int x, int c, int half)
+{
+    const int k = 8 * c + 4 * half;
+    if constexpr (L == F32_KC) {
+        return *reinterpret_cast<const f32x4*>(tile + x * F32Tile<L, T>::LD + k);
+    } else {
+        f32x4 v;
+#pragma unroll
+        for (int q = 0; q < 4; q++) v[q] = tile[(k + q) * F32Tile<L, T>::LD + x];
+        return v;
+    }
+}
+
+template <F32Layout AL, F32Layout BL, int T, int PD>
+__global__ __launch_bounds__(256) void gemm_f32_kernel(GemmF32Args args)
+{
+    constexpr int AW = F32Tile<AL, T>::WORDS, BW = F32Tile<BL, T>::WORDS;
+    __shared__ __attribute__((aligned(16))) float lds[2 * (AW + BW)];
+    const int which = ((int)blockIdx.x < args.job[0].items) ? 0 : 1;
+    const GemmF32Job& j = args.job[which];
+    const int item = (int)blockIdx.x - (which ? args.job[0].items : 0);
+    const int per_split = j.items / j.splits;
+    const int split = item / per_split, t = item - split * per_split;
+    const int m0 = t / j.tiles_n * T, n0 = t % j.tiles_n * T;
+    const int k_begin = split * j.k_chunk;
+    const int k_end = (k_begin + j.k_chunk < j.K) ? k_begin + j.k_chunk : j.K;
+    const bool av = j.a_vec != 0, bv = j.b_vec != 0;
+    const int lane = threadIdx.x & 63, half = lane >> 5, i32 = lane & 31;
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int wm = (T == 32) ? 0 : (wave >> 1) * 32, wn = (T == 32) ? 0 : (wave & 1) * 32;
+
+    f32x4 ra[PD][F32Tile<AL, T>::PIECES], rb[PD][F32Tile<BL, T>::PIECES];
+    f32x16 acc;
+#pragma unroll
+    for (int v = 0; v < 16; v++) acc[v] = 0.f;
+
+    const int steps = (k_end - k_begin + F32_BK - 1) / F32_BK;
+#pragma unroll
+    for (int p = 0; p < PD; p++) {
+        // (beyond the last step the pieces are all out of range: zeros, no access)
+        f32_fetch<AL, T>(ra[p], j.a, j.lda, m0, j.M, k_begin + p * F32_BK, k_end, av);
+        f32_fetch<BL, T>(rb[p], j.b, j.ldb, n0, j.N, k_begin + p * F32_BK, k_end, bv);
+    }
+    for (int s0 = 0; s0 < steps; s0 += PD) {
+#pragma unroll
+        for (int p = 0; p < PD; p++) {
+            const int s = s0 + p;
+            if (s < steps) {
+                float* const sa = lds + (s & 1) * (AW + BW);
+                float* const sb = sa + AW;
+                f32_put<AL, T>(sa, ra[p]);
+                f32_put<BL, T>(sb, rb[p]);
+                __syncthreads();
+                f32_fetch<AL, T>(ra[p], j.a, j.lda, m0, j.M, k_begin + (s + PD) * F32_BK, k_end, av);
+                f32_fetch<BL, T>(rb[p], j.b, j.ldb, n0, j.N, k_begin + (s + PD) * F32_BK, k_end, bv);
+#pragma unroll
+                for (int cc = 0; cc < (T == 32 ? 1 : F32_BK / 8); cc++) {
+                    const int c = (T == 32) ? wave : cc;
+                    const f32x4 fa = f32_frag<AL, T>(sa, wm + i32, c, half);
+                    const f32x4 fb = f32_frag<BL, T>(sb, wn + i32, c, half);
+#pragma unroll
+                    for (int q = 0; q < 4; q++) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[q], fb[q], acc, 0, 0, 0);
+                }
+            }
+        }
+    }
+    float* const C = j.c + (int64_t)split * j.slab;
+    // a lane holds column lane % 32 and, of each group of eight rows, four: rows 8 (v / 4) + 4 (lane / 32) + v % 4
+    if constexpr (T == 32) {
+        // the four waves' sums, added in wave order
+        __syncthreads();
+        float* const red = lds;                                       // [wave - 1][v][lane]
+        static_assert(2 * (AW + BW) >= 3 * 16 * 64, "the waves' sums fit the operand buffers");
+        if (wave > 0)
+#pragma unroll
+            for (int v = 0; v < 16; v++) red[((wave - 1) * 16 + v) * 64 + lane] = acc[v];
+        __syncthreads();
+        if (wave > 0) return;
+#pragma unroll
+        for (int v = 0; v < 16; v++)
+            acc[v] = ((acc[v] + red[v * 64 + lane]) + red[(16 + v) * 64 + lane]) + red[(32 + v) * 64 + lane];
+    }
+    const int n = n0 + wn + i32;
+#pragma unroll
+    for (int v = 0; v < 16; v++) {
+        const int m = m0 + wm + 8 * (v >> 2) + 4 * half + (v & 3);
+        if (m < j.M && n < j.N) C[(int64_t)m * j.ldc + n] = acc[v];
+    }
+}
+
+int64_t gemm_f32_slab(int64_t M, int64_t N) { return (M * N + 3) / 4 * 4; }
+
+GemmF32Plan plan_gemm_f32(int jobs, const int64_t* M, const int64_t* N, const int64_t* K, int units, GemmF32Plan* each)
+{
+    // Microseconds a launch should take: what the busiest compute unit multiplies, the steps a workgroup has to walk one
+    // after the other however idle the unit is, and the slabs with their sum.  Fitted to 16 shapes x 11 slice counts:
+    // 192 x 3072 over 8192 takes 255 / 109 / 116 microseconds in 1 / 12 / 32 slices of 64 x 64 tiles (161 / 126 / - on
+    // 32 x 32), 1024 x 64 over 1024 33 / 10.5 / 10.6 in 1 / 8 / 16 (15.6 / 9.2 / 10.6), and the plan is within a tenth of
+    // the best of each row.
+    const int tiles[2] = {64, 32};
+    const double rate[2] = {0.205e6, 0.15e6};      // multiply-adds per microsecond and compute unit
+    const double step[2] = {1.0, 0.375};           // microseconds per 32-deep step of a lone workgroup
+    GemmF32Plan best = {64, 1, 0};
+    double best_cost = -1.0;
+    for (int t = 0; t < 2; t++) {
+        const int64_t T = tiles[t];
+        int64_t count = 0;
+        for (int i = 0; i < jobs; i++) count += ((M[i] + T - 1) / T) * ((N[i] + T - 1) / T);
+        int64_t last = 0;
+        for (int k = 0; k <= 4; k++) {
+            // unsplit, or as many slices as give every compute unit up to k workgroups
+            int64_t s = (k == 0) ? 1 : (int64_t)k * units / count;
+            if (s > 64) s = 64;
+            if (s <= last) continue;
+            last = s;
+            double items = 0.0, work = 0.0, slabs = 0.0;
+            int64_t deepest = 0;
+            bool split = false;
+            GemmF32Plan got[2];
+            for (int i = 0; i < jobs; i++) {
+                const int64_t ksteps = (K[i] + F32_BK - 1) / F32_BK;
+                int64_t c = s < ksteps / 4 ? s : ksteps / 4;          // slices of four steps at least
+                if (c < 1) c = 1;
+                const int64_t per = (ksteps + c - 1) / c;
+                c = (ksteps + per - 1) / per;
+                const int64_t n = ((M[i] + T - 1) / T) * ((N[i] + T - 1) / T) * c;
+                got[i].tile = (int)T;
+                got[i].splits = (int)c;
+                got[i].k_chunk = (int)(per * F32_BK);
+                items += (double)n;
+                work += (double)n * (double)(T * T) * (double)(per * F32_BK);
+                if (per > deepest) deepest = per;
+                if (c > 1) {
+                    split = true;
+                    slabs += (double)c * (double)M[i] * (double)N[i] * 8.0;
+                }
+            }
+            const double rounds = (double)(int64_t)((items + units - 1) / units);
+            double cost = rounds * (work / items) / rate[t];
+            if (cost < (double)deepest * step[t]) cost = (double)deepest * step[t];
+            if (split) cost += 3.0 + slabs / 6.0e6;
+            if (best_cost < 0.0 || cost < best_cost) {
+                best_cost = cost;
+                best = got[0];
+                for (int i = 0; i < jobs && each; i++) each[i] = got[i];
+            }
+        }
+    }
+    return best;
+}
+
+template <F32Layout AL, F32Layout BL>
+static hipError_t launch_layout(const GemmF32Args& a, unsigned blocks, int tile, hipStream_t s)
+{
+    if (tile == 64) hipLaunchKernelGGL((gemm_f32_kernel<AL, BL, 64, 2>), dim3(blocks), dim3(256), 0, s, a);
+    else if (tile == 32) hipLaunchKernelGGL((gemm_f32_kernel<AL, BL, 32, 4>), dim3(blocks), dim3(256), 0, s, a);
+    else return hipErrorInvalidValue;
+    return hipGetLastError();
+}
+
+hipError_t launch_gemm_f32(F32Layout al, F32Layout bl, const GemmF32Job* jobs, int count, int tile, hipStream_t s)
+{
+    if (count < 1 || count > 2) return hipErrorInvalidValue;
+    GemmF32Args a = {};
+    int64_t blocks = 0;
+    for (int i = 0; i < count; i++) {
+        GemmF32Job& j = a.job[i];
+        j = jobs[i];
+        if (j.M < 1 || j.N < 1 || j.K < 1 || j.splits < 1 || j.k_chunk < 1 || (j.k_chunk % F32_BK) != 0) return hipErrorInvalidValue;
+        if ((int64_t)(j.splits - 1) * j.k_chunk >= j.K || (int64_t)j.splits * j.k_chunk < j.K) return hipErrorInvalidValue;
+        const auto vec = [](const float* p, int64_t ld, int64_t extent) {
+            return ld % 4 == 0 && extent % 4 == 0 && reinterpret_cast<uintptr_t>(p) % 16 == 0;
+        };
+        // (a slice's end inside the reduction is a multiple of 32, so only its far end can cut a piece along k)
+        j.a_vec = vec(j.a, j.lda, al == F32_KC ? j.K : j.M);
+        j.b_vec = vec(j.b, j.ldb, bl == F32_KC ? j.K : j.N);
+        j.tiles_n = (j.N + tile - 1) / tile;
+        const int64_t items = (int64_t)((j.M + tile - 1) / tile) * j.tiles_n * j.splits;
+        if (items > 0x3FFFFFFF) return hipErrorInvalidValue;
+        j.items = (int)items;
+        blocks += items;
+    }
+    if (count == 1) a.job[1] = a.job[0];                     // (never reached: the grid ends with job 0)
+    if (al == F32_KC && bl == F32_XC) return launch_layout<F32_KC, F32_XC>(a, (unsigned)blocks, tile, s);
+    if (al == F32_KC && bl == F32_KC) return launch_layout<F32_KC, F32_KC>(a, (unsigned)blocks, tile, s);
+    if (al == F32_XC && bl == F32_XC) return launch_layout<F32_XC, F32_XC>(a, (unsigned)blocks, tile, s);
+    return hipErrorInvalidValue;
+}
+
+// out[i] = sum over s of slabs[s * slab + i], in slab order; one thread per four outputs, the last ones singly.
+// Up to two sums share a launch.  Bound by reading the slabs once.
+struct SumF32Args {
+    SumF32Job job[2];
+};
+__global__ __launch_bounds__(256) void sum_f32_kernel(SumF32Args args)
+{
+    const int which = ((int)blockIdx.x < args.job[0].blocks) ? 0 : 1;
+    const SumF32Job& j = args.job[which];
+    const int64_t block = (int64_t)blockIdx.x - (which ? args.job[0].blocks : 0);
+    const int64_t n4 = (j.n + 3) / 4;
+    for (int64_t i = block * 256 + threadIdx.x; i < n4; i += (int64_t)j.blocks * 256) {
+        f32x4 a = reinterpret_cast<const f32x4*>(j.slabs)[i];
+        for (int s0 = 1; s0 < j.nslab; s0 += 8) {
+            f32x4 b[8];
+#pragma unroll
+            for (int q = 0; q < 8; q++) {
+                const int s = (s0 + q < j.nslab) ? s0 + q : j.nslab - 1;
+                b[q] = reinterpret_cast<const f32x4*>(j.slabs + (int64_t)s * j.slab)[i];
+            }
+#pragma unroll
+            for (int q = 0; q < 8; q++)
+                if (s0 + q < j.nslab) a += b[q];
+        }
+        if (4 * i + 4 <= j.n) reinterpret_cast<f32x4*>(j.out)[i] = a;
+        else
+            for (int q = 0; 4 * i + q < j.n; q++) j.out[4 * i + q] = a[q];
+    }
+}
+
+hipError_t launch_sum_f32(const SumF32Job* jobs, int count, hipStream_t s)
+{
+    if (count < 1 || count > 2) return hipErrorInvalidValue;
+    SumF32Args a = {};
+    unsigned blocks = 0;
+    for (int i = 0; i < count; i++) {
+        a.job[i] = jobs[i];
+        int64_t b = ((jobs[i].n + 3) / 4 + 255) / 256;
+        if (b > 8192) b = 8192;
+        if (b < 1) b = 1;
+        a.job[i].blocks = (int)b;
+        blocks += (unsigned)b;
+    }
+    if (count == 1) a.job[1] = a.job[0];
+    hipLaunchKernelGGL(sum_f32_kernel, dim3(blocks), dim3(256), 0, s, a);
+    return hipGetLastError();
+}
+
+// ---------------------------------------------------------------------------------
+// Two chained fp32 products through a rank that fits a workgroup's LDS (r <= 64):
+//     P[m][j]   = sum_t L[m][t] R(t, j)          R(t, j) = R[t * ldr + j] (F32_XC) or R[j * ldr + t] (F32_KC)
+//     Out[m][c] = sum_j P[m][j] S(j, c)          S(j, c) = S[j * lds + c] (F32_XC) or S[c * lds + j] (F32_KC)
+// Forward of the factorised layer (Sec. 3.2 eq. low_rank_layer): L = X, R = A, S = B gives H = X A and Y = H B; its
+// input gradient: L = dY, R = B, S = A gives dH = dY B^T and dX = dH A^T.
+// With few rows the layer is bound by launches and by the latency of each one's loads, not by arithmetic.  So a
+// workgroup takes 16 rows and 64 or more columns of Out, and every workgroup of a row block forms that block's P for
+// itself: the chip has units to spare and the repeated reads come from L2.  The four waves take every fourth 16-deep
+// step of the reduction on v_mfma_f32_16x16x4_f32, operands straight from memory with CHAIN_AHEAD steps requested at
+// once, and their sums meet in LDS.  The first column block of S is requested before that.
+// ---------------------------------------------------------------------------------
+constexpr int CHAIN_ROWS = 16, CHAIN_RMAX = 64, CHAIN_AHEAD = 4;
+
+template <int NB, F32Layout RL, F32Layout SL>
+__global__ __launch_bounds__(256) void lowrank_chain_f32_kernel(const float* __restrict__ L, int64_t ldl, const float* __restrict__ R, int64_t ldr,
+                                                                const float* __restrict__ S, int64_t lds, float* __restrict__ Out, int64_t ldo,
+                                                                float* __restrict__ P_out, int M, int T, int r, int C, int cols)
+{
+    constexpr int RP = NB * 16;
+    __shared__ float part[4][CHAIN_ROWS][RP + 1];
+    __shared__ __attribute__((aligned(16))) float sP[CHAIN_ROWS][RP + 4];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, i = lane & 15, g = lane >> 4;
+    const int m0 = blockIdx.x * CHAIN_ROWS;
+    const int c_begin = blockIdx.y * cols, c_end = (c_begin + cols < C) ? c_begin + cols : C;
+    const bool svec = (SL == F32_KC) && (r % 4) == 0;
+
+    // S for the 16 columns from c on: lane (i, g) column c + i, ranks 16 b + 4 g .. + 3
+    f32x4 sv[NB];
+    auto fetch_s = [&](int c) __attribute__((always_inline)) {
+        const int cc = c + i;
+#pragma unroll
+        for (int b = 0; b < NB; b++) {
+            const int j = 16 * b + 4 * g;
+            f32x4 v = {0.f, 0.f, 0.f, 0.f};
+            if (SL == F32_KC && svec) {
+                if (cc < c_end && j < r) v = *reinterpret_cast<const f32x4*>(S + (int64_t)cc * lds + j);
+            } else {
+#pragma unroll
+                for (int q = 0; q < 4; q++)
+                    if (cc < c_end && j + q < r) v[q] = S[SL == F32_KC ? (int64_t)cc * lds + j + q : (int64_t)(j + q) * lds + cc];
+            }
+            sv[b] = v;
+        }
+    };
+    fetch_s(c_begin + wave * 16);
+
+    f32x4 acc[NB];
+#pragma unroll
+    for (int b = 0; b < NB; b++) acc[b] = f32x4{0.f, 0.f, 0.f, 0.f};
+    const int m = m0 + i;
+    const float* const Lrow = L + (int64_t)(m < M ? m : 0) * ldl;
+    for (int t0 = wave * 16; t0 < T; t0 += 64 * CHAIN_AHEAD) {
+        f32x4 lv[CHAIN_AHEAD], rv[CHAIN_AHEAD][NB];
+#pragma unroll
+        for (int u = 0; u < CHAIN_AHEAD; u++) {
+            // (T is a multiple of 8 and t of 4: a piece of four is inside or outside as a whole)
+            const int t = t0 + 64 * u + 4 * g;
+            lv[u] = f32x4{0.f, 0.f, 0.f, 0.f};
+            if (m < M && t < T) lv[u] = *reinterpret_cast<const f32x4*>(Lrow + t);
+#pragma unroll
+            for (int b = 0; b < NB; b++) {
+                const int j = 16 * b + i;
+                f32x4 v = {0.f, 0.f, 0.f, 0.f};
+                if (j < r && t < T) {
+                    if constexpr (RL == F32_KC) {
+                        v = *reinterpret_cast<const f32x4*>(R + (int64_t)j * ldr + t);
+                    } else {
+#pragma unroll
+                        for (int q = 0; q < 4; q++) v[q] = R[(int64_t)(t + q) * ldr + j];
+                    }
+                }
+                rv[u][b] = v;
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < CHAIN_AHEAD; u++)
+#pragma unroll
+            for (int q = 0; q < 4; q++)
+#pragma unroll
+                for (int b = 0; b < NB; b++) acc[b] = __builtin_amdgcn_mfma_f32_16x16x4f32(lv[u][q], rv[u][b][q], acc[b], 0, 0, 0);
+    }
+    // a lane holds rank 16 b + i of the rows 4 g .. 4 g + 3
+#pragma unroll
+    for (int b = 0; b < NB; b++)
+#pragma unroll
+        for (int v = 0; v < 4; v++) part[wave][4 * g + v][16 * b + i] = acc[b][v];
+    __syncthreads();
+#pragma unroll
+    for (int e = 0; e < NB; e++) {
+        const int at = tid + 256 * e, row = at / RP, j = at % RP;
+        const float p = ((part[0][row][j] + part[1][row][j]) + part[2][row][j]) + part[3][row][j];
+        sP[row][j] = (j < r) ? p : 0.f;                       // (beyond r an infinity of L times R's zero would be left)
+        if (P_out && blockIdx.y == 0 && m0 + row < M && j < r) P_out[(int64_t)(m0 + row) * r + j] = p;
+    }
+    __syncthreads();
+    for (int c = c_begin + wave * 16; c < c_end; c += 64) {
+        f32x4 out = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int b = 0; b < NB; b++) {
+            const f32x4 p = *reinterpret_cast<const f32x4*>(&sP[i][16 * b + 4 * g]);
+#pragma unroll
+            for (int q = 0; q < 4; q++) out = __builtin_amdgcn_mfma_f32_16x16x4f32(p[q], sv[b][q], out, 0, 0, 0);
+        }
+        if (c + 64 < c_end) fetch_s(c + 64);
+        if (c + i < c_end)
+#pragma unroll
+            for (int v = 0; v < 4; v++)
+                if (m0 + 4 * g + v < M) Out[(int64_t)(m0 + 4 * g + v) * ldo + c + i] = out[v];
+    }
+}
+
+// It pays while forming P over and over costs less than the launches it saves: that cost goes with the reduction T
+// times the rank in blocks of 16 and hardly with M, until there are more row blocks than units.  Measured, one launch
+// against two or three (forward, microseconds): r = 32, 768 -> 768, 256 / 2048 rows 7.1 / 12.9 against 11.8 / 14.5; r = 64 at 256 rows
+// 10.2 against 12.5, at 512 rows 17.1 against 13.0; T = 3072 at r = 32 (backward, 256 rows) 26.3 against 19.3.
+bool lowrank_chain_f32_pays(int64_t M, int64_t T, int64_t r)
+{
+    if (r > CHAIN_RMAX || M > 4096) return false;
+    const int64_t p = T * ((r + 15) / 16 * 16);
+    return p <= (M <= 256 ? 768 * 64 : 768 * 32);
+}
+
+template <int NB>
+static hipError_t launch_chain(const float* L, int64_t ldl, const float* R, int64_t ldr, F32Layout rl, const float* S, int64_t lds, F32Layout sl,
+                               float* Out, int64_t ldo, float* P_out, int M, int T, int r, int C, int cols, dim3 grid, hipStream_t s)
+{
+    if (rl == F32_XC && sl == F32_XC)
+        hipLaunchKernelGGL((lowrank_chain_f32_kernel<NB, F32_XC, F32_XC>), grid, dim3(256), 0, s, L, ldl, R, ldr, S, lds, Out, ldo, P_out, M, T, r, C, cols);
+    else if (rl == F32_KC && sl == F32_KC)
+        hipLaunchKernelGGL((lowrank_chain_f32_kernel<NB, F32_KC, F32_KC>), grid, dim3(256), 0, s, L, ldl, R, ldr, S, lds, Out, ldo, P_out, M, T, r, C, cols);
+    else
+        return hipErrorInvalidValue;
+    return hipGetLastError();
+}
+
+hipError_t launch_lowrank_chain_f32(const float* L, int64_t ldl, const float* R, int64_t ldr, F32Layout rl,
+                                    const float* S, int64_t lds, F32Layout sl, float* Out, int64_t ldo, float* P_out,
+                                    int M, int T, int r, int C, int units, hipStream_t s)
+{
+    if (M < 1 || C < 0 || (C > 0 && !Out) || r < 1 || r > CHAIN_RMAX || (T % 8) != 0 || (ldl % 4) != 0) return hipErrorInvalidValue;
+    if (rl == F32_KC && (ldr % 4) != 0) return hipErrorInvalidValue;
+    const int rows = (M + CHAIN_ROWS - 1) / CHAIN_ROWS, blocks = (C + 63) / 64;
+    int slices = 2 * units / rows;
+    if (slices > blocks) slices = blocks;
+    if (slices < 1) slices = 1;
+    const int per = (C > 0) ? (blocks + slices - 1) / slices : 1;
+    const dim3 grid((unsigned)rows, (unsigned)((C > 0) ? (blocks + per - 1) / per : 1));
+    if (r <= 16) return launch_chain<1>(L, ldl, R, ldr, rl, S, lds, sl, Out, ldo, P_out, M, T, r, C, 64 * per, grid, s);
+    if (r <= 32) return launch_chain<2>(L, ldl, R, ldr, rl, S, lds, sl, Out, ldo, P_out, M, T, r, C, 64 * per, grid, s);
+    return launch_chain<4>(L, ldl, R, ldr, rl, S, lds, sl, Out, ldo, P_out, M, T, r, C, 64 * per, grid, s);
+}
+
+}  // namespace fhpc

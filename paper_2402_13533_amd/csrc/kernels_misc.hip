@@ -1,4 +1,4 @@
-// fp32 GEMM (true fp32 arithmetic), SiLU gate, weight quantise / unpack / dequantise,
+// SiLU gate, weight quantise / unpack / dequantise,
 // and the small copy / convert kernels the entry points use around the GEMM core.
 #include "kernels_misc.h"
 #include "gate_math.h"
@@ -20,171 +20,6 @@ __device__ __forceinline__ uint16_t float_to_bf16_bits(float f)
     v.y = 0.f;
     bf16x2 b = __builtin_convertvector(v, bf16x2);
     return (uint16_t)(__builtin_bit_cast(uint32_t, b) & 0xFFFFu);
-}
-
-// ---------------------------------------------------------------------------------
-// fp32 GEMM with arbitrary strides: C[m,n] = alpha * sum_k A(m,k) B(k,n),
-// A(m,k) = A[m*ars + k*acs], B(k,n) = B[k*brs + n*bcs].  64x64 tile, 16-deep steps,
-// 256 threads, each a 4x4 block of C, plain v_fma_f32 (no reduced-precision path).
-// ---------------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void gemm_f32_kernel(const float* __restrict__ A, int64_t ars, int64_t acs,
-                                                       const float* __restrict__ B, int64_t brs, int64_t bcs,
-                                                       float* __restrict__ C, int64_t ldc, int M, int N, int K, float alpha)
-{
-    __shared__ float sA[16][64 + 4];
-    __shared__ float sB[16][64 + 4];
-    const int tid = threadIdx.x;
-    const int m0 = blockIdx.y * 64, n0 = blockIdx.x * 64;
-    const int tx = tid & 15, ty = tid >> 4;
-    float acc[4][4] = {};
-    // element i of this thread in the A and B tiles: the faster-varying thread index follows the contiguous stride
-    int amm[4], akk[4], bnn[4], bkk[4];
-#pragma unroll
-    for (int i = 0; i < 4; i++) {
-        const int e = tid + 256 * i;
-        if (acs == 1) { akk[i] = e & 15; amm[i] = e >> 4; } else { amm[i] = e & 63; akk[i] = e >> 6; }
-        if (brs == 1) { bkk[i] = e & 15; bnn[i] = e >> 4; } else { bnn[i] = e & 63; bkk[i] = e >> 6; }
-    }
-    // the next 16-deep step's operands are requested before the current step's sums, so that a step does not wait
-    // out a round trip to memory (the products of the fp32 configuration are small: the latency was all they took)
-    float ra[4], rb[4];
-    auto fetch = [&](int k0) __attribute__((always_inline)) {
-#pragma unroll
-        for (int i = 0; i < 4; i++) {
-            const int m = m0 + amm[i], k = k0 + akk[i];
-            ra[i] = (m < M && k < K) ? A[(int64_t)m * ars + (int64_t)k * acs] : 0.f;
-            const int n = n0 + bnn[i], k2 = k0 + bkk[i];
-            rb[i] = (n < N && k2 < K) ? B[(int64_t)k2 * brs + (int64_t)n * bcs] : 0.f;
-        }
-    };
-    fetch(0);
-    for (int k0 = 0; k0 < K; k0 += 16) {
-#pragma unroll
-        for (int i = 0; i < 4; i++) {
-            sA[akk[i]][amm[i]] = ra[i];
-            sB[bkk[i]][bnn[i]] = rb[i];
-        }
-        __syncthreads();
-        if (k0 + 16 < K) fetch(k0 + 16);
-#pragma unroll
-        for (int kk = 0; kk < 16; kk++) {
-            float a[4], b[4];
-#pragma unroll
-            for (int i = 0; i < 4; i++) a[i] = sA[kk][ty * 4 + i];
-#pragma unroll
-            for (int j = 0; j < 4; j++) b[j] = sB[kk][tx * 4 + j];
-#pragma unroll
-            for (int i = 0; i < 4; i++)
-#pragma unroll
-                for (int j = 0; j < 4; j++) acc[i][j] = __builtin_fmaf(a[i], b[j], acc[i][j]);
-        }
-        __syncthreads();
-    }
-#pragma unroll
-    for (int i = 0; i < 4; i++) {
-        const int m = m0 + ty * 4 + i;
-#pragma unroll
-        for (int j = 0; j < 4; j++) {
-            const int n = n0 + tx * 4 + j;
-            if (m < M && n < N) C[(int64_t)m * ldc + n] = alpha * acc[i][j];
-        }
-    }
-}
-
-hipError_t launch_gemm_f32(const float* A, int64_t ars, int64_t acs, const float* B, int64_t brs, int64_t bcs,
-                           float* C, int64_t ldc, int M, int N, int K, float alpha, hipStream_t s)
-{
-    if (M <= 0 || N <= 0) return hipSuccess;
-    dim3 grid((unsigned)((N + 63) / 64), (unsigned)((M + 63) / 64));
-    hipLaunchKernelGGL(gemm_f32_kernel, grid, dim3(256), 0, s, A, ars, acs, B, brs, bcs, C, ldc, M, N, K, alpha);
-    return hipGetLastError();
-}
-
-// ---------------------------------------------------------------------------------
-// Two chained fp32 products through a rank that fits a workgroup's LDS (r <= 64):
-//     P[m][j]   = sum_t L[m][t] R(t, j)          R(t, j) = R[t * rrs + j * rcs]
-//     Out[m][c] = sum_j P[m][j] S(j, c)          S(j, c) = S[j * srs + c * scs]
-// for 16 rows m per workgroup.  Forward of the factorised layer (Sec. 3.2 eq. low_rank_layer): L = X, R = A,
-// S = B gives H = X A and Y = H B; its input gradient: L = dY, R = B (transposed through the strides),
-// S = A gives dH = dY B^T and dX = dH A^T.  The rank-r intermediate stays in LDS between the two
-// products (it is also stored to P_out when the caller wants it: H for the backward pass, dH for dA); each
-// sum runs in index order, in fp32.
-// ---------------------------------------------------------------------------------
-constexpr int CHAIN_ROWS = 16, CHAIN_TC = 64, CHAIN_RMAX = 64;
-
-__global__ __launch_bounds__(256) void lowrank_chain_f32_kernel(const float* __restrict__ L, int64_t ldl,
-                                                                const float* __restrict__ R, int64_t rrs, int64_t rcs,
-                                                                const float* __restrict__ S, int64_t srs, int64_t scs,
-                                                                float* __restrict__ Out, int64_t ldo, float* __restrict__ P_out,
-                                                                int M, int T, int r, int C)
-{
-    __shared__ float sL[CHAIN_ROWS][CHAIN_TC + 1];
-    __shared__ float sR[CHAIN_TC][CHAIN_RMAX + 1];
-    __shared__ float sP[CHAIN_ROWS][CHAIN_RMAX + 1];
-    const int tid = threadIdx.x;
-    const int m0 = blockIdx.x * CHAIN_ROWS;
-    const int row = tid >> 4, jg = tid & 15;          // thread: one row, the ranks jg, jg + 16, jg + 32, jg + 48
-    float h[4] = {0.f, 0.f, 0.f, 0.f};
-    for (int t0 = 0; t0 < T; t0 += CHAIN_TC) {
-        // the rows' next 64 elements (contiguous along t) ...
-#pragma unroll
-        for (int i = 0; i < CHAIN_ROWS * CHAIN_TC / 256; i++) {
-            const int e = tid + 256 * i, rr = e / CHAIN_TC, tt = e % CHAIN_TC;
-            const int m = m0 + rr, t = t0 + tt;
-            sL[rr][tt] = (m < M && t < T) ? L[(int64_t)m * ldl + t] : 0.f;
-        }
-        // ... and the 64 x r piece of R, read along whichever of its indices is contiguous
-        for (int e = tid; e < CHAIN_TC * r; e += 256) {
-            int tt, j;
-            if (rcs == 1) { tt = e / r; j = e - tt * r; } else { j = e / CHAIN_TC; tt = e - j * CHAIN_TC; }
-            const int t = t0 + tt;
-            sR[tt][j] = (t < T) ? R[(int64_t)t * rrs + (int64_t)j * rcs] : 0.f;
-        }
-        __syncthreads();
-#pragma unroll 8
-        for (int tt = 0; tt < CHAIN_TC; tt++) {
-            const float x = sL[row][tt];
-#pragma unroll
-            for (int c = 0; c < 4; c++) h[c] = __builtin_fmaf(x, sR[tt][jg + 16 * c], h[c]);     // (ranks beyond r: zero columns of sR are never read back)
-        }
-        __syncthreads();
-    }
-#pragma unroll
-    for (int c = 0; c < 4; c++) {
-        const int j = jg + 16 * c;
-        if (j < r) {
-            sP[row][j] = h[c];
-            if (P_out && m0 + row < M) P_out[(int64_t)(m0 + row) * r + j] = h[c];
-        }
-    }
-    __syncthreads();
-    // second product: a thread owns output columns c = tid, tid + 256, ... for all 16 rows
-    for (int c = tid; c < C; c += 256) {
-        float acc[CHAIN_ROWS];
-#pragma unroll
-        for (int rr = 0; rr < CHAIN_ROWS; rr++) acc[rr] = 0.f;
-        for (int j = 0; j < r; j++) {
-            const float b = S[(int64_t)j * srs + (int64_t)c * scs];
-#pragma unroll
-            for (int rr = 0; rr < CHAIN_ROWS; rr++) acc[rr] = __builtin_fmaf(sP[rr][j], b, acc[rr]);
-        }
-#pragma unroll
-        for (int rr = 0; rr < CHAIN_ROWS; rr++)
-            if (m0 + rr < M) Out[(int64_t)(m0 + rr) * ldo + c] = acc[rr];
-    }
-}
-
-bool lowrank_chain_f32_supports(int64_t r) { return r >= 1 && r <= CHAIN_RMAX; }
-
-hipError_t launch_lowrank_chain_f32(const float* L, int64_t ldl, const float* R, int64_t rrs, int64_t rcs,
-                                    const float* S, int64_t srs, int64_t scs, float* Out, int64_t ldo, float* P_out,
-                                    int M, int T, int r, int C, hipStream_t s)
-{
-    if (M <= 0 || C <= 0) return hipSuccess;
-    if (!lowrank_chain_f32_supports(r)) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(lowrank_chain_f32_kernel, dim3((unsigned)((M + CHAIN_ROWS - 1) / CHAIN_ROWS)), dim3(256), 0, s,
-                       L, ldl, R, rrs, rcs, S, srs, scs, Out, ldo, P_out, M, T, r, C);
-    return hipGetLastError();
 }
 
 // ---------------------------------------------------------------------------------

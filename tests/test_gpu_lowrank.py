@@ -42,6 +42,52 @@ def test_config1_fp32():
 
 
 @pytest.mark.parametrize("M,K,r,N", [
+    (16, 48, 16, 64),        # chain: whole 16-row, 16-rank and 64-column blocks
+    (17, 1032, 17, 72),      # chain: one row, one rank and eight columns beyond; a reduction that ends half-way through a step
+    (257, 512, 48, 520),     # chain: more rows than 256 at the largest product of reduction and rank taken there
+    (257, 520, 48, 512),     # ... one beyond it: products of their own in one direction, a chain in the other
+    (65, 3080, 66, 264),     # products: rank not a multiple of four (single-word loads), the reduction in slices
+    (1030, 264, 129, 776),   # products: odd rank, ragged tiles of 64 and 32
+    (4100, 136, 24, 4104),   # products: a rank the chain would hold, too many rows; gradients in many slices
+    (2049, 72, 192, 200),    # products: reductions that end inside a 32-deep step
+])
+def test_fp32_products_and_chain(M, K, r, N):
+    """The fp32 matrix-core products (two tile sizes, whole and sliced reductions, 16-byte and single-word loads) and the
+    chained pair at the edges of the rule between them, against the oracle; H saved and recomputed have the same bits."""
+    import torch
+    fhpc = _fhpc()
+    X, A, B, dY = lowrank_inputs(3, M, K, r, N, bf16=False)
+    Yr, Hr = oracle.lowrank_fwd(X, A, B)
+    ref = (Yr,) + oracle.lowrank_bwd(X, A, B, dY)
+    Xd, Ad, Bd, dYd = (torch.from_numpy(a).cuda() for a in (X, A, B, dY))
+    guard = Guarded()
+    g = [guard.alloc(s, torch.float32) for s in ((M, N), (M, r), (M, K), (K, r), (r, N))]
+    Y, H = fhpc.lowrank_linear_fwd(Xd, Ad, Bd, Y=g[0], H_out=g[1])
+    assert parity_err(from_device(H), Hr, TOL_F32, "H") <= TOL_F32
+    out = fhpc.lowrank_linear_bwd(Xd, Ad, Bd, dYd, H_saved=H, dX=g[2], dA=g[3], dB=g[4])
+    _check_all("f32 %s" % ((M, K, r, N),), (Y,) + out, ref, TOL_F32)
+    guard.check("f32 %s" % ((M, K, r, N),))
+    again = fhpc.lowrank_linear_bwd(Xd, Ad, Bd, dYd)                  # H recomputed
+    assert all(torch.equal(a, b) for a, b in zip(out, again))
+
+
+@pytest.mark.parametrize("M,K,r,N", [(20, 72, 5, 40), (300, 1032, 70, 40)])      # the chain; products of their own
+def test_fp32_infinities_stay_in_their_row(M, K, r, N):
+    """An infinite input makes its own token's outputs infinite or NaN exactly where IEEE arithmetic says, and nothing
+    else: what pads ranks, rows and reductions to the blocks of the matrix instructions must not meet it."""
+    import torch
+    fhpc = _fhpc()
+    X, A, B, _ = lowrank_inputs(3, M, K, r, N, bf16=False)
+    A, B = np.abs(A) + 0.1, np.abs(B) + 0.1
+    X[3, 7] = np.inf
+    Y, H = fhpc.lowrank_linear_fwd(*(torch.from_numpy(a).cuda() for a in (X, A, B)), save_H=True)
+    for got, cols in ((H, r), (Y, N)):
+        got = got.cpu().numpy()
+        assert np.all(got[3] == np.inf) and got.shape[1] == cols
+        assert np.all(np.isfinite(np.delete(got, 3, 0)))
+
+
+@pytest.mark.parametrize("M,K,r,N", [
     (50, 136, 5, 72),        # ragged token count and rank (K and N are multiples of 8 by contract); one launch per chain: H and dH stay in LDS
     (33, 64, 64, 264),       # the largest rank that fits, a ragged row block, more columns than threads
     (17, 200, 65, 96),       # one rank beyond: two launches per chain
