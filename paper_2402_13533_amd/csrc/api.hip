@@ -893,7 +893,8 @@ struct DecompScratch {
     void* Gb;      // bf16 [r][r]
     void* G2b;     // bf16 [r][r]
     void* Sb;      // bf16 [r][r]
-    float* Mf[6];  // fp32 [r][r] each: the r x r iteration of orthonormalise
+    float* Mf[5];  // fp32 [r][r] each: the r x r iteration of orthonormalise
+    float* inv_trace;
     float* T;      // fp32 [r][N]
     void* Tb;      // bf16 [r][N]
     void* Cb;      // bf16 [r][N]
@@ -914,7 +915,8 @@ DecompScratch carve_decompose(Carver& c, int64_t K, int64_t r, int64_t N)
     d.Gb = c.take(r * r * 2);
     d.G2b = c.take(r * r * 2);
     d.Sb = c.take(r * r * 2);
-    for (int i = 0; i < 6; i++) d.Mf[i] = static_cast<float*>(c.take(r * r * 4));
+    for (int i = 0; i < 5; i++) d.Mf[i] = static_cast<float*>(c.take(r * r * 4));
+    d.inv_trace = static_cast<float*>(c.take(4));
     d.T = static_cast<float*>(c.take(r * N * 4));
     d.Tb = c.take(r * N * 2);
     d.Cb = c.take(r * N * 2);
@@ -941,12 +943,6 @@ int product_tn_bf16(GemmOperand a, GemmOperand b, void* P, int64_t M, int64_t n,
     return FHPC_OK;
 }
 
-// fp32 r x r product C = A B (transpose_a: C = A^T B): fp32 operands and accumulation on the matrix cores
-hipError_t small_mm(const float* A, bool transpose_a, const float* B, float* C, int64_t r, hipStream_t st)
-{
-    return launch_mm_f32(A, transpose_a, r, B, r, C, r, r, r, r, st);
-}
-
 // Columns of Y[R][r] (bf16) replaced by an orthonormal basis of their span: out = Y M with an r x r
 // matrix M built by products only.  The iteration  Q <- Q (a I + b G + c G^2),  G = Q^T Q,  is run on M
 // alone: with G0 = Y^T Y (one product over the long dimension, fp32) the Gram matrix of Q = Y M is
@@ -965,30 +961,31 @@ int orthonormalise(const void* Y, void* out, int64_t R, int64_t r, int quintic, 
     float* Mn = d.Mf[1];
     float* const P = d.Mf[2];
     float* const Gi = d.Mf[3];
-    float* const G2 = d.Mf[4];
-    float* const S = d.Mf[5];
+    float* const S = d.Mf[4];
+    const float kQ[3] = {3.4445f, -4.7750f, 2.0315f};               // quintic a, b, c
+    const SquareEpilogue plain;
     FHPC_HIP(gemm_split_f32(OP_XC, OP_XC, operand(Y, r), operand(Y, r), G0, r, r, r, R, 1.f, d.part, run));
-    for (int i = 0; i < quintic + cubic; i++) {
-        const bool first = (i == 0), q5 = (i < quintic);
-        const float* g = G0;
-        if (!first) {
-            FHPC_LAUNCH(run, small_mm(G0, false, M, P, r, st));            // P = G0 M
-            FHPC_LAUNCH(run, small_mm(M, true, P, Gi, r, st));             // Gi = M^T G0 M
-            g = Gi;
-        }
-        float* dst = first ? M : S;                                 // the first step's polynomial is M itself
-        if (q5) {
-            // the first step works on G0 / trace: Gi = that, G2 its square
-            if (first) FHPC_LAUNCH(run, launch_gram_poly(G0, nullptr, Gi, false, r, 0.f, 1.f, 0.f, 1, st));
-            FHPC_LAUNCH(run, small_mm(first ? Gi : g, false, first ? Gi : g, G2, r, st));
-            FHPC_LAUNCH(run, launch_gram_poly(g, G2, dst, false, r, 3.4445f, -4.7750f, 2.0315f, first ? 2 : 0, st));
+    // the first step's Gram matrix is Gi = G0 / trace, and its polynomial times sqrt(1 / trace) is M itself
+    FHPC_LAUNCH(run, launch_gram_scale(G0, Gi, d.inv_trace, r, st));
+    SquareEpilogue poly;
+    poly.poly = true;
+    poly.scale = kQ[2]; poly.diag = kQ[0]; poly.add_scale = kQ[1]; poly.add = G0; poly.inv_trace = d.inv_trace;
+    FHPC_LAUNCH(run, launch_square_f32(Gi, false, Gi, M, r, poly, st));
+    poly.add = Gi;
+    poly.inv_trace = nullptr;
+    for (int i = 1; i < quintic + cubic; i++) {
+        FHPC_LAUNCH(run, launch_square_f32(G0, false, M, P, r, plain, st));                // P = G0 M
+        if (i < quintic) {
+            FHPC_LAUNCH(run, launch_square_f32(M, true, P, Gi, r, plain, st));             // Gi = M^T G0 M
+            FHPC_LAUNCH(run, launch_square_f32(Gi, false, Gi, S, r, poly, st));            // S = a I + b Gi + c Gi^2
         } else {
-            FHPC_LAUNCH(run, launch_gram_poly(g, nullptr, dst, false, r, 1.5f, -0.5f, 0.f, first ? 2 : 0, st));
+            SquareEpilogue lin;
+            lin.poly = true;
+            lin.scale = -0.5f; lin.diag = 1.5f;
+            FHPC_LAUNCH(run, launch_square_f32(M, true, P, S, r, lin, st));                // S = 1.5 I - 0.5 M^T G0 M
         }
-        if (!first) {
-            FHPC_LAUNCH(run, small_mm(M, false, S, Mn, r, st));            // M <- M S
-            float* t = M; M = Mn; Mn = t;
-        }
+        FHPC_LAUNCH(run, launch_square_f32(M, false, S, Mn, r, plain, st));                // M <- M S
+        float* t = M; M = Mn; Mn = t;
     }
     FHPC_LAUNCH(run, launch_compact_f32(M, r, d.Sb, r, r, r, 1.f, true, st));
     FHPC_HIP(gemm_plain(OP_KC, OP_XC, operand(Y, r), operand(d.Sb, r), out, r, R, r, r, run));
@@ -1948,7 +1945,7 @@ static int seq_decompose(Run& run, const DecompScratch& d, const void* W, const 
         const GemmOperand a = operand(Al, r);
         FHPC_HIP(gemm_split_f32(OP_XC, OP_XC, a, w, d.T, N, r, N, K, 1.f, d.part, run));
         FHPC_HIP(gemm_split_f32(OP_XC, OP_XC, a, a, d.G, r, r, r, K, 1.f, d.part, run));
-        FHPC_LAUNCH(run, launch_gram_poly(d.G, nullptr, d.Gb, true, r, -1.f, 1.f, 0.f, 0, st));        // Gb = E = G - I
+        FHPC_LAUNCH(run, launch_minus_identity(d.G, d.Gb, r, st));        // Gb = E = G - I
         FHPC_HIP(gemm_plain(OP_KC, OP_XC, operand(d.Gb, r), operand(d.Gb, r), d.G2b, r, r, r, r, run));   // E^2
         FHPC_HIP(gemm_plain(OP_KC, OP_XC, operand(d.G2b, r), operand(d.Gb, r), d.Sb, r, r, r, r, run));   // E^3
         FHPC_LAUNCH(run, launch_neumann(d.G, d.G2b, d.Sb, d.Gb, r, st));                               // Gb = -E + E^2 - E^3

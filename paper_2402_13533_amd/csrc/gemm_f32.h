@@ -46,4 +46,16 @@ hipError_t launch_lowrank_chain_f32(const float* L, int64_t ldl, const float* R,
                                     const float* S, int64_t lds, F32Layout sl, float* Out, int64_t ldo, float* P_out,
                                     int M, int T, int r, int C, int units, hipStream_t s);
 
+// The r x r products of the rank-r factorisation, C = A' B with A' = A or A^T (all r x r, row-major, r a multiple of 8),
+// with the polynomial step that follows in the same launch when `poly` is set:
+//   C = post * (diag I + pre add_scale Add + scale A' B),   pre = *inv_trace and post = sqrt(pre) when inv_trace is given,
+// 1 otherwise; Add may be NULL.  C may not alias an input.
+struct SquareEpilogue {
+    bool poly = false;
+    float scale = 1.f, diag = 0.f, add_scale = 0.f;
+    const float* add = nullptr;
+    const float* inv_trace = nullptr;
+};
+hipError_t launch_square_f32(const float* A, bool transpose_a, const float* B, float* C, int64_t r, const SquareEpilogue& e, hipStream_t s);
+
 }  // namespace fhpc

@@ -1,5 +1,6 @@
 // fp32 products of the factorised layer (fp32 operands, fp32 accumulation; no reduced-precision path).
 #include "gemm_f32.h"
+#include "gemm_ring.h"
 
 namespace fhpc {
 
@@ -463,6 +464,142 @@ hipError_t launch_lowrank_chain_f32(const float* L, int64_t ldl, const float* R,
     if (r <= 16) return launch_chain<1>(L, ldl, R, ldr, rl, S, lds, sl, Out, ldo, P_out, M, T, r, C, 64 * per, grid, s);
     if (r <= 32) return launch_chain<2>(L, ldl, R, ldr, rl, S, lds, sl, Out, ldo, P_out, M, T, r, C, 64 * per, grid, s);
     return launch_chain<4>(L, ldl, R, ldr, rl, S, lds, sl, Out, ldo, P_out, M, T, r, C, 64 * per, grid, s);
+}
+
+// ---------------------------------------------------------------------------------
+// Square products of a few hundred rows in a long dependent chain (the factorisation's orthonormalisation: some forty
+// per orthonormalisation).  What counts is the latency of one launch.  A wave owns a 16 x 16 block (512 x 512 is then
+// one wave per SIMD of the chip) and the whole reduction, in index order, on v_mfma_f32_16x16x4_f32; up to 512 of the
+// reduction are requested into LDS at once (128 KB a workgroup, no registers, no code to speak of) and multiplied from
+// the first half's arrival on.  The polynomial that the iteration applies next is formed on the way out.
+// The matrix instructions of a block are a dependent chain of r / 4 (2.9 microseconds at r = 512), and a launch that
+// does nothing takes 2.5; 512 x 512 x 512 takes 6.1.  The same sums from sixteen barriered steps through registers:
+// 13, and 4.7 for a launch of the polynomial's own; operands straight into registers, no LDS: 8.3 .. 9.4, and the
+// unrolled loop that needs costs 3 .. 10 microseconds of instruction fetch per launch.
+// ---------------------------------------------------------------------------------
+// HALVES: 256-deep pieces held at once; two up to r = 512, where every compute unit has one workgroup, one beyond, so
+// that two workgroups share a unit (r = 1032: 46 microseconds against 61, r = 520: 9.7 against 12.9).
+constexpr int SQ_LDX = 32;
+
+template <bool TRANSPOSE_A, int HALVES>
+__global__ __launch_bounds__(256) void square_f32_kernel(const float* __restrict__ A, const float* __restrict__ B, float* __restrict__ C,
+                                                         int r, SquareEpilogue e)
+{
+    constexpr int SQ_K = 256 * HALVES;
+    // words between two rows of A in LDS: the 16 rows x 4 k of one operand read fall on 64 different banks
+    constexpr int SQ_LDA = SQ_K + 4;
+    constexpr int AWORDS = TRANSPOSE_A ? SQ_K * SQ_LDX : 32 * SQ_LDA;
+    __shared__ __attribute__((aligned(16))) float lds[AWORDS + SQ_K * SQ_LDX];
+    float* const sa = lds;
+    float* const sb = lds + AWORDS;
+    const int lane = threadIdx.x & 63, g = lane >> 4, i = lane & 15;
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int m0 = blockIdx.y * 32, n0 = blockIdx.x * 32;
+    const uint32_t ld = 4u * (uint32_t)r;                          // bytes of a row
+    const ring::u32x4 ra = ring::make_rsrc(A, (uint32_t)r * ld), rb = ring::make_rsrc(B, (uint32_t)r * ld);
+    const uint32_t la = ring::lds_addr(sa), lb = ring::lds_addr(sb);
+    // One request fills 1 KB: 256 k of a row of A, or 8 k of 32 columns.  What lies beyond the matrix arrives as zeros;
+    // what lies beyond a row of it (k >= r, or a ragged column tile) is the next row and enters no product that is stored.
+    // (uint32 offsets: r < 2^15)
+    auto request = [&](int k0, int h) __attribute__((always_inline)) {
+#pragma unroll 1
+        for (int q = 0; q < 8; q++) {
+            const int u = wave * 8 + q;                            // of 32
+            const int k = 256 * h + 8 * u;                         // (the 8 k of a request for columns)
+            if constexpr (TRANSPOSE_A) {
+                ring::dma_16B(ra, la + (uint32_t)(k * SQ_LDX * 4), (uint32_t)(k0 + k + lane / 8) * ld + 4u * (m0 + 4 * (lane % 8)));
+            } else {
+                ring::dma_16B(ra, la + (uint32_t)((u * SQ_LDA + 256 * h) * 4), (uint32_t)(m0 + u) * ld + 4u * (k0 + 256 * h + 4 * lane));
+            }
+            ring::dma_16B(rb, lb + (uint32_t)(k * SQ_LDX * 4), (uint32_t)(k0 + k + lane / 8) * ld + 4u * (n0 + 4 * (lane % 8)));
+        }
+    };
+    const int wm = (wave >> 1) * 16, wn = (wave & 1) * 16;
+    // this lane's operand words at k = 0 (row wm + i or column wn + i, k = g) and their distance for four k
+    const float* const pa = TRANSPOSE_A ? sa + g * SQ_LDX + wm + i : sa + (wm + i) * SQ_LDA + g;
+    const float* const pb = sb + g * SQ_LDX + wn + i;
+    constexpr int DA = TRANSPOSE_A ? 4 * SQ_LDX : 4, DB = 4 * SQ_LDX;
+    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+    auto multiply = [&](int kb, int ke) __attribute__((always_inline)) {
+        // two sets of 8 operand pairs: the next set is read while the current one is multiplied
+        float a[2][8], b[2][8];
+        auto read = [&](int s, int k) __attribute__((always_inline)) {
+#pragma unroll
+            for (int q = 0; q < 8; q++) {
+                a[s][q] = pa[(k / 4 + q) * DA];                    // (beyond ke: read, not used; inside the buffer)
+                b[s][q] = pb[(k / 4 + q) * DB];
+            }
+        };
+        read(0, kb);
+        for (int k = kb; k < ke; k += 64) {
+#pragma unroll
+            for (int s = 0; s < 2; s++) {
+                const int kk = k + 32 * s;
+                if (kk + 32 < ke) read(s ^ 1, kk + 32);
+                if (kk + 32 <= ke) {
+#pragma unroll
+                    for (int q = 0; q < 8; q++) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a[s][q], b[s][q], acc, 0, 0, 0);
+                } else {
+#pragma unroll
+                    for (int q = 0; q < 8; q += 2)                 // (r is a multiple of 8)
+                        if (kk + 4 * q < ke) {
+                            acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a[s][q], b[s][q], acc, 0, 0, 0);
+                            acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a[s][q + 1], b[s][q + 1], acc, 0, 0, 0);
+                        }
+                }
+            }
+        }
+    };
+    for (int k0 = 0; k0 < r; k0 += SQ_K) {
+        const int kc = (r - k0 < SQ_K) ? r - k0 : SQ_K;
+        if (k0) ring::wg_barrier();                                // (every wave has read the previous piece)
+        request(k0, 0);
+        if constexpr (HALVES == 2)
+            if (kc > 256) {
+                request(k0, 1);
+                FHPC_WAIT_VM(16);                                  // the first half's 16 requests of this wave
+                ring::wg_barrier();
+                multiply(0, 256);
+            }
+        FHPC_WAIT_VM(0);
+        ring::wg_barrier();
+        multiply(HALVES == 2 && kc > 256 ? 256 : 0, kc);
+    }
+    float post = 1.f, as = e.add_scale;
+    if (e.inv_trace) {
+        const float inv = *e.inv_trace;
+        as *= inv;
+        post = sqrtf(inv);
+    }
+    // a lane holds column i of the rows 4 g .. 4 g + 3
+#pragma unroll
+    for (int v = 0; v < 4; v++) {
+        const int mo = m0 + wm + 4 * g + v, no = n0 + wn + i;
+        if (mo < r && no < r) {
+            float o = acc[v];
+            if (e.poly) {
+                o = e.add ? as * e.add[(int64_t)mo * r + no] + e.scale * o : e.scale * o;
+                if (mo == no) o += e.diag;
+                o *= post;
+            }
+            C[(int64_t)mo * r + no] = o;
+        }
+    }
+}
+
+hipError_t launch_square_f32(const float* A, bool transpose_a, const float* B, float* C, int64_t r, const SquareEpilogue& e, hipStream_t s)
+{
+    if (r < 8 || (r % 8) != 0 || r >= (1 << 15)) return hipErrorInvalidValue;
+    const unsigned t = (unsigned)((r + 31) / 32);
+    const dim3 grid(t, t), block(256);
+    if (r <= 512) {
+        if (transpose_a) hipLaunchKernelGGL((square_f32_kernel<true, 2>), grid, block, 0, s, A, B, C, (int)r, e);
+        else hipLaunchKernelGGL((square_f32_kernel<false, 2>), grid, block, 0, s, A, B, C, (int)r, e);
+    } else {
+        if (transpose_a) hipLaunchKernelGGL((square_f32_kernel<true, 1>), grid, block, 0, s, A, B, C, (int)r, e);
+        else hipLaunchKernelGGL((square_f32_kernel<false, 1>), grid, block, 0, s, A, B, C, (int)r, e);
+    }
+    return hipGetLastError();
 }
 
 }  // namespace fhpc

@@ -30,11 +30,9 @@ hipError_t launch_tall_skinny_kc(const void* L, int64_t ldl, const void* R, int6
 bool sum_slabs_is_small(int64_t n, int nslab);
 hipError_t launch_sum_slabs_pair(const float* slabs0, int64_t n0, int nslab0, float* out0,
                                  const float* slabs1, int64_t n1, int nslab1, float* out1, hipStream_t s);
-// C = A' B in fp32 on the matrix cores, A' = A or A^T; dimensions multiples of 4, rows 16-byte aligned
-hipError_t launch_mm_f32(const float* A, bool transpose_a, int64_t lda, const float* B, int64_t ldb, float* C, int64_t ldc,
-                         int64_t M, int64_t N, int64_t K, hipStream_t s);
 // r x r helpers of the rank-r factorisation (see kernels_misc.hip)
-hipError_t launch_gram_poly(const float* G, const float* G2, void* out, bool to_bf16, int64_t r, float a, float b, float c, int mode, hipStream_t s);
+hipError_t launch_gram_scale(const float* G, float* out, float* inv_trace, int64_t r, hipStream_t s);
+hipError_t launch_minus_identity(const float* G, void* out, int64_t r, hipStream_t s);
 hipError_t launch_neumann(const float* G, const void* E2, const void* E3, void* out, int64_t r, hipStream_t s);
 hipError_t launch_add_f32_bf16(const float* a, const void* b, void* out, int64_t n, hipStream_t s);
 hipError_t launch_zero(void* p, int64_t bytes, hipStream_t s);

@@ -694,67 +694,6 @@ __global__ __launch_bounds__(256) void zero_u32_kernel(uint32_t* __restrict__ p,
 // with matrix products only: every step is "Gram matrix -> polynomial of it -> product").
 // ---------------------------------------------------------------------------------
 
-// C[M][N] = A' B in fp32 on the matrix cores (v_mfma_f32_16x16x4_f32: fp32 operands, fp32 accumulation),
-// A' = A (M x K, row-major) or A^T (A is K x M), B is K x N; all dimensions multiples of 4, rows 16-byte
-// aligned.  The matrices here are a few hundred rows, so the tile is small on purpose: a workgroup covers
-// 32 x 32 of the output with one 16 x 16 block per wave (a 512 x 512 product is then 1024 waves, one per
-// SIMD of the chip, instead of 256 that each work four times as long).  32-deep steps are staged in LDS
-// with the reduction index outermost, so that the 16 lanes of an operand read are consecutive floats; the
-// row stride of 48 floats keeps the four k rows of one read on different banks.
-constexpr int MMF_T = 32, MMF_K = 32, MMF_LD = 48;
-template <bool TRANSPOSE_A>
-__global__ __launch_bounds__(256) void mm_f32_kernel(const float* __restrict__ A, int lda, const float* __restrict__ B, int ldb,
-                                                     float* __restrict__ C, int ldc, int M, int N, int K)
-{
-    typedef __attribute__((ext_vector_type(4))) float f32x4;
-    __shared__ __attribute__((aligned(16))) float As[MMF_K][MMF_LD];
-    __shared__ __attribute__((aligned(16))) float Bs[MMF_K][MMF_LD];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int m0 = blockIdx.y * MMF_T, n0 = blockIdx.x * MMF_T;
-    const int wm = (wave >> 1) * 16, wn = (wave & 1) * 16;
-    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-    for (int k0 = 0; k0 < K; k0 += MMF_K) {
-        // 32 x 32 floats of each operand: 256 pieces of four, one per thread
-        f32x4 a = {0.f, 0.f, 0.f, 0.f}, b = {0.f, 0.f, 0.f, 0.f};
-        if constexpr (TRANSPOSE_A) {
-            const int k = tid >> 3, m = (tid & 7) * 4;                      // A[k][m .. m+3]
-            if (k0 + k < K && m0 + m < M) a = *reinterpret_cast<const f32x4*>(A + (int64_t)(k0 + k) * lda + m0 + m);
-            *reinterpret_cast<f32x4*>(&As[k][m]) = a;
-        } else {
-            const int m = tid >> 3, k = (tid & 7) * 4;                      // A[m][k .. k+3]
-            if (m0 + m < M && k0 + k < K) a = *reinterpret_cast<const f32x4*>(A + (int64_t)(m0 + m) * lda + k0 + k);
-            As[k][m] = a.x; As[k + 1][m] = a.y; As[k + 2][m] = a.z; As[k + 3][m] = a.w;
-        }
-        const int kb = tid >> 3, n = (tid & 7) * 4;                         // B[k][n .. n+3]
-        if (k0 + kb < K && n0 + n < N) b = *reinterpret_cast<const f32x4*>(B + (int64_t)(k0 + kb) * ldb + n0 + n);
-        *reinterpret_cast<f32x4*>(&Bs[kb][n]) = b;
-        __syncthreads();
-#pragma unroll
-        for (int kk = 0; kk < MMF_K; kk += 4) {
-            const float av = As[kk + (lane >> 4)][wm + (lane & 15)];
-            const float bv = Bs[kk + (lane >> 4)][wn + (lane & 15)];
-            acc = __builtin_amdgcn_mfma_f32_16x16x4f32(av, bv, acc, 0, 0, 0);
-        }
-        __syncthreads();
-    }
-    // lane holds column wn + lane % 16, rows wm + 4 (lane / 16) .. + 3
-    const int n = n0 + wn + (lane & 15);
-#pragma unroll
-    for (int v = 0; v < 4; v++) {
-        const int m = m0 + wm + 4 * (lane >> 4) + v;
-        if (m < M && n < N) C[(int64_t)m * ldc + n] = acc[v];
-    }
-}
-
-hipError_t launch_mm_f32(const float* A, bool transpose_a, int64_t lda, const float* B, int64_t ldb, float* C, int64_t ldc,
-                         int64_t M, int64_t N, int64_t K, hipStream_t s)
-{
-    const dim3 grid((unsigned)((N + MMF_T - 1) / MMF_T), (unsigned)((M + MMF_T - 1) / MMF_T));
-    if (transpose_a) hipLaunchKernelGGL(mm_f32_kernel<true>, grid, dim3(256), 0, s, A, (int)lda, B, (int)ldb, C, (int)ldc, (int)M, (int)N, (int)K);
-    else hipLaunchKernelGGL(mm_f32_kernel<false>, grid, dim3(256), 0, s, A, (int)lda, B, (int)ldb, C, (int)ldc, (int)M, (int)N, (int)K);
-    return hipGetLastError();
-}
-
 // trace of an r x r fp32 matrix, summed by one workgroup in a fixed order
 __device__ __forceinline__ float block_trace(const float* __restrict__ G, int r)
 {
@@ -770,33 +709,33 @@ __device__ __forceinline__ float block_trace(const float* __restrict__ G, int r)
     return red[0];
 }
 
-// out = post * (a I + b * pre * G + c * G2), fp32 or bf16.  mode 0: pre = post = 1.  mode 1: pre = 1 / trace(G),
-// post = 1.  mode 2: pre = 1 / trace(G), post = sqrt(pre) (the first step of an iteration on a matrix
-// Q that has not been scaled: Q / |Q|_F has the Gram matrix G / trace(G)).  G2 (fp32) may be NULL.
-template <bool TO_BF16>
-__global__ __launch_bounds__(256) void gram_poly_kernel(const float* __restrict__ G, const float* __restrict__ G2,
-                                                        void* __restrict__ out, int r, float a, float b, float c, int mode)
+// out = G / trace(G), and inv_trace = 1 / trace(G) (0 if the trace is not positive)
+__global__ __launch_bounds__(256) void gram_scale_kernel(const float* __restrict__ G, float* __restrict__ out, float* __restrict__ inv_trace, int r)
 {
-    float pre = 1.f, post = 1.f;
-    if (mode) {
-        const float t = block_trace(G, r);
-        pre = (t > 0.f) ? 1.f / t : 0.f;
-        if (mode == 2) post = sqrtf(pre);
-    }
+    const float t = block_trace(G, r);
+    const float inv = (t > 0.f) ? 1.f / t : 0.f;
+    if (blockIdx.x == 0 && threadIdx.x == 0) *inv_trace = inv;
     const int64_t total = (int64_t)r * r;
-    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < total; i += (int64_t)gridDim.x * 256) {
-        float v = b * pre * G[i];
-        if (G2) v += c * G2[i];
-        if (i / r == i % r) v += a;
-        if constexpr (TO_BF16) reinterpret_cast<uint16_t*>(out)[i] = float_to_bf16_bits(post * v);
-        else reinterpret_cast<float*>(out)[i] = post * v;
-    }
+    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < total; i += (int64_t)gridDim.x * 256) out[i] = inv * G[i];
 }
 
-hipError_t launch_gram_poly(const float* G, const float* G2, void* out, bool to_bf16, int64_t r, float a, float b, float c, int mode, hipStream_t s)
+hipError_t launch_gram_scale(const float* G, float* out, float* inv_trace, int64_t r, hipStream_t s)
 {
-    if (to_bf16) hipLaunchKernelGGL(gram_poly_kernel<true>, dim3(grid_for(r * r)), dim3(256), 0, s, G, G2, out, (int)r, a, b, c, mode);
-    else hipLaunchKernelGGL(gram_poly_kernel<false>, dim3(grid_for(r * r)), dim3(256), 0, s, G, G2, out, (int)r, a, b, c, mode);
+    hipLaunchKernelGGL(gram_scale_kernel, dim3(grid_for(r * r)), dim3(256), 0, s, G, out, inv_trace, (int)r);
+    return hipGetLastError();
+}
+
+// out (bf16) = G - I
+__global__ __launch_bounds__(256) void minus_identity_kernel(const float* __restrict__ G, uint16_t* __restrict__ out, int r)
+{
+    const int64_t total = (int64_t)r * r;
+    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < total; i += (int64_t)gridDim.x * 256)
+        out[i] = float_to_bf16_bits(G[i] + ((i / r == i % r) ? -1.f : 0.f));
+}
+
+hipError_t launch_minus_identity(const float* G, void* out, int64_t r, hipStream_t s)
+{
+    hipLaunchKernelGGL(minus_identity_kernel, dim3(grid_for(r * r)), dim3(256), 0, s, G, (uint16_t*)out, (int)r);
     return hipGetLastError();
 }
 
