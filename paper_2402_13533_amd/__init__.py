@@ -9,8 +9,6 @@ from __future__ import annotations
 import ctypes as C
 import os
 
-C_float = C.c_float
-
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libfingpt_hpc.so")
 
@@ -165,7 +163,7 @@ def plan_slab_bytes(call: int, M: int, K: int, r: int, N: int, dtype: int = FHPC
                     outputs: int = 7, base_scale: float = 1.0):
     """Host-only test hook: (status, planned, reserved) partial-sum bytes of an entry point's launch sequence."""
     planned, reserved = C.c_int64(0), C.c_int64(0)
-    rc = load_library().fhpc_plan_slab_bytes(call, M, K, r, N, dtype, qscheme, g, outputs, C_float(base_scale),
+    rc = load_library().fhpc_plan_slab_bytes(call, M, K, r, N, dtype, qscheme, g, outputs, base_scale,
                                              C.byref(planned), C.byref(reserved))
     return int(rc), int(planned.value), int(reserved.value)
 
@@ -176,17 +174,34 @@ def workspace_bytes(op: int, M: int, K: int, r: int, N: int, dtype: int = FHPC_B
 
 # ----------------------------------------------------------------------------- torch side
 
+_torch_module = None
+
+
 def _torch():
-    import torch
-    return torch
+    global _torch_module
+    if _torch_module is None:
+        import torch
+        _torch_module = torch
+    return _torch_module
 
 
 def _ptr(t):
-    return C.c_void_p(0 if t is None else t.data_ptr())
+    return None if t is None else t.data_ptr()
+
+
+# A call with few tokens is over on the GPU in 7 .. 30 microseconds, so the marshalling below is kept to plain Python
+# numbers (ctypes converts them by the declared argument types) and to torch calls that build no Python objects: a
+# forward and backward pair of the 8-bit layer took 47 microseconds of host time otherwise, 33 this way.
+
+def _raw_stream(index: int) -> int:
+    """The device's current stream as an integer handle."""
+    torch = _torch()
+    raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+    return int(torch.cuda.current_stream(index).cuda_stream) if raw is None else raw(index)
 
 
 def _stream():
-    return C.c_void_p(_torch().cuda.current_stream().cuda_stream)
+    return _raw_stream(_torch().cuda.current_device())
 
 
 def _dtype_code(t) -> int:
@@ -203,7 +218,7 @@ def _check(t, name, shape=None, dtype=None):
         return
     if not t.is_cuda or not t.is_contiguous():
         raise ValueError("%s must be a contiguous device tensor" % name)
-    if shape is not None and tuple(t.shape) != tuple(shape):
+    if shape is not None and t.shape != shape:
         raise ValueError("%s has shape %s, expected %s" % (name, tuple(t.shape), tuple(shape)))
     if dtype is not None and t.dtype != dtype:
         raise TypeError("%s has dtype %s, expected %s" % (name, t.dtype, dtype))
@@ -216,7 +231,10 @@ def get_workspace(nbytes: int, device):
     """A cached byte tensor of at least nbytes (grown on demand), one per device and stream: calls that share a
     workspace must be ordered on one stream."""
     torch = _torch()
-    key = (str(device), int(torch.cuda.current_stream(device).cuda_stream))
+    if not isinstance(device, torch.device):
+        device = torch.device(device)
+    index = device.index if device.index is not None else torch.cuda.current_device()
+    key = (index, _raw_stream(index))
     ws = _workspaces.get(key)
     if ws is None or ws.numel() < nbytes:
         # zero once: the library keeps the workspace header (arrival counters) zero from call to call
@@ -228,7 +246,7 @@ def get_workspace(nbytes: int, device):
 def _ws(op, M, K, r, N, dtype, qscheme, device, workspace):
     need = workspace_bytes(op, M, K, r, N, dtype, qscheme)
     ws = workspace if workspace is not None else get_workspace(need, device)
-    return ws, C.c_size_t(ws.numel() * ws.element_size())
+    return ws, ws.numel() * ws.element_size()
 
 
 def lowrank_linear_fwd(X, A, B, Y=None, H_out=None, save_H: bool = False, workspace=None):
@@ -239,9 +257,9 @@ def lowrank_linear_fwd(X, A, B, Y=None, H_out=None, save_H: bool = False, worksp
     r, N = B.shape
     _check(X, "X"); _check(A, "A", (K, r), X.dtype); _check(B, "B", (r, N), X.dtype)
     if Y is None:
-        Y = torch.empty((M, N), dtype=X.dtype, device=X.device)
+        Y = X.new_empty((M, N))
     if H_out is None and save_H:
-        H_out = torch.empty((M, r), dtype=X.dtype, device=X.device)
+        H_out = X.new_empty((M, r))
     _check(Y, "Y", (M, N), X.dtype); _check(H_out, "H_out", (M, r), X.dtype)
     dt = _dtype_code(X)
     ws, wsz = _ws(FHPC_OP_LOWRANK_FWD, M, K, r, N, dt, 0, X.device, workspace)
@@ -262,11 +280,11 @@ def lowrank_linear_bwd(X, A, B, dY, H_saved=None, need_dX=True, need_dA=True, ne
     _check(X, "X"); _check(A, "A", (K, r), X.dtype); _check(B, "B", (r, N), X.dtype)
     _check(dY, "dY", (M, N), X.dtype); _check(H_saved, "H_saved", (M, r), X.dtype)
     if dX is None and need_dX:
-        dX = torch.empty((M, K), dtype=X.dtype, device=X.device)
+        dX = X.new_empty((M, K))
     if dA is None and need_dA:
-        dA = torch.empty((K, r), dtype=torch.float32, device=X.device)
+        dA = X.new_empty((K, r), dtype=torch.float32)
     if dB is None and need_dB:
-        dB = torch.empty((r, N), dtype=torch.float32, device=X.device)
+        dB = X.new_empty((r, N), dtype=torch.float32)
     _check(dX, "dX", (M, K), X.dtype); _check(dA, "dA", (K, r), torch.float32); _check(dB, "dB", (r, N), torch.float32)
     dt = _dtype_code(X)
     ws, wsz = _ws(FHPC_OP_LOWRANK_BWD, M, K, r, N, dt, 0, X.device, workspace)
@@ -289,7 +307,10 @@ def _shared_ws(backward, M, K, r, N, g, device, workspace):
     torch = _torch()
     need = int(load_library().fhpc_workspace_bytes_lowrank_shared_x(int(backward), M, K, r, N, g))
     if workspace is None:
-        workspace = torch.zeros(max(need, 256), dtype=torch.uint8, device=device)
+        # a buffer of the call's own, as its outputs are.  These calls do not use the header and write every other part
+        # before they read it, so it is not cleared (80 and 335 MB for the FFN of a 7B model at 16384 tokens: 51
+        # microseconds of fills per step)
+        workspace = torch.empty(max(need, 256), dtype=torch.uint8, device=device)
     return workspace, workspace.numel()
 
 
@@ -306,11 +327,11 @@ def lowrank_linear_fwd_shared_x(X, A_all, Bs, Ys=None, H_all_out=None, save_H: b
     for B in Bs:
         _check(B, "B", (r, N), bf)
     if Ys is None:
-        Ys = [torch.empty((M, N), dtype=bf, device=X.device) for _ in range(g)]
+        Ys = [X.new_empty((M, N), dtype=bf) for _ in range(g)]
     for Y in Ys:
         _check(Y, "Y", (M, N), bf)
     if H_all_out is None and save_H:
-        H_all_out = torch.empty((M, g * r), dtype=bf, device=X.device)
+        H_all_out = X.new_empty((M, g * r), dtype=bf)
     _check(H_all_out, "H_all_out", (M, g * r), bf)
     ws, wsz = _shared_ws(False, M, K, r, N, g, X.device, workspace)
     rc = lib.lowrank_linear_fwd_shared_x(_ptr(X), _ptr(A_all), _ptr_array(Bs), _ptr_array(Ys), _ptr(H_all_out),
@@ -330,12 +351,12 @@ def lowrank_ffn_gate_up_fwd(X, A_all, B_gate, B_up, G=None, U=None, Z=None, H_al
     r, N = B_gate.shape
     _check(X, "X", None, bf); _check(A_all, "A_all", (K, 2 * r), bf)
     _check(B_gate, "B_gate", (r, N), bf); _check(B_up, "B_up", (r, N), bf)
-    G = torch.empty((M, N), dtype=bf, device=X.device) if G is None else G
-    U = torch.empty((M, N), dtype=bf, device=X.device) if U is None else U
-    Z = torch.empty((M, N), dtype=bf, device=X.device) if Z is None else Z
+    G = X.new_empty((M, N), dtype=bf) if G is None else G
+    U = X.new_empty((M, N), dtype=bf) if U is None else U
+    Z = X.new_empty((M, N), dtype=bf) if Z is None else Z
     _check(G, "G", (M, N), bf); _check(U, "U", (M, N), bf); _check(Z, "Z", (M, N), bf)
     if H_all_out is None and save_H:
-        H_all_out = torch.empty((M, 2 * r), dtype=bf, device=X.device)
+        H_all_out = X.new_empty((M, 2 * r), dtype=bf)
     _check(H_all_out, "H_all_out", (M, 2 * r), bf)
     ws, wsz = _shared_ws(False, M, K, r, N, 2, X.device, workspace)
     rc = lib.lowrank_ffn_gate_up_fwd(_ptr(X), _ptr(A_all), _ptr(B_gate), _ptr(B_up), _ptr(G), _ptr(U), _ptr(Z),
@@ -357,12 +378,12 @@ def lowrank_ffn_down_bwd(Z, A, B, dY, G, U, H_saved=None, need_dA=True, need_dB=
     _check(Z, "Z", None, bf); _check(A, "A", (K, r), bf); _check(B, "B", (r, N), bf)
     _check(dY, "dY", (M, N), bf); _check(H_saved, "H_saved", (M, r), bf)
     _check(G, "G", (M, K), bf); _check(U, "U", (M, K), bf)
-    dG = torch.empty((M, K), dtype=bf, device=Z.device) if dG is None else dG
-    dU = torch.empty((M, K), dtype=bf, device=Z.device) if dU is None else dU
+    dG = Z.new_empty((M, K), dtype=bf) if dG is None else dG
+    dU = Z.new_empty((M, K), dtype=bf) if dU is None else dU
     if dA is None and need_dA:
-        dA = torch.empty((K, r), dtype=torch.float32, device=Z.device)
+        dA = Z.new_empty((K, r), dtype=torch.float32)
     if dB is None and need_dB:
-        dB = torch.empty((r, N), dtype=torch.float32, device=Z.device)
+        dB = Z.new_empty((r, N), dtype=torch.float32)
     _check(dG, "dG", (M, K), bf); _check(dU, "dU", (M, K), bf)
     _check(dA, "dA", (K, r), torch.float32); _check(dB, "dB", (r, N), torch.float32)
     ws, wsz = _ws(FHPC_OP_LOWRANK_BWD, M, K, r, N, FHPC_BF16, 0, Z.device, workspace)
@@ -390,12 +411,12 @@ def lowrank_linear_bwd_shared_x(X, A_all, Bs, dYs, H_all_saved=None, need_dX=Tru
         _check(B, "B", (r, N), bf); _check(dY, "dY", (M, N), bf)
     flags = list(need_dB) if isinstance(need_dB, (list, tuple)) else [bool(need_dB)] * g
     if dX is None and need_dX:
-        dX = torch.empty((M, K), dtype=bf, device=X.device)
+        dX = X.new_empty((M, K), dtype=bf)
     dA = dA_all
     if dA is None and need_dA:
-        dA = torch.empty((K, g * r), dtype=torch.float32, device=X.device)
+        dA = X.new_empty((K, g * r), dtype=torch.float32)
     if dBs is None:
-        dBs = [torch.empty((r, N), dtype=torch.float32, device=X.device) if f else None for f in flags]
+        dBs = [X.new_empty((r, N), dtype=torch.float32) if f else None for f in flags]
     flags = [b is not None for b in dBs]
     _check(dX, "dX", (M, K), bf); _check(dA, "dA_all", (K, g * r), torch.float32)
     for b in dBs:
@@ -434,13 +455,13 @@ def qlinear_lowrank_fwd(X, Wq, scales, qscheme, A, B, scaling, block=64, Y=None,
     _check(X, "X", None, bf); _check(A, "A", (K, r), bf); _check(B, "B", (r, N), bf)
     _q_shapes(Wq, scales, qscheme, K, N, block)
     if Y is None:
-        Y = torch.empty((M, N), dtype=bf, device=X.device)
+        Y = X.new_empty((M, N), dtype=bf)
     if H_out is None and save_H:
-        H_out = torch.empty((M, r), dtype=bf, device=X.device)
+        H_out = X.new_empty((M, r), dtype=bf)
     _check(Y, "Y", (M, N), bf); _check(H_out, "H_out", (M, r), bf)
     ws, wsz = _ws(FHPC_OP_QLINEAR_FWD, M, K, r, N, FHPC_BF16, qscheme, X.device, workspace)
     rc = getattr(lib, _entry)(_ptr(X), _ptr(Wq), _ptr(scales), qscheme, block, _ptr(A), _ptr(B),
-                              C.c_float(scaling), _ptr(Y), _ptr(H_out), M, K, r, N, _ptr(ws), wsz, _stream())
+                              scaling, _ptr(Y), _ptr(H_out), M, K, r, N, _ptr(ws), wsz, _stream())
     if rc:
         raise FhpcError(rc, _entry)
     return (Y, H_out) if H_out is not None else Y
@@ -460,7 +481,7 @@ def qlinear_lowrank_fwd_noalloc(X, Wq, scales, qscheme, A, B, scaling, Y, H_out=
     _q_shapes(Wq, scales, qscheme, K, N, block)
     _check(Y, "Y", (M, N), bf); _check(H_out, "H_out", (M, r), bf)
     rc = load_library().qlinear_lowrank_fwd_noalloc(_ptr(X), _ptr(Wq), _ptr(scales), qscheme, block, _ptr(A), _ptr(B),
-                                                    C.c_float(scaling), _ptr(Y), _ptr(H_out), M, K, r, N, _stream())
+                                                    scaling, _ptr(Y), _ptr(H_out), M, K, r, N, _stream())
     if rc:
         raise FhpcError(rc, "qlinear_lowrank_fwd_noalloc")
     return (Y, H_out) if H_out is not None else Y
@@ -479,15 +500,15 @@ def qlinear_lowrank_bwd(X, Wq, scales, qscheme, A, B, scaling, dY, block=64, H_s
     _check(dY, "dY", (M, N), bf); _check(H_saved, "H_saved", (M, r), bf)
     _q_shapes(Wq, scales, qscheme, K, N, block)
     if dX is None and need_dX:
-        dX = torch.empty((M, K), dtype=bf, device=X.device)
+        dX = X.new_empty((M, K), dtype=bf)
     if dA is None and need_dA:
-        dA = torch.empty((K, r), dtype=torch.float32, device=X.device)
+        dA = X.new_empty((K, r), dtype=torch.float32)
     if dB is None and need_dB:
-        dB = torch.empty((r, N), dtype=torch.float32, device=X.device)
+        dB = X.new_empty((r, N), dtype=torch.float32)
     _check(dX, "dX", (M, K), bf); _check(dA, "dA", (K, r), torch.float32); _check(dB, "dB", (r, N), torch.float32)
     ws, wsz = _ws(FHPC_OP_QLINEAR_BWD, M, K, r, N, FHPC_BF16, qscheme, X.device, workspace)
     rc = getattr(lib, _entry)(_ptr(X), _ptr(Wq), _ptr(scales), qscheme, block, _ptr(A), _ptr(B),
-                              C.c_float(scaling), _ptr(dY), _ptr(H_saved), _ptr(dX), _ptr(dA), _ptr(dB),
+                              scaling, _ptr(dY), _ptr(H_saved), _ptr(dX), _ptr(dA), _ptr(dB),
                               M, K, r, N, _ptr(ws), wsz, _stream())
     if rc:
         raise FhpcError(rc, _entry)
@@ -543,7 +564,7 @@ def fhpc_add(a, b, out=None):
 def fhpc_gemm_bf16(A, lda, a_mode, B, ldb, b_mode, C, ldc, out_mode, M, N, K, alpha=1.0, tile=0, splits=1, dbg=0):
     """Diagnostic: one launch of the GEMM core (see the header for the argument meanings)."""
     rc = load_library().fhpc_gemm_bf16(_ptr(A), lda, a_mode, _ptr(B), ldb, b_mode, _ptr(C), ldc, out_mode,
-                                       M, N, K, C_float(alpha), tile, splits, dbg, _stream())
+                                       M, N, K, alpha, tile, splits, dbg, _stream())
     if rc:
         raise FhpcError(rc, "fhpc_gemm_bf16")
     return C
@@ -584,8 +605,8 @@ def qlinear_lowrank_fwd_shared_x(X, weights, qscheme, block=64, save_H: bool = F
         N = B.shape[1]
         _check(A, "A", (K, r), bf); _check(B, "B", (r, N), bf)
         _q_shapes(Wq, sc, qscheme, K, N, block)
-        Y = torch.empty((M, N), dtype=bf, device=X.device)
-        H = torch.empty((M, r), dtype=bf, device=X.device) if save_H else None
+        Y = X.new_empty((M, N), dtype=bf)
+        H = X.new_empty((M, r), dtype=bf) if save_H else None
         arr[j] = QlinearWeight(Wq.data_ptr(), sc.data_ptr(), A.data_ptr(), B.data_ptr(), Y.data_ptr(),
                                0 if H is None else H.data_ptr(), N, float(scaling))
         Ns[j] = N
@@ -593,7 +614,7 @@ def qlinear_lowrank_fwd_shared_x(X, weights, qscheme, block=64, save_H: bool = F
     need = int(lib.fhpc_workspace_bytes_shared_x(Ns, count, M, K, r, qscheme))
     ws = workspace if workspace is not None else get_workspace(need, X.device)
     rc = lib.qlinear_lowrank_fwd_shared_x(_ptr(X), arr, count, qscheme, block, M, K, r, _ptr(ws),
-                                          C.c_size_t(ws.numel() * ws.element_size()), _stream())
+                                          ws.numel() * ws.element_size(), _stream())
     if rc:
         raise FhpcError(rc, "qlinear_lowrank_fwd_shared_x")
     return outs
@@ -617,7 +638,7 @@ def lowrank_merge(W, scales, qscheme, A, B, scaling=1.0, block=64, out_dtype=Non
     ws = None
     if need:
         ws = workspace if workspace is not None else get_workspace(need, A.device)
-    wsz = C.c_size_t(0 if ws is None else ws.numel() * ws.element_size())
+    wsz = 0 if ws is None else ws.numel() * ws.element_size()
     rc = lib.lowrank_merge(_ptr(W), _ptr(scales), qscheme, block, _ptr(A), _ptr(B), float(scaling), _ptr(W_out),
                            _dtype_code(W_out), K, r, N, _ptr(ws), wsz, _stream())
     if rc:
@@ -645,7 +666,7 @@ def lowrank_decompose(W, r, Omega=None, power_iters=2, seed=0, workspace=None):
     need = workspace_bytes(FHPC_OP_DECOMPOSE, 1, K, r, N)
     ws = workspace if workspace is not None else get_workspace(need, W.device)
     rc = lib.lowrank_decompose(_ptr(W), _ptr(Omega), int(power_iters), _ptr(A), _ptr(B), K, r, N, L,
-                               _ptr(ws), C.c_size_t(ws.numel() * ws.element_size()), _stream())
+                               _ptr(ws), ws.numel() * ws.element_size(), _stream())
     if rc:
         raise FhpcError(rc, "lowrank_decompose")
     return A, B

@@ -398,3 +398,23 @@ def test_shared_x_matches_the_single_layer_calls():
         dX_sum += from_device(dX1)
     assert parity_err(from_device(dX), dX_sum) <= TOL_BF16
     torch.cuda.synchronize()
+
+
+@pytest.mark.parametrize("M,K,r,N,g", [(40, 264, 16, 136, 3), (300, 1024, 64, 2048, 2), (2500, 520, 128, 512, 3)])
+def test_shared_x_calls_write_their_scratch_before_they_read_it(M, K, r, N, g):
+    """The binding hands the shared-X calls a workspace it has not cleared: with one full of NaN bit patterns they give
+    the bits they give with a cleared one."""
+    import torch
+    fhpc = _fhpc()
+    X, A = Bf16.normal(1, (M, K)).cuda(), Bf16.normal(2, (K, g * r), K ** -0.5).cuda()
+    Bs = [Bf16.normal(3 + i, (r, N), r ** -0.5).cuda() for i in range(g)]
+    dYs = [Bf16.normal(20 + i, (M, N)).cuda() for i in range(g)]
+    got = []
+    for fill in (0, 255):
+        need = fhpc.load_library().fhpc_workspace_bytes_lowrank_shared_x(1, M, K, r, N, g)
+        ws = torch.full((need,), fill, dtype=torch.uint8, device="cuda")
+        Ys, H = fhpc.lowrank_linear_fwd_shared_x(X, A, Bs, save_H=True, workspace=ws)
+        ws.fill_(fill)
+        dX, dA, dBs = fhpc.lowrank_linear_bwd_shared_x(X, A, Bs, dYs, workspace=ws)
+        got.append([*Ys, H, dX, dA, *dBs])
+    assert all(torch.equal(a, b) for a, b in zip(*got))
