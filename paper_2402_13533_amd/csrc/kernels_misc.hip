@@ -10,6 +10,7 @@ namespace fhpc {
 
 typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
 typedef __attribute__((ext_vector_type(2))) float f32x2;
+typedef __attribute__((ext_vector_type(4))) float f32x4;
 
 __device__ __forceinline__ float bf16_bits_to_float(uint32_t b) { return __builtin_bit_cast(float, b << 16); }
 
@@ -473,6 +474,29 @@ hipError_t launch_compact_f32(const float* src, int64_t ld_src, void* dst, int64
     return hipGetLastError();
 }
 
+// Element i of `count` slabs, `stride` floats apart, added in slab order from zero.  `count` is the same for a whole wave.
+// Eight are requested before the first is added: with one load behind the other a sum of 64 slabs was a chain of 16
+// round trips (300 x 8 outputs: 6.4 microseconds, all latency; 3.5 this way).
+__device__ __forceinline__ f32x4 add_slabs(const float* __restrict__ slabs, int64_t stride, int count, int64_t i)
+{
+    f32x4 a = {0.f, 0.f, 0.f, 0.f};
+    count = __builtin_amdgcn_readfirstlane(count);
+    if (count <= 4) {
+        for (int s = 0; s < count; s++) a += reinterpret_cast<const f32x4*>(slabs + (int64_t)s * stride)[i];
+        return a;
+    }
+    for (int s0 = 0; s0 < count; s0 += 8) {
+        f32x4 b[8];
+#pragma unroll
+        for (int q = 0; q < 8; q++)
+            if (s0 + q < count) b[q] = reinterpret_cast<const f32x4*>(slabs + (int64_t)(s0 + q) * stride)[i];
+#pragma unroll
+        for (int q = 0; q < 8; q++)
+            if (s0 + q < count) a += b[q];
+    }
+    return a;
+}
+
 // out[i] = sum over s of slabs[s * slab + i]: the second half of a split reduction.  A workgroup
 // covers 64 float4 outputs with four groups of threads, group g adding the slabs g, g+4, ...; the
 // four partial sums are then added in group order through LDS, so the result is the same from run
@@ -481,26 +505,23 @@ template <bool TO_BF16>
 __global__ __launch_bounds__(256) void sum_slabs_kernel(const float* __restrict__ slabs, int64_t slab, int nslab,
                                                         void* __restrict__ out, int64_t n4)
 {
-    typedef __attribute__((ext_vector_type(4))) float f32x4;
     typedef __attribute__((ext_vector_type(2))) uint32_t u32x2_t;
     __shared__ f32x4 red[3][64];
     const int lane = threadIdx.x & 63, g = threadIdx.x >> 6;
     for (int64_t base = (int64_t)blockIdx.x * 64; base < n4; base += (int64_t)gridDim.x * 64) {
         const int64_t i = base + lane;
-        f32x4 a = {0.f, 0.f, 0.f, 0.f};
-        if (i < n4)
-            for (int s = g; s < nslab; s += 4) a += reinterpret_cast<const f32x4*>(slabs + (int64_t)s * slab)[i];
+        const f32x4 a = (i < n4) ? add_slabs(slabs + (int64_t)g * slab, 4 * slab, (nslab - g + 3) / 4, i) : f32x4{0.f, 0.f, 0.f, 0.f};
         if (g > 0) red[g - 1][lane] = a;
         __syncthreads();
         if (g == 0 && i < n4) {
-            a = ((a + red[0][lane]) + red[1][lane]) + red[2][lane];
+            const f32x4 sum = ((a + red[0][lane]) + red[1][lane]) + red[2][lane];
             if constexpr (TO_BF16) {
                 u32x2_t o;
-                o.x = bf16_pack(a.x, a.y);
-                o.y = bf16_pack(a.z, a.w);
+                o.x = bf16_pack(sum.x, sum.y);
+                o.y = bf16_pack(sum.z, sum.w);
                 reinterpret_cast<u32x2_t*>(out)[i] = o;
             } else {
-                reinterpret_cast<f32x4*>(out)[i] = a;
+                reinterpret_cast<f32x4*>(out)[i] = sum;
             }
         }
         __syncthreads();
@@ -519,7 +540,6 @@ struct SlabSumPair {
 };
 __global__ __launch_bounds__(256) void sum_slabs_pair_kernel(SlabSumPair p)
 {
-    typedef __attribute__((ext_vector_type(4))) float f32x4;
     __shared__ f32x4 red[3][64];
     const int which = ((int)blockIdx.x < p.blocks[0]) ? 0 : 1;
     const float* const slabs = which ? p.slabs[1] : p.slabs[0];
@@ -531,14 +551,11 @@ __global__ __launch_bounds__(256) void sum_slabs_pair_kernel(SlabSumPair p)
     const int lane = threadIdx.x & 63, g = threadIdx.x >> 6;
     for (int64_t base = (int64_t)block * 64; base < n4; base += (int64_t)nblocks * 64) {
         const int64_t i = base + lane;
-        f32x4 a = {0.f, 0.f, 0.f, 0.f};
-        if (i < n4)
-            for (int s = g; s < nslab; s += 4) a += reinterpret_cast<const f32x4*>(slabs + (int64_t)s * slab)[i];
+        const f32x4 a = (i < n4) ? add_slabs(slabs + (int64_t)g * slab, 4 * slab, (nslab - g + 3) / 4, i) : f32x4{0.f, 0.f, 0.f, 0.f};
         if (g > 0) red[g - 1][lane] = a;
         __syncthreads();
         if (g == 0 && i < n4) {
-            a = ((a + red[0][lane]) + red[1][lane]) + red[2][lane];
-            reinterpret_cast<f32x4*>(out)[i] = a;
+            reinterpret_cast<f32x4*>(out)[i] = ((a + red[0][lane]) + red[1][lane]) + red[2][lane];
         }
         __syncthreads();
     }
@@ -616,15 +633,23 @@ __global__ __launch_bounds__(64 * TS_WAVES) void tall_skinny_kc_kernel(const uin
 }
 
 // Large outputs with few slabs: one thread per float4 output adds its slabs in order.
+template <bool TO_BF16>
 __global__ __launch_bounds__(256) void sum_slabs_wide_kernel(const float* __restrict__ slabs, int64_t slab, int nslab,
-                                                             float* __restrict__ out, int64_t n4)
+                                                             void* __restrict__ out, int64_t n4)
 {
-    typedef __attribute__((ext_vector_type(4))) float f32x4;
+    typedef __attribute__((ext_vector_type(2))) uint32_t u32x2_t;
     const int64_t stride = (int64_t)gridDim.x * 256;
     for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n4; i += stride) {
         f32x4 a = reinterpret_cast<const f32x4*>(slabs)[i];
         for (int s = 1; s < nslab; s++) a += reinterpret_cast<const f32x4*>(slabs + (int64_t)s * slab)[i];
-        reinterpret_cast<f32x4*>(out)[i] = a;
+        if constexpr (TO_BF16) {
+            u32x2_t o;
+            o.x = bf16_pack(a.x, a.y);
+            o.y = bf16_pack(a.z, a.w);
+            reinterpret_cast<u32x2_t*>(out)[i] = o;
+        } else {
+            reinterpret_cast<f32x4*>(out)[i] = a;
+        }
     }
 }
 
@@ -633,9 +658,12 @@ hipError_t launch_sum_slabs(const float* slabs, int64_t n, int nslab, void* out,
 {
     if (n <= 0) return hipSuccess;
     const int64_t n4 = n / 4;
-    if (!to_bf16 && nslab <= 8 && n4 >= 65536) {
-        // enough independent outputs to fill the chip with one thread each
-        hipLaunchKernelGGL(sum_slabs_wide_kernel, dim3(grid_for(n4)), dim3(256), 0, s, slabs, n, nslab, (float*)out, n4);
+    if (!sum_slabs_is_small(n, nslab)) {
+        // enough independent outputs to fill the chip with one thread each (bf16, 300 x 4096 from 5 slabs: 5.1 microseconds against
+        // 6.3 with four groups per output, 1000 x 1600 from 2: 4.2 against 4.6)
+        const dim3 grid(grid_for(n4)), block(256);
+        if (to_bf16) hipLaunchKernelGGL(sum_slabs_wide_kernel<true>, grid, block, 0, s, slabs, n, nslab, out, n4);
+        else hipLaunchKernelGGL(sum_slabs_wide_kernel<false>, grid, block, 0, s, slabs, n, nslab, out, n4);
         return hipGetLastError();
     }
     int64_t blocks = (n4 + 63) / 64;
