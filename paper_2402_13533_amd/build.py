@@ -8,7 +8,7 @@ import sys
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libfingpt_hpc.so")
-SOURCES = ["api.hip", "gemm_bf16.hip", "gemm_f32.hip", "gemm_pp.hip", "gemm_w4.hip", "kernels_misc.hip", "merge.hip", "qskinny.hip", "qskinny_dx.hip", "profile.hip", "peaks.hip"]
+SOURCES = ["api.hip", "gemm_bf16.hip", "gemm_f32.hip", "gemm_pp.hip", "gemm_w4.hip", "kernels_misc.hip", "merge.hip", "qskinny.hip", "qskinny_dx.hip", "qskinny_rows.hip", "profile.hip", "peaks.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = ["--offload-arch=gfx950", "-O3", "-fPIC", "-std=c++17",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
@@ -18,7 +18,7 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-fPIC", "-std=c++17",
 # Per-file compiler options.  qskinny.hip: keep the matrix instructions' results in ordinary vector
 # registers; its loop scales every 64-deep block sum on the vector ALU, and with the results in
 # accumulation registers each of those values costs an extra register move (an eighth of the loop).
-EXTRA = {"qskinny.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"]}
+EXTRA = {"qskinny.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"], "qskinny_rows.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"]}
 
 
 def build_library(verbose: bool = False) -> str:

@@ -46,6 +46,12 @@ constexpr int QSKINNY_HEADER_BYTES = 16384;
 hipError_t launch_qskinny_fwd(const void* X, const QskinnyJob* jobs, int count, int scheme, int64_t M, int64_t K, int64_t r,
                               const QskinnyPlan& p, float* part, float* hpart, uint32_t* tickets, hipStream_t st);
 
+// The same for one to a few tokens without slabs (csrc/qskinny_rows.hip), where that is the faster way; launch_qskinny_fwd
+// takes it.  hpart holds count * ceil(K / 1024) * M * r floats.
+bool qskinny_rows_pay(int64_t M, int64_t K, int64_t r, int64_t N_all, int num_cu);
+hipError_t launch_qskinny_rows(const void* X, const QskinnyJob* jobs, int count, int scheme, int64_t M, int64_t K, int64_t r,
+                               float* hpart, hipStream_t st);
+
 // ---- input gradient dX for a handful of tokens (csrc/qskinny_dx.hip)
 struct QskinnyDxPlan {
     int tt;                // blocks of 16 tokens that share a pass over the codes: 1 or 2

@@ -312,6 +312,37 @@ def test_few_token_forward(scheme, M, K, r, N):
 
 
 @pytest.mark.parametrize("scheme", [8, 4])
+@pytest.mark.parametrize("M,K,r,N", [
+    (1, 256, 1, 8),            # the smallest: one unit of the reduction, one rank, half a workgroup's channels
+    (1, 2048, 16, 24),         # channels not a multiple of 16
+    (3, 2560, 12, 40),         # the longest reduction taken at any width; a rank that is no multiple of 8
+    (10, 2048, 25, 72),        # ranks beyond 16
+    (16, 1280, 16, 88),        # the most tokens x reduction and tokens x ranks
+    (2, 8192, 64, 136),        # the longest reduction and the largest rank
+    (4, 5120, 16, 12296),      # taken for its channels; ragged last workgroup
+])
+def test_few_token_forward_whole_rows(scheme, M, K, r, N):
+    """The few-token forward whose workgroups own whole rows of the weight (no partial-sum slabs), at the edges of what it
+    takes, against the oracle; H to one bf16 rounding; outputs between guard regions."""
+    import torch
+    fhpc = _fhpc()
+    W, X, A, B, _ = qlinear_inputs(8, M, K, r, N, 260)
+    Wq, sc = _quantize_host(W, scheme)
+    Wd = oracle.dequant(Wq, sc, scheme, 64)
+    Wq_d, sc_d = _to_dev(Wq, sc)
+    guard = Guarded()
+    Y, H = guard.alloc((M, N), torch.bfloat16), guard.alloc((M, r), torch.bfloat16)
+    fhpc.qlinear_lowrank_fwd(X.cuda(), Wq_d, sc_d, scheme, A.cuda(), B.cuda(), 2.0, Y=Y, H_out=H)
+    guard.check("whole rows q%d %s" % (scheme, (M, K, r, N)))
+    Yr, Hr = oracle.qlinear_lowrank_fwd(X.f64, Wd, A.f64, B.f64, 2.0)
+    assert parity_err(from_device(Y), Yr) <= TOL_BF16 and parity_err(from_device(H), Hr) <= TOL_BF16
+    base = X.f64 @ Wd
+    low = 2.0 * (Hr @ B.f64)                       # the rank-r branch, against which a wrong or missing one shows
+    err = np.linalg.norm(from_device(Y) - base - low) / np.linalg.norm(low)
+    assert err <= 2.0 ** -8 * np.linalg.norm(Yr) / np.linalg.norm(low), err         # Y's own rounding
+
+
+@pytest.mark.parametrize("scheme", [8, 4])
 @pytest.mark.parametrize("M", [1, 16, 40, 100])
 def test_shared_x_forward(scheme, M):
     """Three projections that read the same X (widths as with grouped key/value heads, one of them not a
