@@ -225,7 +225,9 @@ bool split_pays(int64_t M, int64_t Nout, int64_t Kred)
     if (Nout <= 32) return false;
     if (M > 32) {
         const int64_t tiles = ((M + 127) / 128) * ((Nout + 127) / 128);
-        if (2 * tiles > num_cu() || Kred < 256) return false;
+        // (at most 512 deep, eight steps: the slices save less than their slab sum costs; forward of 4096 -> 512 -> 4096 at 64 /
+        // 300 tokens 24 -> 21, 31 -> 24 microseconds, 2048 -> 256 -> 2048 at 600 26 -> 19; a tile or two stay in slices)
+        if (2 * tiles > num_cu() || Kred < 256 || (Kred <= 512 && tiles >= 4)) return false;
     }
     return plan_split(M, Nout, Kred, true).splits > 1;
 }
@@ -379,6 +381,44 @@ int64_t f32_part_bytes(bool bwd, int64_t M, int64_t K, int64_t r, int64_t N)
     return part;
 }
 
+// The products of a layer's backward pass that follow dH, in one launch of 256 x 128 tiles (launch_gemm_pp_backward): dA (K x R)
+// and g times dB (r x N), both reduced over the M tokens and cut into slices while that fills the chip, and dX (M x K, reduced
+// over the R = g r ranks) where it fits as well.  The plan does not depend on which outputs a call wants, so that each
+// has the same bits whatever else is asked for.
+struct JointPlan {
+    bool pays = false, with_dx = false;
+    int splits = 1, k_chunk = 0;
+};
+JointPlan plan_joint(int64_t M, int64_t K, int64_t r, int64_t N, int g)
+{
+    JointPlan p;
+    // One round of workgroups, two while the reductions are short (longer ones go better through the persistent 256 x 256
+    // tiles).  Backward of one layer in microseconds, launches of their own / together: 1600 -> 384 -> 6400 at 300 / 1000 /
+    // 4096 tokens 73 / 31, 91 / 46, 119 / 97; 4096 -> 512 -> 4096 at 300 / 2000 / 16384 83 / 30, 104 / 67, 312 / 306;
+    // 4096 -> 1024 -> 11008 (two rounds) at 300 / 4096 121 / 74, 316 / 286.  Four rounds gain or lose a few per cent.
+    const int64_t R = r * g, units = num_cu(), limit = units * (M <= 4096 ? 2 : 1);
+    // (a long reduction on tiles a good part of whose rows lie beyond the rank: 1600 -> 384 -> 6400 at 16384 tokens 260 / 265)
+    if (r <= 32 || (M > 8192 && r > 256 && r % 256 != 0)) return p;
+    const auto blocks = [](int64_t tiles) { return round_up(tiles, 8); };
+    const int64_t n_db = blocks(tile_count(TILE_256x128, r, N) * g), n_da = blocks(tile_count(TILE_256x128, K, R));
+    const int64_t n_dx = blocks(tile_count(TILE_256x128, M, K)), steps = (M + 63) / 64;
+    if (n_db + n_da > limit) return p;
+    p.pays = true;
+    p.with_dx = n_db + n_da + n_dx <= limit;
+    int64_t s = (units - (p.with_dx ? n_dx : 0)) / (n_db + n_da);
+    if (s > steps / 8) s = steps / 8;
+    if (s < 1) s = 1;
+    const int64_t per = (steps + s - 1) / s;
+    p.k_chunk = (int)(per * 64);
+    p.splits = (int)((steps + per - 1) / per);
+    return p;
+}
+int64_t joint_part_bytes(int64_t M, int64_t K, int64_t r, int64_t N, int g)
+{
+    const JointPlan p = plan_joint(M, K, r, N, g);
+    return p.pays && p.splits > 1 ? (int64_t)p.splits * (K * r * g + (int64_t)g * r * N) * 4 : 0;
+}
+
 Scratch carve(Carver& c, int op, int64_t M, int64_t K, int64_t r, int64_t N, int dtype, bool quantised = true,
               bool premerged = false)
 {
@@ -446,6 +486,7 @@ Scratch carve(Carver& c, int op, int64_t M, int64_t K, int64_t r, int64_t N, int
     if (op == FHPC_OP_LOWRANK_BWD) upto(product_part_bytes(M, K, rp));     // dX = dH A^T
     if (bwd) {
         upto(split_bytes(K, rp, rp, M) + split_bytes(rp, N, N, M));   // dA = X^T dH and dB = H^T dY, slabs side by side
+        if (op == FHPC_OP_LOWRANK_BWD) upto(joint_part_bytes(M, K, rp, N, 1));
     }
     s.part = static_cast<float*>(c.take(part));
     s.part_bytes = part;
@@ -473,7 +514,7 @@ int check_common(int64_t M, int64_t K, int64_t r, int64_t N)
 // 50 %; the 128x128 kernel runs two workgroups per compute unit).  What it decides in practice: an
 // output of 320 tiles of 256x256 (4096 tokens x 5120 channels) would run two rounds, the second a
 // quarter full; as 640 tiles of 256x128 it runs 2.5 (measured 196 against 217 microseconds).
-int pick_tile(int64_t M, int64_t N, bool allow_skinny)
+int pick_tile(int64_t M, int64_t N, bool allow_skinny, double* cost_out = nullptr)
 {
     if (allow_skinny && N <= 32) return TILE_256x32;
     if (allow_skinny && M <= 32) return TILE_32x256;
@@ -494,7 +535,14 @@ int pick_tile(int64_t M, int64_t N, bool allow_skinny)
             best_cost = cost;
         }
     }
+    if (cost_out) *cost_out = best_cost;
     return best;
+}
+double pick_cost(int64_t M, int64_t N)
+{
+    double cost = 0.0;
+    pick_tile(M, N, false, &cost);
+    return cost;
 }
 
 // What pick_tile minimises, for the tile it picks.
@@ -709,15 +757,20 @@ int prepare_factors(const void* A, const void* B, int64_t K, int64_t r, int64_t 
     return FHPC_OK;
 }
 
+// A handful of tokens: M-deep sums, until the sums over the tokens outweigh writing the outputs once.
+bool token_outer_pays(int64_t M, int64_t K, int64_t rp, int64_t N)
+{
+    return token_outer_supports(M) && (M <= 32 || rp * (K + N) <= ((int64_t)8 << 20));
+}
+
 // dA[K][r] = alpha X^T dH and dB[r][N] = alpha H^T dY, both reductions over the M tokens.
 int weight_grads(const void* X, const void* dY, const void* H, const void* dH, float* dA, float* dB,
                  int64_t M, int64_t K, int64_t r, int64_t rp, int64_t N, float alpha,
                  const Scratch& s, Run& run)
 {
     hipStream_t st = run.st;
-    // a handful of tokens: M-deep sums, both products in one launch of the vector-ALU kernel, until the sums
-    // over the tokens outweigh writing the outputs once
-    if ((dA || dB) && token_outer_supports(M) && (M <= 32 || rp * (K + N) <= ((int64_t)8 << 20))) {
+    // both products in one launch of the vector-ALU kernel
+    if ((dA || dB) && token_outer_pays(M, K, rp, N)) {
         FHPC_LAUNCH(run, launch_token_outer_grads(X, dH, dA, H, dY, dB, M, K, r, rp, N, alpha, st));
         return FHPC_OK;
     }
@@ -759,6 +812,66 @@ int weight_grads(const void* X, const void* dY, const void* H, const void* dH, f
         FHPC_HIP(gemm_split_f32(OP_XC, OP_XC, operand(H, rp), operand(dY, N), dst, N, rp, N, M, alpha, s.part, run));
         if (rp != r) FHPC_LAUNCH(run, launch_compact_f32(s.dB_t, N, dB, N, r, N, 1.f, false, st));
     }
+    return FHPC_OK;
+}
+
+// dX, dA and the g dB of factorised layers on one X by plan_joint's launch, any of them NULL; slab sums follow if it cut the
+// reductions.  H and dH are [M][R], A [K][R], R = g r.
+int joint_backward(const JointPlan& p, const void* X, const void* A, const void* const* dY, const void* H, const void* dH, void* dX, float* dA,
+                   float* const* dB, int64_t M, int64_t K, int64_t r, int64_t N, int g, float* part, Run& run)
+{
+    const int64_t R = r * g, na = K * R, nb = r * N;
+    if (!run.claim(p.splits > 1 ? (int64_t)p.splits * (na + g * nb) * 4 : 0)) return FHPC_ERR_WORKSPACE;
+    if (run.dry) return FHPC_OK;
+    GemmArgs a = {}, b = {}, x = {};
+    SumF32Job sums[SUM_F32_MAX] = {};
+    int n = 0;
+    const auto slabs = [&](float* out, int64_t elems) -> float* {          // where a product's sums go
+        if (p.splits == 1) return out;
+        float* const at = part;
+        part += (int64_t)p.splits * elems;
+        sums[n].slabs = at; sums[n].out = out; sums[n].n = elems; sums[n].slab = elems; sums[n].nslab = p.splits;
+        n++;
+        return at;
+    };
+    if (dA) {
+        a.a = operand(X, K); a.b = operand(dH, R); a.c = slabs(dA, na); a.ldc = R;
+        a.M = (int)K; a.N = (int)R; a.K = (int)M; a.alpha = 1.f; a.mid_scale = 1.f;
+        a.splits = p.splits; a.k_chunk = p.k_chunk; a.split_stride = na;
+    }
+    int groups = 0;
+    for (int i = 0; i < g && dB; i++) {
+        if (!dB[i]) continue;
+        b.ga[groups] = static_cast<const uint16_t*>(H) + i * r;
+        b.gb[groups] = dY[i];
+        b.gc[groups] = slabs(dB[i], nb);
+        groups++;
+    }
+    if (groups) {
+        b.a = operand(b.ga[0], R); b.b = operand(b.gb[0], N); b.c = b.gc[0]; b.ldc = N; b.groups = groups;
+        b.M = (int)r; b.N = (int)N; b.K = (int)M; b.alpha = 1.f; b.mid_scale = 1.f;
+        b.splits = p.splits; b.k_chunk = p.k_chunk; b.split_stride = nb;
+    }
+    if (dX) {
+        x.a = operand(dH, R); x.b = operand(A, R); x.c = dX; x.ldc = K;
+        x.M = (int)M; x.N = (int)K; x.K = (int)R; x.alpha = 1.f; x.mid_scale = 1.f;
+        x.splits = 1; x.k_chunk = (int)round_up(R, 64);
+    }
+    FHPC_HIP(launch_gemm_pp_backward(groups ? &b : nullptr, dA ? &a : nullptr, dX ? &x : nullptr, run.st));
+    if (n) FHPC_HIP(launch_sum_f32(sums, n, run.st));
+    return FHPC_OK;
+}
+static_assert(SUM_F32_MAX >= FHPC_MAX_SHARED + 1 && GEMM_MAX_GROUPS >= FHPC_MAX_SHARED, "dA and the dB of all layers on one X");
+
+// weight_grads for one factorised layer with plan_joint's launch, dX in it or (dX NULL) not
+int joint_layer_backward(const JointPlan& p, const void* X, const void* A, const void* dY, const void* H, const void* dH, void* dX, float* dA, float* dB,
+                         int64_t M, int64_t K, int64_t r, int64_t rp, int64_t N, const Scratch& s, Run& run)
+{
+    float* const ob = (dB && rp != r) ? s.dB_t : dB;
+    const int rc = joint_backward(p, X, A, &dY, H, dH, dX, (dA && rp != r) ? s.dA_t : dA, &ob, M, K, rp, N, 1, s.part, run);
+    if (rc || rp == r) return rc;
+    if (dA) FHPC_LAUNCH(run, launch_compact_f32(s.dA_t, rp, dA, r, K, r, 1.f, false, run.st));
+    if (dB) FHPC_LAUNCH(run, launch_compact_f32(s.dB_t, N, dB, N, r, N, 1.f, false, run.st));
     return FHPC_OK;
 }
 
@@ -1046,8 +1159,10 @@ int seq_lowrank_bwd(Run& run, const Scratch& s, const void* X, const void* A, co
     }
     if (dX || dA)
         FHPC_HIP(rank_product(OP_KC, operand(dY, N), operand(f.B, N), s.dH, rp, s.Hf, s.part, M, N, run));
-    if (dX)
+    const JointPlan joint = ((dA || dB) && !token_outer_pays(M, K, rp, N)) ? plan_joint(M, K, rp, N, 1) : JointPlan();
+    if (dX && !joint.with_dx)
         FHPC_HIP(product_bf16(OP_KC, operand(s.dH, rp), operand(f.A, rp), dX, K, K, M, rp, s.part, run));
+    if (joint.pays) return joint_layer_backward(joint, X, f.A, dY, H, s.dH, joint.with_dx ? dX : nullptr, dA, dB, M, K, r, rp, N, s, run);
     return weight_grads(X, dY, H, s.dH, dA, dB, M, K, r, rp, N, 1.f, s, run);
 }
 
@@ -1131,6 +1246,7 @@ struct SharedScratch {
 };
 
 static bool groupable_f32(int64_t M, int64_t N, int64_t Kred, int g);
+static int64_t grouped_dh_bytes(int64_t M, int64_t r, int64_t N, int g);
 
 static SharedScratch carve_shared(Carver& c, bool bwd, int64_t M, int64_t K, int64_t r, int64_t N, int g)
 {
@@ -1150,6 +1266,8 @@ static SharedScratch carve_shared(Carver& c, bool bwd, int64_t M, int64_t K, int
         // runs unsplit, except for g = 1, where the block is the whole (dense) matrix and may take the 32-row split
         if (r <= 32) upto(split_bytes(M, r, r, N));
         else if (g == 1) upto(product_part_bytes(M, r, N));
+        if (g > 1) upto(grouped_dh_bytes(M, r, N, g));  // dH_i in one launch in slices
+        upto(joint_part_bytes(M, K, r, N, g));         // dA_all and the dB_i in one launch, or
         upto(split_bytes(K, R, R, M));                 // dA_all = X^T dH_all
         // dB_i = H_i^T dY_i: one product's slabs, or all g products' when they go out in one launch
         if (groupable_f32(r, N, M, g)) {
@@ -1201,11 +1319,26 @@ static inline void* bf16_col(const void* p, int64_t col)
 // the request-fed kernels: one ramp and one tail instead of g, and the workgroups of the persistent shape run on
 // from one product into the next.  Whether that is possible for a product shape: unsplit bf16 output, or fp32
 // output (split or not), on the tiles those kernels serve.
+// Tile of a grouped launch: pick_tile's rule over the tiles of all g products, among the shapes that carry groups.  The
+// 256 x 128 shape is not persistent: over many rounds, and where a tile has next to no reduction, it has to be ahead by
+// more (2 x 4096 x 11008 from 1024: 274 microseconds in 11 rounds of it against 229 in six of 256 x 256; 2 x 16384 x 2752
+// from 96: 92 against 62).
+static int grouped_tile(int64_t M, int64_t Nout, int64_t Kred, int g, double* cost)
+{
+    const double large = (double)((tile_count(TILE_256x256, M, Nout) * g + num_cu() - 1) / num_cu()) * 256 * 256;
+    const double half = (double)((tile_count(TILE_256x128, M, Nout) * g + num_cu() - 1) / num_cu()) * 256 * 128 * (Kred <= 128 ? 1.4 : 1.15);
+    if (cost) *cost = half < large ? half : large;
+    return half < large ? TILE_256x128 : TILE_256x256;
+}
+
 static bool groupable_bf16(int b_mode, int64_t M, int64_t Nout, int64_t ldp, int64_t Kred, int g)
 {
     if (g < 2 || g > GEMM_MAX_GROUPS) return false;
     if (ldp == Nout && (large_split_pays(M, Nout, Kred) || split_pays(M, Nout, Kred))) return false;
-    return gemm_pp_supports(OP_KC, b_mode, OP_NONE, OUT_BF16, pick_tile(M, Nout, false));
+    // not where g launches on a smaller tile would be over sooner
+    double cost;
+    const int tile = grouped_tile(M, Nout, Kred, g, &cost);
+    return cost <= 1.15 * g * pick_cost(M, Nout) && gemm_pp_supports(OP_KC, b_mode, OP_NONE, OUT_BF16, tile);
 }
 
 // P_i[M][Nout] (bf16, row stride ldp) = a_i * b_i^(b_mode), i < g; a_i has k contiguous
@@ -1219,7 +1352,7 @@ static hipError_t grouped_bf16(int b_mode, const GemmOperand* a, const GemmOpera
     ga.alpha = 1.f; ga.mid_scale = 1.f; ga.splits = 1; ga.k_chunk = (int)round_up(Kred, 64);
     ga.groups = g;
     for (int i = 0; i < g; i++) { ga.ga[i] = a[i].ptr; ga.gb[i] = b[i].ptr; ga.gc[i] = P[i]; }
-    return launch_gemm_bf16(OP_KC, b_mode, OP_NONE, OUT_BF16, pick_tile(M, Nout, false), ga, run.st);
+    return launch_gemm_bf16(OP_KC, b_mode, OP_NONE, OUT_BF16, grouped_tile(M, Nout, Kred, g, nullptr), ga, run.st);
 }
 
 // C_i[M][N] (fp32, dense) = a_i^T-type products reduced over Kred (both operands reduction-major), i < g: the g
@@ -1228,6 +1361,47 @@ static bool groupable_f32(int64_t M, int64_t N, int64_t Kred, int g)
 {
     if (g < 2 || g > GEMM_MAX_GROUPS) return false;
     return gemm_pp_supports(OP_XC, OP_XC, OP_NONE, OUT_F32, plan_split(M, N, Kred).tile);
+}
+
+// dH_i = dY_i B_i^T of g layers into the column blocks of dH_all: few tiles under a long reduction.  All g products in
+// slices of at least 512 on the 256 x 128 tile in one launch, the slab sums of all blocks in another.  1 slice: not taken.
+static SplitPlan plan_grouped_dh(int64_t M, int64_t r, int64_t N, int g)
+{
+    SplitPlan sp = {TILE_256x128, 1, 0};
+    const int64_t tiles = tile_count(TILE_256x128, M, r) * g, steps = (N + 63) / 64;
+    int64_t s = num_cu() / tiles;
+    if (s > steps / 8) s = steps / 8;
+    if (r <= 32 || s < 2) return sp;
+    const int64_t per = (steps + s - 1) / s;
+    sp.k_chunk = (int)(per * 64);
+    sp.splits = (int)((steps + per - 1) / per);
+    return sp;
+}
+static int64_t grouped_dh_bytes(int64_t M, int64_t r, int64_t N, int g)
+{
+    const SplitPlan sp = plan_grouped_dh(M, r, N, g);
+    return sp.splits > 1 ? (int64_t)sp.splits * g * M * r * 4 : 0;
+}
+static hipError_t grouped_dh(const SplitPlan& sp, const void* const* dY, const void* const* B, void* dH, int64_t M, int64_t r, int64_t N, int g,
+                             float* part, Run& run)
+{
+    const int64_t n = M * r, R = r * g;
+    if (!run.claim((int64_t)sp.splits * g * n * 4)) return hipErrorOutOfMemory;
+    if (run.dry) return hipSuccess;
+    GemmArgs a = {};
+    SumF32Job sums[SUM_F32_MAX] = {};
+    a.a = operand(dY[0], N); a.b = operand(B[0], N); a.ldc = r;
+    a.M = (int)M; a.N = (int)r; a.K = (int)N; a.alpha = 1.f; a.mid_scale = 1.f;
+    a.splits = sp.splits; a.k_chunk = sp.k_chunk; a.split_stride = n; a.groups = g;
+    for (int i = 0; i < g; i++) {
+        float* const slabs = part + (int64_t)i * sp.splits * n;
+        a.ga[i] = dY[i]; a.gb[i] = B[i]; a.gc[i] = slabs;
+        sums[i].slabs = slabs; sums[i].out = bf16_col(dH, i * r); sums[i].n = n; sums[i].slab = n; sums[i].nslab = sp.splits;
+        sums[i].cols = (int)r; sums[i].ldo = R;
+    }
+    a.c = a.gc[0];
+    const hipError_t e = launch_gemm_bf16(OP_KC, OP_KC, OP_NONE, OUT_F32, sp.tile, a, run.st);
+    return e != hipSuccess ? e : launch_sum_f32(sums, g, run.st);
 }
 
 static hipError_t grouped_split_f32(const GemmOperand* a, const GemmOperand* b, float* const* C, int64_t M, int64_t N,
@@ -1284,7 +1458,10 @@ static int seq_shared_bwd(Run& run, const SharedScratch& s, const void* X, const
         FHPC_HIP(narrow_product(OP_XC, operand(X, K), operand(A_all, R), s.H, R, R, s.Pf, s.part, M, K, run));
         H = s.H;
     }
-    if ((dX || dA_all) && r > 32 && groupable_bf16(OP_KC, M, r, R, N, g)) {
+    const SplitPlan dh = plan_grouped_dh(M, r, N, g);
+    if ((dX || dA_all) && g > 1 && dh.splits > 1) {
+        FHPC_HIP(grouped_dh(dh, dY, B, s.dH, M, r, N, g, s.part, run));
+    } else if ((dX || dA_all) && r > 32 && groupable_bf16(OP_KC, M, r, R, N, g)) {
         GemmOperand a[GEMM_MAX_GROUPS], b[GEMM_MAX_GROUPS];
         void* P[GEMM_MAX_GROUPS];
         for (int i = 0; i < g; i++) { a[i] = operand(dY[i], N); b[i] = operand(B[i], N); P[i] = bf16_col(s.dH, i * r); }
@@ -1293,7 +1470,10 @@ static int seq_shared_bwd(Run& run, const SharedScratch& s, const void* X, const
         for (int i = 0; i < g; i++)
             FHPC_HIP(narrow_product(OP_KC, operand(dY[i], N), operand(B[i], N), bf16_col(s.dH, i * r), R, r, s.Pf, s.part, M, N, run));
     }
-    if (dX) FHPC_HIP(product_bf16(OP_KC, operand(s.dH, R), operand(A_all, R), dX, K, K, M, R, s.part, run));
+    const JointPlan joint = (dA_all || any_dB) ? plan_joint(M, K, r, N, g) : JointPlan();
+    if (dX && !joint.with_dx) FHPC_HIP(product_bf16(OP_KC, operand(s.dH, R), operand(A_all, R), dX, K, K, M, R, s.part, run));
+    if (joint.pays)
+        return joint_backward(joint, X, A_all, dY, H, s.dH, joint.with_dx ? dX : nullptr, dA_all, any_dB ? dB : nullptr, M, K, r, N, g, s.part, run);
     if (dA_all) FHPC_HIP(gemm_split_f32(OP_XC, OP_XC, operand(X, K), operand(s.dH, R), dA_all, R, K, R, M, 1.f, s.part, run));
     bool all_dB = any_dB;
     for (int i = 0; i < g && all_dB; i++) all_dB = dB[i] != nullptr;
@@ -1409,6 +1589,9 @@ static int seq_ffn_down_bwd(Run& run, const Scratch& s, const void* Z, const voi
         FHPC_HIP(product_bf16(OP_KC, operand(s.dH, rp), operand(f.A, rp), dU, K, K, M, rp, s.part, run));
         FHPC_LAUNCH(run, launch_swiglu_bwd(G, U, dU, dG, dU, M * K, true, run.st));
     }
+    // (by the same rule as lowrank_linear_bwd: the same bits)
+    const JointPlan joint = ((dA || dB) && !token_outer_pays(M, K, rp, N)) ? plan_joint(M, K, rp, N, 1) : JointPlan();
+    if (joint.pays) return joint_layer_backward(joint, Z, f.A, dY, H, s.dH, nullptr, dA, dB, M, K, r, rp, N, s, run);
     return weight_grads(Z, dY, H, s.dH, dA, dB, M, K, r, rp, N, 1.f, s, run);
 }
 

@@ -107,6 +107,10 @@ hipError_t launch_gemm_bf16(int a_mode, int b_mode, int b2_mode, int out_mode, i
 bool gemm_pp_supports(int a_mode, int b_mode, int b2_mode, int out_mode, int tile);
 hipError_t launch_gemm_pp(int a_mode, int b_mode, int out_mode, int tile, const GemmArgs& args, hipStream_t stream);
 
+// dB, dA (OP_XC, OP_XC, fp32 output) and dX (OP_KC, OP_KC, bf16 output) of a layer's backward pass in one launch on the
+// 256x128 tile; any of them may be NULL.
+hipError_t launch_gemm_pp_backward(const GemmArgs* db, const GemmArgs* da, const GemmArgs* dx, hipStream_t stream);
+
 // The four-wave kernel (gemm_w4.hip) covers the same products on the 256x256 tile.  It matches
 // the ping-pong kernels when the reduction is long and the output has at least one 256x256 tile
 // per compute unit, and loses to them otherwise, so it is selected only by args.dbg bit 3.

@@ -31,12 +31,17 @@ GemmF32Plan plan_gemm_f32(int jobs, const int64_t* M, const int64_t* N, const in
 int64_t gemm_f32_slab(int64_t M, int64_t N);      // floats of one slab of an M x N output
 hipError_t launch_gemm_f32(F32Layout al, F32Layout bl, const GemmF32Job* jobs, int count, int tile, hipStream_t s);
 
+// out[i] = sum of the slabs' elements i, i < n.  With cols > 0 the output is bf16 [n / cols][cols] with row stride ldo
+// (cols a multiple of 4, rows 8-byte aligned).
 struct SumF32Job {
     const float* slabs;
-    float* out;
+    void* out;
     int64_t n, slab;
     int nslab, blocks;
+    int cols;
+    int64_t ldo;
 };
+constexpr int SUM_F32_MAX = 9;                    // jobs of a launch
 hipError_t launch_sum_f32(const SumF32Job* jobs, int count, hipStream_t s);
 
 // Two chained products with the rank-r intermediate kept in LDS (r <= 64), see gemm_f32.hip:

@@ -6,6 +6,7 @@ namespace fhpc {
 
 typedef __attribute__((ext_vector_type(4))) float f32x4;
 typedef __attribute__((ext_vector_type(16))) float f32x16;
+typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4;
 
 // ---------------------------------------------------------------------------------
 // C[m][n] = sum_k a(m, k) b(n, k) on v_mfma_f32_32x32x2_f32: 256 flop per clock and compute unit, twice what separate
@@ -266,15 +267,17 @@ hipError_t launch_gemm_f32(F32Layout al, F32Layout bl, const GemmF32Job* jobs, i
 }
 
 // out[i] = sum over s of slabs[s * slab + i], in slab order; one thread per four outputs, the last ones singly.
-// Up to two sums share a launch.  Bound by reading the slabs once.
+// Several sums share a launch; fp32 output, or bf16 into a block of columns.  Bound by reading the slabs once.
 struct SumF32Args {
-    SumF32Job job[2];
+    SumF32Job job[SUM_F32_MAX];
+    int count;
 };
 __global__ __launch_bounds__(256) void sum_f32_kernel(SumF32Args args)
 {
-    const int which = ((int)blockIdx.x < args.job[0].blocks) ? 0 : 1;
+    int64_t block = blockIdx.x;
+    int which = 0;
+    while (which + 1 < args.count && block >= args.job[which].blocks) block -= args.job[which++].blocks;
     const SumF32Job& j = args.job[which];
-    const int64_t block = (int64_t)blockIdx.x - (which ? args.job[0].blocks : 0);
     const int64_t n4 = (j.n + 3) / 4;
     for (int64_t i = block * 256 + threadIdx.x; i < n4; i += (int64_t)j.blocks * 256) {
         f32x4 a = reinterpret_cast<const f32x4*>(j.slabs)[i];
@@ -289,26 +292,36 @@ __global__ __launch_bounds__(256) void sum_f32_kernel(SumF32Args args)
             for (int q = 0; q < 8; q++)
                 if (s0 + q < j.nslab) a += b[q];
         }
-        if (4 * i + 4 <= j.n) reinterpret_cast<f32x4*>(j.out)[i] = a;
-        else
-            for (int q = 0; 4 * i + q < j.n; q++) j.out[4 * i + q] = a[q];
+        if (j.cols > 0) {
+            const int64_t row = 4 * i / j.cols, col = 4 * i - row * j.cols;
+            bf16x4 o;
+#pragma unroll
+            for (int q = 0; q < 4; q++) o[q] = (__bf16)a[q];
+            *reinterpret_cast<bf16x4*>(static_cast<uint16_t*>(j.out) + row * j.ldo + col) = o;
+        } else if (4 * i + 4 <= j.n) {
+            static_cast<f32x4*>(j.out)[i] = a;
+        } else {
+            for (int q = 0; 4 * i + q < j.n; q++) static_cast<float*>(j.out)[4 * i + q] = a[q];
+        }
     }
 }
 
 hipError_t launch_sum_f32(const SumF32Job* jobs, int count, hipStream_t s)
 {
-    if (count < 1 || count > 2) return hipErrorInvalidValue;
+    if (count < 1 || count > SUM_F32_MAX) return hipErrorInvalidValue;
     SumF32Args a = {};
+    a.count = count;
     unsigned blocks = 0;
     for (int i = 0; i < count; i++) {
         a.job[i] = jobs[i];
+        if (jobs[i].cols < 0 || (jobs[i].cols > 0 && (jobs[i].cols % 4 != 0 || jobs[i].ldo % 4 != 0 || jobs[i].n % jobs[i].cols != 0)))
+            return hipErrorInvalidValue;
         int64_t b = ((jobs[i].n + 3) / 4 + 255) / 256;
         if (b > 8192) b = 8192;
         if (b < 1) b = 1;
         a.job[i].blocks = (int)b;
         blocks += (unsigned)b;
     }
-    if (count == 1) a.job[1] = a.job[0];
     hipLaunchKernelGGL(sum_f32_kernel, dim3(blocks), dim3(256), 0, s, a);
     return hipGetLastError();
 }

@@ -55,8 +55,13 @@ __device__ unsigned long long g_trace[TRACE_WGS * TRACE_SLOTS];
 #define FHPC_TS(slot) do { } while (0)
 #endif
 
+// LDS of an instantiation: the ring, and for bf16 output a 4 KiB patch private to each writing wave, outside the ring
+template <int BM, int BN, int BK, bool KSPLIT, int NSTAGE, int OUT_MODE>
+constexpr int lds_bytes() { return NSTAGE * (BM + BN) * BK * 2 + (OUT_MODE == OUT_BF16 ? (KSPLIT ? 4 : 8) * 32 * 64 * 2 : 0); }
+
+// One launch's work for this workgroup: the items `first`, `first` + `stride`, ... (k-split: `first` alone).
 template <int BM, int BN, int BK, bool KSPLIT, int NSTAGE, int A_MODE, int B_MODE, int OUT_MODE, int GATE = 0>
-__global__ __launch_bounds__(NT) void gemm_pp_kernel(GemmArgs p)
+__device__ __forceinline__ void pp_body(const GemmArgs& p, const int first, const int stride, unsigned char* const lds)
 {
     constexpr int TM = 4, TN = 2;                              // every wave: 128 x 64 accumulators
     constexpr int WTM = 128, WTN = 64;
@@ -74,12 +79,10 @@ __global__ __launch_bounds__(NT) void gemm_pp_kernel(GemmArgs p)
     constexpr int OUT_WAVES = KSPLIT ? 4 : 8;
     constexpr int PATCH_BYTES = 32 * WTN * 2;
     constexpr int LDS_BYTES = RING_BYTES + (OUT_MODE == OUT_BF16 ? OUT_WAVES * PATCH_BYTES : 0);
-    static_assert(LDS_BYTES <= 160 * 1024, "LDS ring and output patches");
+    static_assert(LDS_BYTES <= 160 * 1024 && LDS_BYTES == lds_bytes<BM, BN, BK, KSPLIT, NSTAGE, OUT_MODE>(), "LDS ring and output patches");
     static_assert(!KSPLIT || 4 * 128 * 256 <= RING_BYTES, "LDS for the accumulator hand-over");
     // The spatial shape is launched with one workgroup per compute unit that walks over output tiles.
     constexpr bool PERSISTENT = !KSPLIT;
-
-    __shared__ __attribute__((aligned(1024))) unsigned char lds[LDS_BYTES];
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
@@ -135,11 +138,11 @@ __global__ __launch_bounds__(NT) void gemm_pp_kernel(GemmArgs p)
     constexpr int STORES = TM * 4;
     bool chained = false, relaxed = false;
     FHPC_TS(0);
-    item_of(blockIdx.x, cur);
+    item_of(first, cur);
     int trace_tile = 0;
     (void)trace_tile;
 
-    for (int pid = blockIdx.x; pid < total; pid += gridDim.x) {
+    for (int pid = first; pid < total; pid += stride) {
     const int out_m0 = cur.m0, out_n0 = cur.n0, out_split = cur.split;
     void* const out_c = (p.groups > 1) ? p.gc[cur.grp] : p.c;
     const int kbeg = cur.kbeg, kend = cur.kend, kld = cur.kld;
@@ -156,8 +159,8 @@ __global__ __launch_bounds__(NT) void gemm_pp_kernel(GemmArgs p)
         fb.set_tile(p.b, cur.n0, p.N, wave, lane);
     }
     if (!chained) first_requests();
-    const bool has_next = PERSISTENT && pid + (int)gridDim.x < total;
-    if (has_next) item_of(pid + (int)gridDim.x, nxt);
+    const bool has_next = PERSISTENT && pid + stride < total;
+    if (has_next) item_of(pid + stride, nxt);
     // whole trips: the first k position past this item's loop
     const int kpad = kbeg + (kend - kbeg + NSTAGE * BK - 1) / (NSTAGE * BK) * (NSTAGE * BK);
     // (the successor's requests use this item's operand descriptors: no chaining into another product)
@@ -534,6 +537,27 @@ __global__ __launch_bounds__(NT) void gemm_pp_kernel(GemmArgs p)
     }
 }
 
+template <int BM, int BN, int BK, bool KSPLIT, int NSTAGE, int A_MODE, int B_MODE, int OUT_MODE, int GATE = 0>
+__global__ __launch_bounds__(NT) void gemm_pp_kernel(GemmArgs p)
+{
+    __shared__ __attribute__((aligned(1024))) unsigned char lds[lds_bytes<BM, BN, BK, KSPLIT, NSTAGE, OUT_MODE>()];
+    pp_body<BM, BN, BK, KSPLIT, NSTAGE, A_MODE, B_MODE, OUT_MODE, GATE>(p, (int)blockIdx.x, (int)gridDim.x, lds);
+}
+
+// The three products of a factorised layer's backward pass that follow dH, in one launch: dB = H^T dY and dA = X^T dH (fp32,
+// possibly in slices), dX = dH A^T (bf16).  For layers too small to fill the chip with one of them: at 1000 tokens,
+// 1600 -> 384 -> 6400, they take 100, 21 and 52 workgroups of the 256 x 128 shape, and as launches of their own each left most
+// compute units idle or was cut into slices whose slabs cost more than the slices gained (70 microseconds with the three
+// slab sums; 23 together).  The longest reductions come first.
+__global__ __launch_bounds__(NT) void gemm_pp_backward_kernel(GemmArgs db, GemmArgs da, GemmArgs dx, int blocks_db, int blocks_da)
+{
+    __shared__ __attribute__((aligned(1024))) unsigned char lds[lds_bytes<256, 128, 64, true, 3, OUT_BF16>()];
+    const int b = (int)blockIdx.x;
+    if (b < blocks_db) pp_body<256, 128, 64, true, 3, OP_XC, OP_XC, OUT_F32>(db, b, 1 << 30, lds);
+    else if (b < blocks_db + blocks_da) pp_body<256, 128, 64, true, 3, OP_XC, OP_XC, OUT_F32>(da, b - blocks_db, 1 << 30, lds);
+    else pp_body<256, 128, 64, true, 3, OP_KC, OP_KC, OUT_BF16>(dx, b - blocks_db - blocks_da, 1 << 30, lds);
+}
+
 }  // namespace pp
 
 // compute units of the current device, rounded down to whole multiples of the eight XCDs (256 when no
@@ -642,6 +666,31 @@ hipError_t launch_gemm_pp(int a_mode, int b_mode, int out_mode, int tile, const 
     if (a_mode == OP_KC && b_mode == OP_XC && out_mode == OUT_F32) return launch_pp_tile<OP_KC, OP_XC, OUT_F32>(tile, args, stream);
     if (a_mode == OP_KC && b_mode == OP_KC && out_mode == OUT_F32) return launch_pp_tile<OP_KC, OP_KC, OUT_F32>(tile, args, stream);
     return hipErrorInvalidValue;
+}
+
+hipError_t launch_gemm_pp_backward(const GemmArgs* db, const GemmArgs* da, const GemmArgs* dx, hipStream_t s)
+{
+    const GemmArgs* const given = db ? db : da ? da : dx;
+    if (!given) return hipErrorInvalidValue;
+    // whole multiples of eight workgroups each, so that the workgroup -> XCD map of every product holds (the surplus finds no item)
+    const auto blocks = [](const GemmArgs* a) {
+        if (!a) return 0;
+        const int n = ((a->M + 255) / 256) * ((a->N + 127) / 128) * (a->splits > 1 ? a->splits : 1) * (a->groups > 1 ? a->groups : 1);
+        return (n + 7) / 8 * 8;
+    };
+    const int n_db = blocks(db), n_da = blocks(da), n_dx = blocks(dx);
+    double flops = 0.0;
+    for (const GemmArgs* a : {db, da, dx}) {
+        if (!a) continue;
+        if (a->M <= 0 || a->N <= 0 || a->gate != 0 || a->n_split != 0) return hipErrorInvalidValue;
+        flops += 2.0 * a->M * a->N * (double)a->K * (a->groups > 1 ? a->groups : 1);
+    }
+    if (dx && dx->splits > 1) return hipErrorInvalidValue;
+    const int slot = prof_begin("gemm_pp_backward", flops, 0.0, s);
+    hipLaunchKernelGGL(pp::gemm_pp_backward_kernel, dim3((unsigned)(n_db + n_da + n_dx)), dim3(pp::NT), 0, s, db ? *db : *given, da ? *da : *given,
+                       dx ? *dx : *given, n_db, n_da);
+    prof_end(slot, s);
+    return hipGetLastError();
 }
 
 }  // namespace fhpc

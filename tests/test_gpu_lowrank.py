@@ -400,6 +400,62 @@ def test_shared_x_matches_the_single_layer_calls():
     torch.cuda.synchronize()
 
 
+@pytest.mark.parametrize("M,K,r,N", [
+    (65, 264, 40, 520),          # one token more than the vector-ALU gradients take at this rank; tiles mostly outside
+    (130, 1032, 100, 264),       # a padded rank
+    (1100, 264, 264, 776),       # ragged tiles of all three products; the reductions in slices
+    (300, 4096, 1024, 4104),     # two rounds of workgroups
+    (4097, 136, 64, 264),        # one token beyond two rounds
+])
+def test_backward_products_in_one_launch(M, K, r, N):
+    """dX, dA and dB of one layer from a single launch, against the oracle, between guard regions; each output has the same
+    bits when others are left out and when H is recomputed."""
+    import torch
+    fhpc = _fhpc()
+    X, A, B, dY = lowrank_inputs(12, M, K, r, N)
+    ref = oracle.lowrank_bwd(X.f64, A.f64, B.f64, dY.f64)
+    Xd, Ad, Bd, dYd = X.cuda(), A.cuda(), B.cuda(), dY.cuda()
+    _, H = fhpc.lowrank_linear_fwd(Xd, Ad, Bd, save_H=True)
+    guard = Guarded()
+    g = [guard.alloc((M, K), torch.bfloat16), guard.alloc((K, r), torch.float32), guard.alloc((r, N), torch.float32)]
+    out = fhpc.lowrank_linear_bwd(Xd, Ad, Bd, dYd, H_saved=H, dX=g[0], dA=g[1], dB=g[2])
+    guard.check("one launch %s" % ((M, K, r, N),))
+    _check_all("one launch %s" % ((M, K, r, N),), (None,) + out, (None,) + ref, TOL_BF16)
+    for want in ((True, True, False), (True, False, True), (False, True, True), (False, True, False)):
+        some = fhpc.lowrank_linear_bwd(Xd, Ad, Bd, dYd, need_dX=want[0], need_dA=want[1], need_dB=want[2])
+        assert all(s is None if not w else torch.equal(s, o) for s, o, w in zip(some, out, want)), want
+
+
+@pytest.mark.parametrize("M,K,r,N,g", [
+    (33, 264, 40, 1032, 2),      # few tokens; dH in slices into column blocks of 40
+    (200, 520, 136, 1032, 3),    # all of it in one launch, dH in slices
+    (1000, 264, 64, 2056, 8),    # the most layers on one X
+])
+def test_shared_x_backward_in_few_launches(M, K, r, N, g):
+    """dH of all layers in slices of one launch and the products that follow it in another, against the oracle's single
+    layers; each dB has the same bits when others are left out."""
+    import torch
+    fhpc = _fhpc()
+    X, A = Bf16.normal(1, (M, K)), Bf16.normal(2, (K, g * r), K ** -0.5)
+    Bs = [Bf16.normal(3 + i, (r, N), r ** -0.5) for i in range(g)]
+    dYs = [Bf16.normal(20 + i, (M, N)) for i in range(g)]
+    Xd, Ad, Bd, dYd = X.cuda(), A.cuda(), [b.cuda() for b in Bs], [d.cuda() for d in dYs]
+    guard = Guarded()
+    o = [guard.alloc((M, K), torch.bfloat16), guard.alloc((K, g * r), torch.float32), [guard.alloc((r, N), torch.float32) for _ in range(g)]]
+    dX, dA, dBs = fhpc.lowrank_linear_bwd_shared_x(Xd, Ad, Bd, dYd, dX=o[0], dA_all=o[1], dBs=o[2])
+    guard.check("shared one launch")
+    rX = 0.0
+    for i in range(g):
+        a = A.f64[:, i * r:(i + 1) * r]
+        x, da, db = oracle.lowrank_bwd(X.f64, np.ascontiguousarray(a), Bs[i].f64, dYs[i].f64)
+        rX = rX + x
+        assert parity_err(from_device(dA)[:, i * r:(i + 1) * r], da) <= TOL_BF16
+        assert parity_err(from_device(dBs[i]), db) <= TOL_BF16
+    assert parity_err(from_device(dX), rX) <= TOL_BF16
+    _, dA2, dB2 = fhpc.lowrank_linear_bwd_shared_x(Xd, Ad, Bd, dYd, need_dX=False, need_dB=[i % 2 == 1 for i in range(g)])
+    assert torch.equal(dA2, dA) and all(torch.equal(dB2[i], dBs[i]) for i in range(1, g, 2))
+
+
 @pytest.mark.parametrize("M,K,r,N,g", [(40, 264, 16, 136, 3), (300, 1024, 64, 2048, 2), (2500, 520, 128, 512, 3)])
 def test_shared_x_calls_write_their_scratch_before_they_read_it(M, K, r, N, g):
     """The binding hands the shared-X calls a workspace it has not cleared: with one full of NaN bit patterns they give
