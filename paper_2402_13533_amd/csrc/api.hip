@@ -7,6 +7,7 @@
 #include "kernels_misc.h"
 #include "merge.h"
 #include "qskinny.h"
+#include "rank_grads.h"
 
 #include <atomic>
 
@@ -772,6 +773,10 @@ int weight_grads(const void* X, const void* dY, const void* H, const void* dH, f
     // both products in one launch of the vector-ALU kernel
     if ((dA || dB) && token_outer_pays(M, K, rp, N)) {
         FHPC_LAUNCH(run, launch_token_outer_grads(X, dH, dA, H, dY, dB, M, K, r, rp, N, alpha, st));
+        return FHPC_OK;
+    }
+    if ((dA || dB) && rank_grads_pay(M, rp)) {
+        FHPC_LAUNCH(run, launch_rank_grads(X, dH, dA, H, dY, dB, M, K, r, rp, N, alpha, st));
         return FHPC_OK;
     }
     if (dA && dB) {

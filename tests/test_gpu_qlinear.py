@@ -473,6 +473,37 @@ def test_few_token_backward_optional_outputs_and_canaries(scheme, M, r):
     assert only_db[1] is None and torch.equal(only_db[0], ref[0]) and torch.equal(only_db[2], ref[2])
 
 
+@pytest.mark.parametrize("M,K,r,N", [(65, 72, 1, 136), (97, 256, 8, 200), (255, 320, 16, 64), (257, 8256, 12, 8136), (300, 8192, 17, 8200),
+                                     (1100, 512, 24, 264), (4096, 64, 32, 72)])
+def test_rank_gradients_in_one_launch(M, K, r, N):
+    """dA and dB at a rank of at most 32: part of a 32-token step, a wave without tokens, ragged column panels (64 and 128 wide),
+    ranks on both sides of 16, both outputs and each alone, nothing outside them."""
+    import torch
+    fhpc = _fhpc()
+    W, X, A, B, dY = qlinear_inputs(8, M, K, r, N, 61)
+    Wq, sc = _quantize_host(W, 8)
+    Wq_d, sc_d = _to_dev(Wq, sc)
+    Xd, Ad, Bd, dYd = X.cuda(), A.cuda(), B.cuda(), dY.cuda()
+    H = Bf16.normal(62, (M, r), 1.0)
+    pad = 64
+    bufs = [torch.full((n + 2 * pad,), float("nan"), device="cuda") for n in (K * r, r * N)]
+    dA, dB = bufs[0][pad:pad + K * r].view(K, r), bufs[1][pad:pad + r * N].view(r, N)
+    fhpc.qlinear_lowrank_bwd(Xd, Wq_d, sc_d, 8, Ad, Bd, 1.5, dYd, H_saved=H.cuda(), need_dX=False, dA=dA, dB=dB)
+    # fp32 sums of M exact products, the rounding of the scaled result, and for dA dH = dY B^T rounded to bf16 after an N-deep fp32 sum
+    u = 2.0 ** -24
+    aX, aY, aB, aH = np.abs(X.f64), np.abs(dY.f64), np.abs(B.f64), np.abs(H.f64)
+    dH, dH_abs = dY.f64 @ B.f64.T, aY @ aB.T
+    errB = np.abs(from_device(dB).astype(np.float64) - 1.5 * (H.f64.T @ dY.f64))
+    assert (errB <= 1.5 * (M + 2) * u * (aH.T @ aY) + 1e-30).all()
+    errA = np.abs(from_device(dA).astype(np.float64) - 1.5 * (X.f64.T @ dH))
+    assert (errA <= 1.5 * (aX.T @ (2.0 ** -8 * np.abs(dH) + 2 * (N + M + 2) * u * dH_abs)) + 1e-30).all()
+    for b in bufs:
+        assert torch.isnan(b[:pad]).all() and torch.isnan(b[-pad:]).all()
+    one = fhpc.qlinear_lowrank_bwd(Xd, Wq_d, sc_d, 8, Ad, Bd, 1.5, dYd, H_saved=H.cuda(), need_dX=False, need_dB=False)
+    two = fhpc.qlinear_lowrank_bwd(Xd, Wq_d, sc_d, 8, Ad, Bd, 1.5, dYd, H_saved=H.cuda(), need_dX=False, need_dA=False)
+    assert torch.equal(one[1], dA) and torch.equal(two[2], dB)
+
+
 def test_few_token_blend_backward():
     """The blend layer's backward at a handful of tokens: alpha scales the frozen-weight term of dX."""
     fhpc = _fhpc()
