@@ -632,7 +632,10 @@ __global__ __launch_bounds__(64 * TS_WAVES) void tall_skinny_kc_kernel(const uin
     }
 }
 
-// Large outputs with few slabs: one thread per float4 output adds its slabs in order.
+// Large outputs with few slabs (at most SUM_WIDE_SLABS): one thread per float4 output.  fp32 adds the slabs in order; bf16 in the
+// order of sum_slabs_kernel's four groups, so that a product rounds to the same bits whichever kernel adds its slabs (the subspace
+// iteration of lowrank_decompose amplifies a last-bit difference of its iterates to another, equally good pair).
+constexpr int SUM_WIDE_SLABS = 8;
 template <bool TO_BF16>
 __global__ __launch_bounds__(256) void sum_slabs_wide_kernel(const float* __restrict__ slabs, int64_t slab, int nslab,
                                                              void* __restrict__ out, int64_t n4)
@@ -640,14 +643,25 @@ __global__ __launch_bounds__(256) void sum_slabs_wide_kernel(const float* __rest
     typedef __attribute__((ext_vector_type(2))) uint32_t u32x2_t;
     const int64_t stride = (int64_t)gridDim.x * 256;
     for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n4; i += stride) {
-        f32x4 a = reinterpret_cast<const f32x4*>(slabs)[i];
-        for (int s = 1; s < nslab; s++) a += reinterpret_cast<const f32x4*>(slabs + (int64_t)s * slab)[i];
         if constexpr (TO_BF16) {
+            f32x4 v[SUM_WIDE_SLABS], part[4];
+#pragma unroll
+            for (int s = 0; s < SUM_WIDE_SLABS; s++)
+                if (s < nslab) v[s] = reinterpret_cast<const f32x4*>(slabs + (int64_t)s * slab)[i];
+#pragma unroll
+            for (int g = 0; g < 4; g++) {
+                part[g] = f32x4{0.f, 0.f, 0.f, 0.f};
+                if (g < nslab) part[g] += v[g];
+                if (g + 4 < nslab) part[g] += v[g + 4];
+            }
+            const f32x4 a = ((part[0] + part[1]) + part[2]) + part[3];
             u32x2_t o;
             o.x = bf16_pack(a.x, a.y);
             o.y = bf16_pack(a.z, a.w);
             reinterpret_cast<u32x2_t*>(out)[i] = o;
         } else {
+            f32x4 a = reinterpret_cast<const f32x4*>(slabs)[i];
+            for (int s = 1; s < nslab; s++) a += reinterpret_cast<const f32x4*>(slabs + (int64_t)s * slab)[i];
             reinterpret_cast<f32x4*>(out)[i] = a;
         }
     }
@@ -688,7 +702,7 @@ hipError_t launch_tall_skinny_kc(const void* L, int64_t ldl, const void* R, int6
 
 bool sum_slabs_is_small(int64_t n, int nslab)
 {
-    return !(nslab <= 8 && n / 4 >= 65536);
+    return !(nslab <= SUM_WIDE_SLABS && n / 4 >= 65536);
 }
 
 hipError_t launch_sum_slabs_pair(const float* slabs0, int64_t n0, int nslab0, float* out0,
