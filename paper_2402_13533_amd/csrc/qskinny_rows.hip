@@ -102,6 +102,7 @@ __global__ __launch_bounds__(64 * RH_NW) void qrows_h_kernel(RowJobs jb, const u
 }
 
 constexpr int ROWS_CH = 16, ROWS_NW = 4;      // channels and waves of a workgroup
+constexpr int ROWS_TOK = 16;                  // token rows of the matrix instructions: the most tokens of a call
 constexpr int SUM_LD = 20;                    // floats between channels of a wave's sums (16 tokens)
 constexpr int RX_PAD = 16;                    // bytes between token rows in LDS beyond their length
 constexpr int RX_MOST = 20480;                // elements of X a workgroup holds
@@ -293,6 +294,13 @@ __global__ __launch_bounds__(64 * ROWS_NW) void qrows_fwd_kernel(RowJobs jb, con
     }
 }
 
+// What the kernels hold: one block of token rows, in LDS (four workgroups to a unit), a thread per number of H, its
+// chunks in registers.
+static bool rows_fit(int64_t M, int64_t K, int64_t r)
+{
+    return M >= 1 && M <= ROWS_TOK && r >= 1 && r <= RH_MAX && (K % 256) == 0 && M * K <= RX_MOST && M * r <= 64 * ROWS_NW && K <= RH_MOST * RH_CHUNK;
+}
+
 }  // namespace skinny
 
 // Where it is the faster way (microseconds per call, replayed from a graph, one token, sliced kernel / this one):
@@ -301,12 +309,11 @@ __global__ __launch_bounds__(64 * ROWS_NW) void qrows_fwd_kernel(RowJobs jb, con
 //   more than 16 ranks, where the sliced kernel's chunks of H are what it waits for: 4096 -> 4096 r = 32 16.5 / 11.9,
 //   r = 64 25.4 / 20.5;
 //   a short reduction, few chunks of H to form: 2048 -> 4096 11.2 / 9.2.
-// The rest are its limits: the token rows in LDS (four workgroups to a unit), a thread per number of H, its chunks in
-// registers.
+// The rest are its limits.
 bool qskinny_rows_pay(int64_t M, int64_t K, int64_t r, int64_t N_all, int num_cu)
 {
     using namespace skinny;
-    if (M * K > RX_MOST || M * r > 64 * ROWS_NW || K > RH_MOST * RH_CHUNK) return false;
+    if (!rows_fit(M, K, r)) return false;
     return N_all >= (int64_t)3 * num_cu * ROWS_CH || r > 16 || K <= 2560;
 }
 
@@ -314,8 +321,7 @@ hipError_t launch_qskinny_rows(const void* X, const QskinnyJob* jobs, int count,
                                float* hpart, hipStream_t st)
 {
     using namespace skinny;
-    if (count < 1 || count > QSKINNY_MAX_JOBS || M < 1 || M > 16 || r < 1 || r > RH_MAX || (K % 256) != 0) return hipErrorInvalidValue;
-    if (M * K > RX_MOST || M * r > 64 * ROWS_NW || K > RH_MOST * RH_CHUNK) return hipErrorInvalidValue;
+    if (count < 1 || count > QSKINNY_MAX_JOBS || !rows_fit(M, K, r)) return hipErrorInvalidValue;
     RowJobs jb = {};
     jb.count = count;
     int wg = 0;

@@ -343,6 +343,36 @@ def test_few_token_forward_whole_rows(scheme, M, K, r, N):
 
 
 @pytest.mark.parametrize("scheme", [8, 4])
+@pytest.mark.parametrize("M,K,r,N", [
+    (17, 1024, 8, 264),        # one token more than the kernel with whole rows holds, everything else inside its limits
+    (20, 768, 12, 136),
+    (32, 512, 8, 16392),       # ... on a weight too wide for blocks of 16 tokens
+    (17, 1024, 15, 8264),
+    (64, 256, 4, 4168),
+])
+def test_more_tokens_than_whole_rows_hold(scheme, M, K, r, N):
+    """17 .. 64 tokens whose tokens x reduction and tokens x ranks would fit the kernel with whole rows: every call that can
+    reach it (one weight, no workspace, blend, weights on one X) goes through the sliced kernel, against the oracle."""
+    import torch
+    fhpc = _fhpc()
+    W, X, A, B, _ = qlinear_inputs(8, M, K, r, N, 265)
+    Wq, sc = _quantize_host(W, scheme)
+    Wd = oracle.dequant(Wq, sc, scheme, 64)
+    Wq_d, sc_d = _to_dev(Wq, sc)
+    Xd, Ad, Bd = X.cuda(), A.cuda(), B.cuda()
+    Yr, Hr = oracle.qlinear_lowrank_fwd(X.f64, Wd, A.f64, B.f64, 2.0)
+    Y, H = fhpc.qlinear_lowrank_fwd(Xd, Wq_d, sc_d, scheme, Ad, Bd, 2.0, save_H=True)
+    assert parity_err(from_device(Y), Yr) <= TOL_BF16 and parity_err(from_device(H), Hr) <= TOL_BF16
+    Y2 = torch.empty_like(Y)
+    fhpc.qlinear_lowrank_fwd_noalloc(Xd, Wq_d, sc_d, scheme, Ad, Bd, 2.0, Y2)
+    assert torch.equal(Y2, Y)
+    Yb = fhpc.qlinear_blend_fwd(Xd, Wq_d, sc_d, scheme, Ad, Bd, 0.25)
+    assert parity_err(from_device(Yb), oracle.blend_fwd(X.f64, Wd, A.f64, B.f64, 0.25)[0]) <= TOL_BF16
+    for Ys, Hs in fhpc.qlinear_lowrank_fwd_shared_x(Xd, [(Wq_d, sc_d, Ad, Bd, 2.0)] * 3, scheme, save_H=True):
+        assert parity_err(from_device(Ys), Yr) <= TOL_BF16 and parity_err(from_device(Hs), Hr) <= TOL_BF16
+
+
+@pytest.mark.parametrize("scheme", [8, 4])
 @pytest.mark.parametrize("M", [1, 16, 40, 100])
 def test_shared_x_forward(scheme, M):
     """Three projections that read the same X (widths as with grouped key/value heads, one of them not a
