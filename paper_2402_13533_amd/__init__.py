@@ -233,6 +233,8 @@ def get_workspace(nbytes: int, device):
     torch = _torch()
     if not isinstance(device, torch.device):
         device = torch.device(device)
+    if device.type != "cuda":
+        raise ValueError("a workspace is device memory, not %s" % device)
     index = device.index if device.index is not None else torch.cuda.current_device()
     key = (index, _raw_stream(index))
     ws = _workspaces.get(key)

@@ -170,3 +170,15 @@ def test_binding_refuses_cpu_tensors():
     x = torch.zeros((8, 64), dtype=torch.bfloat16)
     with pytest.raises(ValueError):
         fhpc.lowrank_linear_fwd(x, torch.zeros((64, 8), dtype=torch.bfloat16), torch.zeros((8, 64), dtype=torch.bfloat16))
+
+
+def test_workspaces_are_device_memory(monkeypatch):
+    """A host tensor must not end up in the cache under the current device's key, where every later call would find it."""
+    import torch
+    monkeypatch.setattr(torch.cuda, "current_device", lambda: 0)
+    monkeypatch.setattr(fhpc, "_raw_stream", lambda index: 0)
+    monkeypatch.setattr(fhpc, "_workspaces", {})
+    for device in ("cpu", torch.device("cpu"), "meta"):
+        with pytest.raises(ValueError):
+            fhpc.get_workspace(256, device)
+    assert not fhpc._workspaces
