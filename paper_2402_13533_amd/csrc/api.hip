@@ -1274,12 +1274,12 @@ static SharedScratch carve_shared(Carver& c, bool bwd, int64_t M, int64_t K, int
         if (g > 1) upto(grouped_dh_bytes(M, r, N, g));  // dH_i in one launch in slices
         upto(joint_part_bytes(M, K, r, N, g));         // dA_all and the dB_i in one launch, or
         upto(split_bytes(K, R, R, M));                 // dA_all = X^T dH_all
-        // dB_i = H_i^T dY_i: one product's slabs, or all g products' when they go out in one launch
+        // dB_i = H_i^T dY_i: one product's slabs (also where only some of the g are wanted), or all g products' when they
+        // go out in one launch
+        upto(split_bytes(r, N, N, M));
         if (groupable_f32(r, N, M, g)) {
             const SplitPlan gp = plan_split(r, N, M, false, g);
             upto(gp.splits > 1 ? (int64_t)g * gp.splits * r * N * 4 : 0);
-        } else {
-            upto(split_bytes(r, N, N, M));
         }
     }
     s.part = static_cast<float*>(c.take(part));
@@ -2269,8 +2269,8 @@ int fhpc_plan_slab_bytes(int call, int64_t M, int64_t K, int64_t r, int64_t N, i
         const void* in[FHPC_MAX_SHARED];
         void* out[FHPC_MAX_SHARED];
         float* dB[FHPC_MAX_SHARED];
-        for (int i = 0; i < g; i++) { in[i] = fake; out[i] = fake; dB[i] = o2; }
-        rc = bwd ? seq_shared_bwd(run, s, fake, fake, in, in, hs, o0, o1, dB, o2 != nullptr, M, K, r, N, g)
+        for (int i = 0; i < g; i++) { in[i] = fake; out[i] = fake; dB[i] = (i == 0 && (outputs & 16)) ? nullptr : o2; }
+        rc = bwd ? seq_shared_bwd(run, s, fake, fake, in, in, hs, o0, o1, dB, dB[g - 1] != nullptr, M, K, r, N, g)
                  : seq_shared_fwd(run, s, fake, fake, in, out, o0, M, K, r, N, g);
     } else if (call == FHPC_PLAN_FFN_GATE_UP) {
         rc = check_shared(M, K, r, N, 2);

@@ -50,6 +50,15 @@ def test_shared_x_slabs_fit():
         assert rc == 0 and 0 < planned <= reserved, (M, K, r, N, planned, reserved)
 
 
+def test_shared_x_slabs_fit_when_some_dB_are_left_out():
+    """The weight gradients that are wanted then go out one by one, each cut deeper than in the launch that carries all g."""
+    _assert_fits(fhpc.FHPC_PLAN_SHARED_BWD, "shared_bwd", M=1861, K=5816, r=296, N=5104, g=4, outputs=7 | 16)
+    for M, K, N, r, g in itertools.product(Ms, KNs, KNs, [8, 16, 32, 40, 64, 128, 296, 512, 1024], [1, 2, 3, 4, 8]):
+        if (M + K + N + r + g) % 3 == 0:
+            for outputs in (7 | 16, 4 | 8 | 16):
+                _assert_fits(fhpc.FHPC_PLAN_SHARED_BWD, "shared_bwd", M=M, K=K, r=r, N=N, g=g, outputs=outputs)
+
+
 def test_ffn_gate_calls_slabs_fit():
     """lowrank_ffn_gate_up_fwd and lowrank_ffn_down_bwd: the gate in the epilogue of the large tiles, the streaming
     gate kernel elsewhere, the same workspace layouts as the calls they stand for."""
