@@ -1436,12 +1436,10 @@ static hipError_t grouped_split_f32(const GemmOperand* a, const GemmOperand* b, 
     return hipSuccess;
 }
 
-static int seq_shared_fwd(Run& run, const SharedScratch& s, const void* X, const void* A_all, const void* const* B,
-                          void* const* Y, void* H_all_out, int64_t M, int64_t K, int64_t r, int64_t N, int g)
+// Y_i = H_i B_i of g layers, H_i the column blocks of H [M][g r]
+static int shared_outputs(Run& run, const SharedScratch& s, const void* H, const void* const* B, void* const* Y, int64_t M, int64_t r, int64_t N, int g)
 {
     const int64_t R = r * g;
-    void* H = H_all_out ? H_all_out : s.H;
-    FHPC_HIP(narrow_product(OP_XC, operand(X, K), operand(A_all, R), H, R, R, s.Pf, s.part, M, K, run));
     if (groupable_bf16(OP_XC, M, N, N, r, g)) {
         GemmOperand a[GEMM_MAX_GROUPS], b[GEMM_MAX_GROUPS];
         for (int i = 0; i < g; i++) { a[i] = operand(bf16_col(H, i * r), R); b[i] = operand(B[i], N); }
@@ -1451,6 +1449,15 @@ static int seq_shared_fwd(Run& run, const SharedScratch& s, const void* X, const
     for (int i = 0; i < g; i++)
         FHPC_HIP(product_bf16(OP_XC, operand(bf16_col(H, i * r), R), operand(B[i], N), Y[i], N, N, M, r, s.part, run));
     return FHPC_OK;
+}
+
+static int seq_shared_fwd(Run& run, const SharedScratch& s, const void* X, const void* A_all, const void* const* B,
+                          void* const* Y, void* H_all_out, int64_t M, int64_t K, int64_t r, int64_t N, int g)
+{
+    const int64_t R = r * g;
+    void* H = H_all_out ? H_all_out : s.H;
+    FHPC_HIP(narrow_product(OP_XC, operand(X, K), operand(A_all, R), H, R, R, s.Pf, s.part, M, K, run));
+    return shared_outputs(run, s, H, B, Y, M, r, N, g);
 }
 
 static int seq_shared_bwd(Run& run, const SharedScratch& s, const void* X, const void* A_all, const void* const* B,
@@ -1554,12 +1561,17 @@ static int seq_ffn_gate_up_fwd(Run& run, const SharedScratch& s, const void* X, 
     const int64_t R = 2 * r;
     void* H = H_all_out ? H_all_out : s.H;
     FHPC_HIP(narrow_product(OP_XC, operand(X, K), operand(A_all, R), H, R, R, s.Pf, s.part, M, K, run));
-    FHPC_HIP(product_bf16(OP_XC, operand(H, R), operand(B_gate, N), G, N, N, M, r, s.part, run));
-    if (gate_rides(M, N, r)) {
+    // (only where the shared-X call takes 256 x 256 tiles as well: another tile may add the reduction in another order, and the
+    // two calls promise the same bits)
+    if (gate_rides(M, N, r) && (!groupable_bf16(OP_XC, M, N, N, r, 2) || grouped_tile(M, N, r, 2, nullptr) == TILE_256x256)) {
+        FHPC_HIP(product_bf16(OP_XC, operand(H, R), operand(B_gate, N), G, N, N, M, r, s.part, run));
         FHPC_HIP(gemm_gated(OP_XC, operand(bf16_col(H, r), R), operand(B_up, N), U, M, N, r, 1, G, nullptr, Z, nullptr, run));
         return FHPC_OK;
     }
-    FHPC_HIP(product_bf16(OP_XC, operand(bf16_col(H, r), R), operand(B_up, N), U, N, N, M, r, s.part, run));
+    const void* const B[2] = {B_gate, B_up};
+    void* const Y[2] = {G, U};
+    const int rc = shared_outputs(run, s, H, B, Y, M, r, N, 2);
+    if (rc) return rc;
     FHPC_LAUNCH(run, launch_swiglu_fwd(G, U, Z, M * N, true, run.st));
     return FHPC_OK;
 }

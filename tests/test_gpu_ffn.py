@@ -188,6 +188,27 @@ def test_gate_in_the_epilogue_gives_the_bits_of_the_separate_calls(M, d, r, f):
         assert parity_err(from_device(got), ref) <= TOL_BF16, name
 
 
+@pytest.mark.parametrize("M,d,r,f", [
+    (1000, 256, 384, 6400),      # one projection alone would take 256 x 128 tiles, both together 256 x 256
+    (1697, 136, 960, 6208),
+    (400, 264, 136, 1000),       # both in one round of 256 x 128 tiles
+    (1290, 72, 40, 6704),        # a last, nearly empty round of 256 x 256 tiles
+    (70, 512, 640, 1032),        # the reduction in slices
+    (4096, 256, 72, 4104),       # the gate in the epilogue
+])
+def test_gate_up_forward_has_the_bits_of_the_shared_x_call(M, d, r, f):
+    """Whatever tiles the two calls take, G, U, Z and H of lowrank_ffn_gate_up_fwd are those of lowrank_linear_fwd_shared_x and
+    swiglu_fwd, bit for bit."""
+    import torch
+    fhpc = _fhpc()
+    X, _, (Ag, Bg, Au, Bu, _, _) = _ffn_inputs(M, d, r, f, base=60)
+    A_gu = torch.cat([Ag.cuda(), Au.cuda()], dim=1).contiguous()
+    (G0, U0), H0 = fhpc.lowrank_linear_fwd_shared_x(X.cuda(), A_gu, [Bg.cuda(), Bu.cuda()], save_H=True)
+    got = fhpc.lowrank_ffn_gate_up_fwd(X.cuda(), A_gu, Bg.cuda(), Bu.cuda(), save_H=True)
+    differ = [n for n, a, b in zip("GUZH", (G0, U0, fhpc.swiglu_fwd(G0, U0), H0), got) if not torch.equal(a.view(torch.int16), b.view(torch.int16))]
+    assert not differ
+
+
 def _oracle_ffn_full_size(X, dY, W, rows, J):
     """The oracle's chain on every token (G, U, Z, dZ, dG, dU in fp64), then: Y and dX on the token rows `rows`, and
     each weight gradient restricted to the rank indices J (column j of dA and row j of dB depend on the pair only
