@@ -515,7 +515,7 @@ int check_common(int64_t M, int64_t K, int64_t r, int64_t N)
 // 50 %; the 128x128 kernel runs two workgroups per compute unit).  What it decides in practice: an
 // output of 320 tiles of 256x256 (4096 tokens x 5120 channels) would run two rounds, the second a
 // quarter full; as 640 tiles of 256x128 it runs 2.5 (measured 196 against 217 microseconds).
-int pick_tile(int64_t M, int64_t N, bool allow_skinny, double* cost_out = nullptr)
+int pick_tile(int64_t M, int64_t N, bool allow_skinny)
 {
     if (allow_skinny && N <= 32) return TILE_256x32;
     if (allow_skinny && M <= 32) return TILE_32x256;
@@ -536,16 +536,8 @@ int pick_tile(int64_t M, int64_t N, bool allow_skinny, double* cost_out = nullpt
             best_cost = cost;
         }
     }
-    if (cost_out) *cost_out = best_cost;
     return best;
 }
-double pick_cost(int64_t M, int64_t N)
-{
-    double cost = 0.0;
-    pick_tile(M, N, false, &cost);
-    return cost;
-}
-
 // What pick_tile minimises, for the tile it picks.
 static double tile_cost(int64_t M, int64_t N, int* tile_out)
 {
@@ -1324,26 +1316,24 @@ static inline void* bf16_col(const void* p, int64_t col)
 // the request-fed kernels: one ramp and one tail instead of g, and the workgroups of the persistent shape run on
 // from one product into the next.  Whether that is possible for a product shape: unsplit bf16 output, or fp32
 // output (split or not), on the tiles those kernels serve.
-// Tile of a grouped launch: pick_tile's rule over the tiles of all g products, among the shapes that carry groups.  The
-// 256 x 128 shape is not persistent: over many rounds, and where a tile has next to no reduction, it has to be ahead by
-// more (2 x 4096 x 11008 from 1024: 274 microseconds in 11 rounds of it against 229 in six of 256 x 256; 2 x 16384 x 2752
-// from 96: 92 against 62).
-static int grouped_tile(int64_t M, int64_t Nout, int64_t Kred, int g, double* cost)
+// Tile of a grouped launch, among the shapes that carry groups: 256 x 256, whose workgroups walk on from tile to tile, unless the
+// tiles of all g products are so few that 256 x 128 halves the rounds.  Microseconds of the shared-X forward, 256 x 128 / 256 x
+// 256 / g launches: one round of either 22 / 24 / 34 (3 x 310 x 3952 from 168), two of either 40 / 43 / 42 (2 x 10910 x 528 from
+// 184), three against two 47 / 39 / 52 (3 x 966 x 6648 from 224), four against three 54 / 47 / 64 (4 x 11863 x 608 from 72), five
+// against three 121 / 101 / 108 (3 x 7853 x 1432 from 584).  Of 750 shapes of 2 .. 8 products at 2 .. 16384 tokens, g launches
+// are ahead of this by more than the noise (5 %) on two.
+static int grouped_tile(int64_t M, int64_t Nout, int g)
 {
-    const double large = (double)((tile_count(TILE_256x256, M, Nout) * g + num_cu() - 1) / num_cu()) * 256 * 256;
-    const double half = (double)((tile_count(TILE_256x128, M, Nout) * g + num_cu() - 1) / num_cu()) * 256 * 128 * (Kred <= 128 ? 1.4 : 1.15);
-    if (cost) *cost = half < large ? half : large;
-    return half < large ? TILE_256x128 : TILE_256x256;
+    const int64_t large = (tile_count(TILE_256x256, M, Nout) * g + num_cu() - 1) / num_cu();
+    const int64_t half = (tile_count(TILE_256x128, M, Nout) * g + num_cu() - 1) / num_cu();
+    return 4 * half < 5 * large ? TILE_256x128 : TILE_256x256;
 }
 
 static bool groupable_bf16(int b_mode, int64_t M, int64_t Nout, int64_t ldp, int64_t Kred, int g)
 {
     if (g < 2 || g > GEMM_MAX_GROUPS) return false;
     if (ldp == Nout && (large_split_pays(M, Nout, Kred) || split_pays(M, Nout, Kred))) return false;
-    // not where g launches on a smaller tile would be over sooner
-    double cost;
-    const int tile = grouped_tile(M, Nout, Kred, g, &cost);
-    return cost <= 1.15 * g * pick_cost(M, Nout) && gemm_pp_supports(OP_KC, b_mode, OP_NONE, OUT_BF16, tile);
+    return gemm_pp_supports(OP_KC, b_mode, OP_NONE, OUT_BF16, grouped_tile(M, Nout, g));
 }
 
 // P_i[M][Nout] (bf16, row stride ldp) = a_i * b_i^(b_mode), i < g; a_i has k contiguous
@@ -1357,7 +1347,7 @@ static hipError_t grouped_bf16(int b_mode, const GemmOperand* a, const GemmOpera
     ga.alpha = 1.f; ga.mid_scale = 1.f; ga.splits = 1; ga.k_chunk = (int)round_up(Kred, 64);
     ga.groups = g;
     for (int i = 0; i < g; i++) { ga.ga[i] = a[i].ptr; ga.gb[i] = b[i].ptr; ga.gc[i] = P[i]; }
-    return launch_gemm_bf16(OP_KC, b_mode, OP_NONE, OUT_BF16, grouped_tile(M, Nout, Kred, g, nullptr), ga, run.st);
+    return launch_gemm_bf16(OP_KC, b_mode, OP_NONE, OUT_BF16, grouped_tile(M, Nout, g), ga, run.st);
 }
 
 // C_i[M][N] (fp32, dense) = a_i^T-type products reduced over Kred (both operands reduction-major), i < g: the g
@@ -1563,7 +1553,7 @@ static int seq_ffn_gate_up_fwd(Run& run, const SharedScratch& s, const void* X, 
     FHPC_HIP(narrow_product(OP_XC, operand(X, K), operand(A_all, R), H, R, R, s.Pf, s.part, M, K, run));
     // (only where the shared-X call takes 256 x 256 tiles as well: another tile may add the reduction in another order, and the
     // two calls promise the same bits)
-    if (gate_rides(M, N, r) && (!groupable_bf16(OP_XC, M, N, N, r, 2) || grouped_tile(M, N, r, 2, nullptr) == TILE_256x256)) {
+    if (gate_rides(M, N, r) && (!groupable_bf16(OP_XC, M, N, N, r, 2) || grouped_tile(M, N, 2) == TILE_256x256)) {
         FHPC_HIP(product_bf16(OP_XC, operand(H, R), operand(B_gate, N), G, N, N, M, r, s.part, run));
         FHPC_HIP(gemm_gated(OP_XC, operand(bf16_col(H, r), R), operand(B_up, N), U, M, N, r, 1, G, nullptr, Z, nullptr, run));
         return FHPC_OK;
