@@ -427,6 +427,31 @@ def test_backward_products_in_one_launch(M, K, r, N):
 
 
 @pytest.mark.parametrize("M,K,r,N,g", [
+    (65, 264, 40, 520, 1),       # dX in the launch of the weight gradients
+    (300, 4096, 1024, 4104, 1),
+    (1100, 2056, 264, 776, 2),
+    (33, 264, 40, 1032, 2),
+    (40, 264, 40, 520, 1),       # few tokens: gradients on the vector ALU, dX by itself
+    (4200, 2056, 40, 520, 1),    # dX by itself, beside a launch of the weight gradients
+    (4200, 2056, 40, 520, 2),
+])
+def test_input_gradient_alone_has_the_bits_of_the_full_call(M, K, r, N, g):
+    """dX of a frozen pair (no weight gradients wanted), of one layer and of g on one X."""
+    import torch
+    fhpc = _fhpc()
+    X, A = Bf16.normal(1, (M, K)).cuda(), Bf16.normal(2, (K, g * r), K ** -0.5).cuda()
+    Bs = [Bf16.normal(3 + i, (r, N), r ** -0.5).cuda() for i in range(g)]
+    dYs = [Bf16.normal(20 + i, (M, N)).cuda() for i in range(g)]
+    if g == 1:
+        full = fhpc.lowrank_linear_bwd(X, A, Bs[0], dYs[0])
+        alone = fhpc.lowrank_linear_bwd(X, A, Bs[0], dYs[0], need_dA=False, need_dB=False)
+        assert alone[1] is None and alone[2] is None and bool((alone[0] == full[0]).all())
+    full = fhpc.lowrank_linear_bwd_shared_x(X, A, Bs, dYs)
+    alone = fhpc.lowrank_linear_bwd_shared_x(X, A, Bs, dYs, need_dA=False, need_dB=False)
+    assert alone[1] is None and bool((alone[0] == full[0]).all())
+
+
+@pytest.mark.parametrize("M,K,r,N,g", [
     (33, 264, 40, 1032, 2),      # few tokens; dH in slices into column blocks of 40
     (200, 520, 136, 1032, 3),    # all of it in one launch, dH in slices
     (1000, 264, 64, 2056, 8),    # the most layers on one X
