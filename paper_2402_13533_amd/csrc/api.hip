@@ -1568,8 +1568,8 @@ static int seq_ffn_gate_up_fwd(Run& run, const SharedScratch& s, const void* X, 
 }
 
 // Backward of the down projection Y = (Z A) B with its input gradient taken through the gate: the tiles of
-// dZ = dH A^T leave as dG and dU, and dZ is never stored.  Without the gate epilogue (small or narrow outputs) dZ is
-// written where dU will be and the streaming gate kernel turns it into dG and dU in place.
+// dZ = dH A^T leave as dG and dU, and dZ is never stored.  Without the gate epilogue (small or narrow outputs, or dZ in the launch
+// of the weight gradients) dZ is written where dU will be and the streaming gate kernel turns it into dG and dU in place.
 static int seq_ffn_down_bwd(Run& run, const Scratch& s, const void* Z, const void* A, const void* B, const void* dY,
                             const void* H_saved, const void* G, const void* U, void* dG, void* dU, float* dA, float* dB,
                             int64_t M, int64_t K, int64_t r, int64_t N)
@@ -1591,16 +1591,19 @@ static int seq_ffn_down_bwd(Run& run, const Scratch& s, const void* Z, const voi
         }
     }
     FHPC_HIP(rank_product(OP_KC, operand(dY, N), operand(f.B, N), s.dH, rp, s.Hf, s.part, M, N, run));
-    if (gate_rides(M, K, rp)) {
+    // (by the same rule as lowrank_linear_bwd, dX there being dZ here: the same bits)
+    const JointPlan joint = token_outer_pays(M, K, rp, N) ? JointPlan() : plan_joint(M, K, rp, N, 1);
+    const bool gated = !joint.with_dx && gate_rides(M, K, rp);
+    if (gated) {
         FHPC_HIP(gemm_gated(OP_KC, operand(s.dH, rp), operand(f.A, rp), nullptr, M, K, rp, 2, G, U, dG, dU, run));
-    } else {
+    } else if (!joint.with_dx) {
         FHPC_HIP(product_bf16(OP_KC, operand(s.dH, rp), operand(f.A, rp), dU, K, K, M, rp, s.part, run));
-        FHPC_LAUNCH(run, launch_swiglu_bwd(G, U, dU, dG, dU, M * K, true, run.st));
     }
-    // (by the same rule as lowrank_linear_bwd: the same bits)
-    const JointPlan joint = ((dA || dB) && !token_outer_pays(M, K, rp, N)) ? plan_joint(M, K, rp, N, 1) : JointPlan();
-    if (joint.pays) return joint_layer_backward(joint, Z, f.A, dY, H, s.dH, nullptr, dA, dB, M, K, r, rp, N, s, run);
-    return weight_grads(Z, dY, H, s.dH, dA, dB, M, K, r, rp, N, 1.f, s, run);
+    rc = joint.pays ? joint_layer_backward(joint, Z, f.A, dY, H, s.dH, joint.with_dx ? dU : nullptr, dA, dB, M, K, r, rp, N, s, run)
+                    : weight_grads(Z, dY, H, s.dH, dA, dB, M, K, r, rp, N, 1.f, s, run);
+    if (rc) return rc;
+    if (!gated) FHPC_LAUNCH(run, launch_swiglu_bwd(G, U, dU, dG, dU, M * K, true, run.st));
+    return FHPC_OK;
 }
 
 int lowrank_ffn_gate_up_fwd(const void* X, const void* A_all, const void* B_gate, const void* B_up,

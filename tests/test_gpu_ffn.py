@@ -209,6 +209,29 @@ def test_gate_up_forward_has_the_bits_of_the_shared_x_call(M, d, r, f):
     assert not differ
 
 
+@pytest.mark.parametrize("M,f,r,d", [
+    (2048, 5504, 256, 264),      # 256 x 256 tiles would fit the gate, but dZ shares the launch of the weight gradients
+    (1100, 11008, 72, 264),
+    (300, 776, 136, 520),        # the same on a small layer
+    (20, 776, 24, 264),          # gradients on the vector ALU
+    (4200, 4104, 40, 264),       # the gate in the epilogue, the weight gradients in one launch
+    (300, 4104, 1024, 1032),     # two rounds of workgroups
+])
+def test_down_backward_has_the_bits_of_the_separate_calls(M, f, r, d):
+    """dG, dU, dA and dB of lowrank_ffn_down_bwd are those of lowrank_linear_bwd and swiglu_bwd bit for bit, also where dX
+    shares a launch with the weight gradients; dG and dU also without them."""
+    import torch
+    fhpc = _fhpc()
+    Z, dY, G, U = (Bf16.normal(i, s).cuda() for i, s in ((1, (M, f)), (2, (M, d)), (3, (M, f)), (4, (M, f))))
+    A, B = Bf16.normal(5, (f, r), f ** -0.5).cuda(), Bf16.normal(6, (r, d), r ** -0.5).cuda()
+    dZ, dA, dB = fhpc.lowrank_linear_bwd(Z, A, B, dY)
+    want = (*fhpc.swiglu_bwd(G, U, dZ), dA, dB)
+    got = fhpc.lowrank_ffn_down_bwd(Z, A, B, dY, G, U)
+    alone = fhpc.lowrank_ffn_down_bwd(Z, A, B, dY, G, U, need_dA=False, need_dB=False)
+    assert [torch.equal(a, b) for a, b in zip(got, want)] == [True] * 4
+    assert [torch.equal(a, b) for a, b in zip(alone[:2], want)] == [True] * 2
+
+
 def _oracle_ffn_full_size(X, dY, W, rows, J):
     """The oracle's chain on every token (G, U, Z, dZ, dG, dU in fp64), then: Y and dX on the token rows `rows`, and
     each weight gradient restricted to the rank indices J (column j of dA and row j of dB depend on the pair only
