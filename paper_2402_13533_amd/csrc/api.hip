@@ -398,18 +398,25 @@ JointPlan plan_joint(int64_t M, int64_t K, int64_t r, int64_t N, int g)
     // 4096 tokens 73 / 31, 91 / 46, 119 / 97; 4096 -> 512 -> 4096 at 300 / 2000 / 16384 83 / 30, 104 / 67, 312 / 306;
     // 4096 -> 1024 -> 11008 (two rounds) at 300 / 4096 121 / 74, 316 / 286.  Four rounds gain or lose a few per cent.
     const int64_t R = r * g, units = num_cu(), limit = units * (M <= 4096 ? 2 : 1);
-    // (a long reduction on tiles a good part of whose rows lie beyond the rank: 1600 -> 384 -> 6400 at 16384 tokens 260 / 265)
-    if (r <= 32 || (M > 8192 && r > 256 && r % 256 != 0)) return p;
+    if (r <= 32) return p;
     const auto blocks = [](int64_t tiles) { return round_up(tiles, 8); };
     const int64_t n_db = blocks(tile_count(TILE_256x128, r, N) * g), n_da = blocks(tile_count(TILE_256x128, K, R));
     const int64_t n_dx = blocks(tile_count(TILE_256x128, M, K)), steps = (M + 63) / 64;
     if (n_db + n_da > limit) return p;
+    const auto depth = [&](int64_t room) {         // 64-deep steps of a slice when `room` workgroups share the reductions
+        int64_t s = room / (n_db + n_da);
+        if (s > steps / 8) s = steps / 8;
+        return s > 1 ? (steps + s - 1) / s : steps;
+    };
+    // a long reduction on tiles a good part of whose rows lie beyond the rank (1600 -> 384 -> 6400 at 16384 tokens 260 / 265,
+    // 1104 -> 104 -> 8032 at 15922, 83 steps, 226 / 239)
+    if (M > 8192 && r % 256 != 0 && (r > 256 || (g == 1 && depth(units) > 72))) return p;
     p.pays = true;
-    p.with_dx = n_db + n_da + n_dx <= limit;
-    int64_t s = (units - (p.with_dx ? n_dx : 0)) / (n_db + n_da);
-    if (s > steps / 8) s = steps / 8;
-    if (s < 1) s = 1;
-    const int64_t per = (steps + s - 1) / s;
+    // dX saves a launch (4 .. 10 microseconds) where the units it takes do not leave the slices of the others much longer: the two
+    // are even at 24 steps more, 32 where dX may run in a second round (microseconds without / with dX, steps: 41 against 11 80 /
+    // 74, 45 against 9 69 / 71, 39 against 9 55 / 61, 84 against 9 65 / 89, 236 against 15 56 / 155)
+    p.with_dx = n_db + n_da + n_dx <= limit && depth(units - n_dx) - depth(units) <= (M <= 4096 ? 32 : 24);
+    const int64_t per = depth(units - (p.with_dx ? n_dx : 0));
     p.k_chunk = (int)(per * 64);
     p.splits = (int)((steps + per - 1) / per);
     return p;

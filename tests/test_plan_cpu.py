@@ -59,6 +59,15 @@ def test_shared_x_slabs_fit_when_some_dB_are_left_out():
                 _assert_fits(fhpc.FHPC_PLAN_SHARED_BWD, "shared_bwd", M=M, K=K, r=r, N=N, g=g, outputs=outputs)
 
 
+@pytest.mark.parametrize("M,K,r,N,g", [(15060, 464, 168, 368, 1), (9531, 664, 48, 576, 1), (5315, 1192, 200, 912, 1), (9339, 608, 96, 568, 4)])
+def test_input_gradient_does_not_displace_the_slices_of_the_weight_gradients(M, K, r, N, g):
+    """Many tokens on a small layer: the tiles of dX would leave one workgroup per tile of dA and dB to walk all tokens
+    (155 microseconds against 56 on the first of these)."""
+    call = fhpc.FHPC_OP_LOWRANK_BWD if g == 1 else fhpc.FHPC_PLAN_SHARED_BWD
+    slabs = _assert_fits(call, "dB", M=M, K=K, r=r, N=N, g=g, outputs=4 | 8)          # (the slabs of dA and dB, nothing else)
+    assert slabs >= 4 * 4 * g * r * (K + N)
+
+
 def test_ffn_gate_calls_slabs_fit():
     """lowrank_ffn_gate_up_fwd and lowrank_ffn_down_bwd: the gate in the epilogue of the large tiles, the streaming
     gate kernel elsewhere, the same workspace layouts as the calls they stand for."""
