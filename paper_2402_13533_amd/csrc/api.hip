@@ -226,9 +226,12 @@ bool split_pays(int64_t M, int64_t Nout, int64_t Kred)
     if (Nout <= 32) return false;
     if (M > 32) {
         const int64_t tiles = ((M + 127) / 128) * ((Nout + 127) / 128);
-        // (at most 512 deep, eight steps: the slices save less than their slab sum costs; forward of 4096 -> 512 -> 4096 at 64 /
-        // 300 tokens 24 -> 21, 31 -> 24 microseconds, 2048 -> 256 -> 2048 at 600 26 -> 19; a tile or two stay in slices)
-        if (2 * tiles > num_cu() || Kred < 256 || (Kred <= 512 && tiles >= 4)) return false;
+        if (2 * tiles > num_cu() || Kred < 256) return false;
+        // at most 512 deep, eight steps, the slices save less than their slab sum costs once the output is large enough (forward,
+        // microseconds, slices / whole: 4096 -> 512 -> 4096 at 64 / 300 tokens 24 / 21, 31 / 24, 2048 -> 256 -> 2048 at 600 26 / 19;
+        // but X A at 695 tokens, 416 -> 48, 17 / 19, at 386, 504 -> 112, 18 / 19).  The two are even at 32 K outputs, 128 K on
+        // narrow ones, whose 128-wide tiles are mostly outside, and half as much again beyond 384.
+        if (Kred <= 512 && 2 * M * Nout >= (int64_t)(Nout > 256 ? 32768 : 131072) * (Kred > 384 ? 3 : 2)) return false;
     }
     return plan_split(M, Nout, Kred, true).splits > 1;
 }

@@ -68,6 +68,13 @@ def test_input_gradient_does_not_displace_the_slices_of_the_weight_gradients(M, 
     assert slabs >= 4 * 4 * g * r * (K + N)
 
 
+@pytest.mark.parametrize("M,K,r,N,sliced", [(936, 416, 40, 264, True), (386, 504, 112, 688, True), (153, 448, 168, 264, True), (1430, 464, 45, 704, True),
+                                            (600, 264, 256, 2048, False), (590, 264, 264, 712, False), (1431, 360, 160, 264, False)])
+def test_short_reductions_in_slices(M, K, r, N, sliced):
+    """H = X A of few ranks goes out in slices of a reduction down to 256, larger outputs whole (what either takes stands at the rule)."""
+    assert (_assert_fits(fhpc.FHPC_OP_LOWRANK_FWD, "forward", M=M, K=K, r=r, N=N, outputs=1) > 0) == sliced
+
+
 def test_ffn_gate_calls_slabs_fit():
     """lowrank_ffn_gate_up_fwd and lowrank_ffn_down_bwd: the gate in the epilogue of the large tiles, the streaming
     gate kernel elsewhere, the same workspace layouts as the calls they stand for."""
