@@ -421,7 +421,7 @@ def test_backward_products_in_one_launch(M, K, r, N):
     out = fhpc.lowrank_linear_bwd(Xd, Ad, Bd, dYd, H_saved=H, dX=g[0], dA=g[1], dB=g[2])
     guard.check("one launch %s" % ((M, K, r, N),))
     _check_all("one launch %s" % ((M, K, r, N),), (None,) + out, (None,) + ref, TOL_BF16)
-    for want in ((True, True, False), (True, False, True), (False, True, True), (False, True, False)):
+    for want in ((True, True, False), (True, False, True), (False, True, True), (False, True, False), (True, False, False)):
         some = fhpc.lowrank_linear_bwd(Xd, Ad, Bd, dYd, need_dX=want[0], need_dA=want[1], need_dB=want[2])
         assert all(s is None if not w else torch.equal(s, o) for s, o, w in zip(some, out, want)), want
 
@@ -497,5 +497,7 @@ def test_shared_x_calls_write_their_scratch_before_they_read_it(M, K, r, N, g):
         Ys, H = fhpc.lowrank_linear_fwd_shared_x(X, A, Bs, save_H=True, workspace=ws)
         ws.fill_(fill)
         dX, dA, dBs = fhpc.lowrank_linear_bwd_shared_x(X, A, Bs, dYs, workspace=ws)
-        got.append([*Ys, H, dX, dA, *dBs])
+        ws.fill_(fill)
+        gate_up = fhpc.lowrank_ffn_gate_up_fwd(X, A[:, :2 * r].contiguous(), Bs[0], Bs[1], save_H=True, workspace=ws)
+        got.append([*Ys, H, dX, dA, *dBs, *gate_up])
     assert all(torch.equal(a, b) for a, b in zip(*got))

@@ -624,12 +624,13 @@ def test_blend_layer_dense_weight(M):
         fhpc.qlinear_lowrank_fwd(Xd, Wd_, None, fhpc.FHPC_W_BF16, Ad, Bd, 2.0)
 
 
-def test_few_token_forward_in_a_hip_graph():
+@pytest.mark.parametrize("K", [2048, 2816])          # workgroups with whole rows; slices with arrival counters
+def test_few_token_forward_in_a_hip_graph(K):
     """The few-token forward enqueues kernels only, so a caller can capture it in a HIP graph: three
     replays, with eager work and synchronisations in between, must each reproduce the eager result."""
     import torch
     fhpc = _fhpc()
-    M, K, r, N = 8, 2048, 16, 328
+    M, r, N = 8, 16, 328
     W, X, A, B, _ = qlinear_inputs(8, M, K, r, N, 97)
     Wq, sc = _quantize_host(W, 4)
     Wq_d, sc_d = _to_dev(Wq, sc)
