@@ -1327,24 +1327,26 @@ static inline void* bf16_col(const void* p, int64_t col)
 // the request-fed kernels: one ramp and one tail instead of g, and the workgroups of the persistent shape run on
 // from one product into the next.  Whether that is possible for a product shape: unsplit bf16 output, or fp32
 // output (split or not), on the tiles those kernels serve.
-// Tile of a grouped launch, among the shapes that carry groups: 256 x 256, whose workgroups walk on from tile to tile, unless the
-// tiles of all g products are so few that 256 x 128 halves the rounds.  Microseconds of the shared-X forward, 256 x 128 / 256 x
-// 256 / g launches: one round of either 22 / 24 / 34 (3 x 310 x 3952 from 168), two of either 40 / 43 / 42 (2 x 10910 x 528 from
-// 184), three against two 47 / 39 / 52 (3 x 966 x 6648 from 224), four against three 54 / 47 / 64 (4 x 11863 x 608 from 72), five
-// against three 121 / 101 / 108 (3 x 7853 x 1432 from 584).  Of 750 shapes of 2 .. 8 products at 2 .. 16384 tokens, g launches
-// are ahead of this by more than the noise (5 %) on two.
-static int grouped_tile(int64_t M, int64_t Nout, int g)
+// Tile of a grouped launch, among the shapes that carry groups: 256 x 256, whose workgroups walk on from tile to tile, unless
+// 256 x 128 tiles fill the rounds better by a margin, smaller for the backward's dH from a reduction of 1024 on.
+// Microseconds of the shared-X forward, 256 x 128 / 256 x 256 / g launches: one round of either 22 / 24 / 34 (3 x 310 x 3952 from 168),
+// two of either 40 / 43 / 42 (2 x 10910 x 528 from 184), three against two 47 / 39 / 52 (3 x 966 x 6648 from 224), four against three
+// 54 / 47 / 64 (4 x 11863 x 608 from 72), five against three 121 / 101 / 108 (3 x 7853 x 1432 from 584).  Of the backward, dH in
+// three against two: 121 / 117 / 143 (5 x 13715 x 168 from 800), 151 / 150 / 155 (3 x 11893 x 400 from 800), 178 /
+// 184 / 208 (5 x 14572 x 144 from 1408), 208 / 224 / 213 (3 x 10795 x 416 from 1688), attention of 16384 x 512 from 4096 1677 / 1699.
+// Of 750 forward shapes of 2 .. 8 products at 2 .. 16384 tokens, g launches are ahead of this by more than the noise (5 %) on two.
+static int grouped_tile(int b_mode, int64_t M, int64_t Nout, int64_t Kred, int g)
 {
     const int64_t large = (tile_count(TILE_256x256, M, Nout) * g + num_cu() - 1) / num_cu();
     const int64_t half = (tile_count(TILE_256x128, M, Nout) * g + num_cu() - 1) / num_cu();
-    return 4 * half < 5 * large ? TILE_256x128 : TILE_256x256;
+    return (b_mode == OP_KC && Kred >= 1024 ? 5 * half < 8 * large : 4 * half < 5 * large) ? TILE_256x128 : TILE_256x256;
 }
 
 static bool groupable_bf16(int b_mode, int64_t M, int64_t Nout, int64_t ldp, int64_t Kred, int g)
 {
     if (g < 2 || g > GEMM_MAX_GROUPS) return false;
     if (ldp == Nout && (large_split_pays(M, Nout, Kred) || split_pays(M, Nout, Kred))) return false;
-    return gemm_pp_supports(OP_KC, b_mode, OP_NONE, OUT_BF16, grouped_tile(M, Nout, g));
+    return gemm_pp_supports(OP_KC, b_mode, OP_NONE, OUT_BF16, grouped_tile(b_mode, M, Nout, Kred, g));
 }
 
 // P_i[M][Nout] (bf16, row stride ldp) = a_i * b_i^(b_mode), i < g; a_i has k contiguous
@@ -1358,7 +1360,7 @@ static hipError_t grouped_bf16(int b_mode, const GemmOperand* a, const GemmOpera
     ga.alpha = 1.f; ga.mid_scale = 1.f; ga.splits = 1; ga.k_chunk = (int)round_up(Kred, 64);
     ga.groups = g;
     for (int i = 0; i < g; i++) { ga.ga[i] = a[i].ptr; ga.gb[i] = b[i].ptr; ga.gc[i] = P[i]; }
-    return launch_gemm_bf16(OP_KC, b_mode, OP_NONE, OUT_BF16, grouped_tile(M, Nout, g), ga, run.st);
+    return launch_gemm_bf16(OP_KC, b_mode, OP_NONE, OUT_BF16, grouped_tile(b_mode, M, Nout, Kred, g), ga, run.st);
 }
 
 // C_i[M][N] (fp32, dense) = a_i^T-type products reduced over Kred (both operands reduction-major), i < g: the g
@@ -1564,7 +1566,7 @@ static int seq_ffn_gate_up_fwd(Run& run, const SharedScratch& s, const void* X, 
     FHPC_HIP(narrow_product(OP_XC, operand(X, K), operand(A_all, R), H, R, R, s.Pf, s.part, M, K, run));
     // (only where the shared-X call takes 256 x 256 tiles as well: another tile may add the reduction in another order, and the
     // two calls promise the same bits)
-    if (gate_rides(M, N, r) && (!groupable_bf16(OP_XC, M, N, N, r, 2) || grouped_tile(M, N, 2) == TILE_256x256)) {
+    if (gate_rides(M, N, r) && (!groupable_bf16(OP_XC, M, N, N, r, 2) || grouped_tile(OP_XC, M, N, r, 2) == TILE_256x256)) {
         FHPC_HIP(product_bf16(OP_XC, operand(H, R), operand(B_gate, N), G, N, N, M, r, s.part, run));
         FHPC_HIP(gemm_gated(OP_XC, operand(bf16_col(H, r), R), operand(B_up, N), U, M, N, r, 1, G, nullptr, Z, nullptr, run));
         return FHPC_OK;
