@@ -233,12 +233,16 @@ def get_workspace(nbytes: int, device):
     torch = _torch()
     if not isinstance(device, torch.device):
         device = torch.device(device)
-    if device.type != "cuda":
-        raise ValueError("a workspace is device memory, not %s" % device)
-    index = device.index if device.index is not None else torch.cuda.current_device()
-    key = (index, _raw_stream(index))
+    index = device.index
+    if index is None and device.type == "cuda":
+        index = torch.cuda.current_device()
+        device = torch.device("cuda", index)
+    # (the device itself is the key, so that only GPUs are ever found: its type, a quarter of a microsecond to ask for, is looked at on a miss)
+    key = (device, None if index is None else _raw_stream(index))
     ws = _workspaces.get(key)
     if ws is None or ws.numel() < nbytes:
+        if device.type != "cuda":
+            raise ValueError("a workspace is device memory, not %s" % device)
         # zero once: the library keeps the workspace header (arrival counters) zero from call to call
         ws = torch.zeros(max(int(nbytes), 256), dtype=torch.uint8, device=device)
         _workspaces[key] = ws

@@ -178,7 +178,9 @@ def test_workspaces_are_device_memory(monkeypatch):
     monkeypatch.setattr(torch.cuda, "current_device", lambda: 0)
     monkeypatch.setattr(fhpc, "_raw_stream", lambda index: 0)
     monkeypatch.setattr(fhpc, "_workspaces", {})
-    for device in ("cpu", torch.device("cpu"), "meta"):
+    fhpc._workspaces[torch.device("cuda", 0), 0] = torch.empty(512, dtype=torch.uint8, device="meta")       # (stands for one that is there)
+    for device in ("cpu", "cpu:0", torch.device("cpu"), "meta"):
         with pytest.raises(ValueError):
             fhpc.get_workspace(256, device)
-    assert not fhpc._workspaces
+    assert len(fhpc._workspaces) == 1
+    assert fhpc.get_workspace(256, "cuda") is fhpc.get_workspace(256, "cuda:0")
