@@ -681,7 +681,7 @@ def quantised_stream(fhpc):
                                  "gbs": io / (mean * 1e-3) / 1e9, "frac_hbm_peak": io / (mean * 1e-3) / 1e9 / PEAK_HBM_GBS})
                 if cfg == "c5" and fwd_only:
                     # the same forward as a decoder layer issues it: q, k and v read one X and so do gate and up, each
-                    # group in one call of qlinear_lowrank_fwd_shared_x (four launches per step instead of seven)
+                    # group in one call of qlinear_lowrank_fwd_shared_x (four calls per step instead of seven)
                     shared = []
                     for cs in sets:
                         q, k, v, o, gate, up, down = cs

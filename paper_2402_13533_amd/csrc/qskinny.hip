@@ -153,11 +153,17 @@ __device__ __forceinline__ void hpart_body(unsigned char* smem, int kc, const ui
     }
 }
 
+// Until this wave's own shared_stores have been acknowledged by the level all compute units share.  (A release fence of
+// workgroup scope does not do that: the waves of a workgroup share a cache, so for them the compiler need not wait, and
+// neither does the barrier.)
+__device__ __forceinline__ void wait_for_stores() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+
 // Arrival at a counter in the workspace header.  Every thread waits until its own shared_stores have been
 // acknowledged, the workgroup meets, and one thread draws the ticket (the number of earlier arrivals).  The
 // workgroup that draws the last ticket may shared_load what all earlier arrivals stored.
 __device__ __forceinline__ uint32_t arrive(uint32_t* counter, uint32_t* s_ticket)
 {
+    wait_for_stores();
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
     __syncthreads();
     if (threadIdx.x == 0) *s_ticket = __hip_atomic_fetch_add(counter, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -374,13 +380,16 @@ __global__ __launch_bounds__(NT) void qskinny_fwd_kernel(SkinnyJobs jb, float* _
                 H_out[i] = __builtin_bit_cast(uint16_t, hb);
             }
         }
+        wait_for_stores();
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
         __syncthreads();
         if (threadIdx.x == 0) __hip_atomic_store(tickets + HCOUNT + hj, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         QTS(3);
-        // H is in memory: the flag the blocks' finishers look at
+        // H is in memory: the flag the blocks' finishers look at.  (It is up before this event is counted: the launch's last
+        // event takes it down.)
         if (threadIdx.x == 0) {
             __hip_atomic_store(tickets + HREADY + hj, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            wait_for_stores();
             done();
         }
         QTS(4);

@@ -684,6 +684,38 @@ def test_few_token_forward_when_the_finisher_forms_H_itself(scheme, M, r):
     assert torch.equal(Y2, Y0)
 
 
+@pytest.mark.parametrize("scheme,M,K,r,N,count", [
+    (4, 1, 13824, 16, 5120, 1),      # one token, a reduction beyond the kernel with whole rows
+    (8, 16, 4096, 8, 4096, 1),
+    (4, 15, 5120, 64, 5168, 2),      # two weights on one X, the largest rank
+    (8, 40, 512, 16, 5632, 1),       # two and four token tiles per pass
+    (4, 64, 1024, 8, 520, 1),        # blocks of 16 tokens
+])
+def test_few_token_forward_reads_what_this_call_wrote(scheme, M, K, r, N, count):
+    """Slices, chunk sums of H and H itself pass from workgroup to workgroup through the workspace within the launch: with a
+    workspace full of NaN patterns before every call (but for the header, which the calls keep zero) nothing of them may
+    be read before it is written.  Every repetition gives the bits of the first, and those are the oracle's layer."""
+    import torch
+    fhpc = _fhpc()
+    W, X, A, B, _ = qlinear_inputs(8, M, K, r, N, 140)
+    Wq, sc = _quantize_host(W, scheme)
+    Wq_d, sc_d = _to_dev(Wq, sc)
+    Xd, w = X.cuda(), (Wq_d, sc_d, A.cuda(), B.cuda(), 2.0)
+    ws = torch.zeros(64 << 20, dtype=torch.uint8, device="cuda")
+    first, wrong = None, 0
+    for rep in range(100):
+        ws[16384:] = 255
+        out = [t for pair in fhpc.qlinear_lowrank_fwd_shared_x(Xd, [w] * count, scheme, save_H=True, workspace=ws) for t in pair]
+        out += fhpc.qlinear_lowrank_fwd(Xd, w[0], w[1], scheme, *w[2:], save_H=True, workspace=ws)
+        first = first or out
+        wrong += sum(not torch.equal(a, b) for a, b in zip(out, first))
+    Yr, Hr = oracle.qlinear_lowrank_fwd(X.f64, oracle.dequant(Wq, sc, scheme, 64), A.f64, B.f64, 2.0)
+    for Y, H in zip(first[::2], first[1::2]):
+        assert parity_err(from_device(Y), Yr) <= TOL_BF16 and parity_err(from_device(H), Hr) <= TOL_BF16
+    assert wrong == 0
+    assert int(ws[:16384].count_nonzero()) == 0
+
+
 @pytest.mark.parametrize("scheme,M,r", [(4, 12, 16), (8, 40, 24)])
 def test_few_token_step_in_a_hip_graph(scheme, M, r):
     """Forward and backward of the few-token routes captured in one HIP graph (streaming kernels, their
