@@ -2,6 +2,7 @@
 // launches that makes up each pass of the layer.  See include/fingpt_hpc.h for the
 // contract of every function.
 #include "../../include/fingpt_hpc.h"
+#include "few_lowrank.h"
 #include "gemm_bf16.h"
 #include "gemm_f32.h"
 #include "kernels_misc.h"
@@ -430,6 +431,9 @@ int64_t joint_part_bytes(int64_t M, int64_t K, int64_t r, int64_t N, int g)
     return p.pays && p.splits > 1 ? (int64_t)p.splits * (K * r * g + (int64_t)g * r * N) * 4 : 0;
 }
 
+// The bf16 layer with at most 64 tokens: a launch per rank product, and one for all that follows it (few_lowrank.hip).
+bool few_pays(int64_t M, int64_t r) { return M <= FEW_MMAX && r % 8 == 0 && r <= FEW_RMAX; }
+
 Scratch carve(Carver& c, int op, int64_t M, int64_t K, int64_t r, int64_t N, int dtype, bool quantised = true,
               bool premerged = false)
 {
@@ -494,6 +498,10 @@ Scratch carve(Carver& c, int op, int64_t M, int64_t K, int64_t r, int64_t N, int
     if (op == FHPC_OP_QLINEAR_FWD) upto(fused_part_bytes(M, N, K));        // Y  = X deq(W) + s H B
     if (op == FHPC_OP_QLINEAR_BWD) upto(fused_part_bytes(M, K, N));        // dX = dY deq(W)^T + s dH A^T
     if (op == FHPC_OP_LOWRANK_FWD) upto(product_part_bytes(M, N, rp));     // Y  = H B
+    if ((op == FHPC_OP_LOWRANK_FWD || op == FHPC_OP_LOWRANK_BWD) && few_pays(M, r)) {
+        upto(plan_few(M, K, r, num_cu()).part_bytes);
+        if (bwd) upto(plan_few(M, N, r, num_cu()).part_bytes);
+    }
     if (op == FHPC_OP_LOWRANK_BWD) upto(product_part_bytes(M, K, rp));     // dX = dH A^T
     if (bwd) {
         upto(split_bytes(K, rp, rp, M) + split_bytes(rp, N, N, M));   // dA = X^T dH and dB = H^T dY, slabs side by side
@@ -737,6 +745,14 @@ hipError_t fused_product(int b_mode, int b2_mode, GemmArgs g, void* C, int64_t M
     hipError_t e = launch_gemm_bf16(OP_KC, b_mode, b2_mode, OUT_F32, sp.tile, g, st);
     if (e != hipSuccess) return e;
     return launch_sum_slabs(part, M * Nout, sp.splits, C, true, st);
+}
+
+// T[M][r] = left right, few tokens (few_pays)
+hipError_t few_rank_product(const void* left, const void* right, bool right_kc, void* T, int64_t M, int64_t Kred, int64_t r, const Scratch& s, Run& run)
+{
+    const FewPlan p = plan_few(M, Kred, r, num_cu());
+    if (!run.claim(p.part_bytes)) return hipErrorOutOfMemory;
+    return run.dry ? hipSuccess : launch_few_in(left, right, right_kc, T, M, Kred, r, p, s.part, s.header, run.st);
 }
 
 struct Factors {
@@ -1131,6 +1147,12 @@ int seq_lowrank_fwd(Run& run, const Scratch& s, const void* X, const void* A, co
 {
     if (dtype == FHPC_F32)
         return lowrank_fwd_f32((const float*)X, (const float*)A, (const float*)B, (float*)Y, (float*)H_out, M, K, r, N, s, run);
+    if (few_pays(M, r)) {
+        void* const H = H_out ? H_out : s.H;
+        FHPC_HIP(few_rank_product(X, A, false, H, M, K, r, s, run));
+        FHPC_LAUNCH(run, launch_few_out(H, B, false, Y, M, r, N, nullptr, num_cu(), run.st));
+        return FHPC_OK;
+    }
     const int64_t rp = rank_pad(r);
     Factors f;
     int rc = prepare_factors(A, B, K, r, rp, N, s, run, &f);
@@ -1142,6 +1164,21 @@ int seq_lowrank_fwd(Run& run, const Scratch& s, const void* X, const void* A, co
     return FHPC_OK;
 }
 
+// The backward pass of a layer with few tokens (few_pays): dH, then dX and the weight gradients in one launch
+int few_backward(const void* X, const void* A, const void* B, const void* dY, const void* H_saved, void* dX, float* dA, float* dB,
+                 int64_t M, int64_t K, int64_t r, int64_t N, const Scratch& s, Run& run)
+{
+    const void* H = H_saved;
+    if (dB && !H) {
+        FHPC_HIP(few_rank_product(X, A, false, s.H, M, K, r, s, run));
+        H = s.H;
+    }
+    if (dX || dA) FHPC_HIP(few_rank_product(dY, B, true, s.dH, M, N, r, s, run));
+    const FewGrads grads = {X, s.dH, H, dY, dA, dB, K, N};
+    FHPC_LAUNCH(run, launch_few_out(s.dH, A, true, dX, M, r, K, &grads, num_cu(), run.st));
+    return FHPC_OK;
+}
+
 int seq_lowrank_bwd(Run& run, const Scratch& s, const void* X, const void* A, const void* B, const void* dY,
                     const void* H_saved, void* dX, float* dA, float* dB,
                     int64_t M, int64_t K, int64_t r, int64_t N, int dtype)
@@ -1149,6 +1186,7 @@ int seq_lowrank_bwd(Run& run, const Scratch& s, const void* X, const void* A, co
     if (dtype == FHPC_F32)
         return lowrank_bwd_f32((const float*)X, (const float*)A, (const float*)B, (const float*)dY,
                                (const float*)H_saved, (float*)dX, dA, dB, M, K, r, N, s, run);
+    if (few_pays(M, r)) return few_backward(X, A, B, dY, H_saved, dX, dA, dB, M, K, r, N, s, run);
     const int64_t rp = rank_pad(r);
     Factors f;
     int rc = prepare_factors(A, B, K, r, rp, N, s, run, &f);
@@ -1586,6 +1624,12 @@ static int seq_ffn_down_bwd(Run& run, const Scratch& s, const void* Z, const voi
                             const void* H_saved, const void* G, const void* U, void* dG, void* dU, float* dA, float* dB,
                             int64_t M, int64_t K, int64_t r, int64_t N)
 {
+    if (few_pays(M, r)) {
+        const int rc = few_backward(Z, A, B, dY, H_saved, dU, dA, dB, M, K, r, N, s, run);
+        if (rc) return rc;
+        FHPC_LAUNCH(run, launch_swiglu_bwd(G, U, dU, dG, dU, M * K, true, run.st));
+        return FHPC_OK;
+    }
     const int64_t rp = rank_pad(r);
     Factors f;
     int rc = prepare_factors(A, B, K, r, rp, N, s, run, &f);

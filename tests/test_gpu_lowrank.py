@@ -501,3 +501,66 @@ def test_shared_x_calls_write_their_scratch_before_they_read_it(M, K, r, N, g):
         gate_up = fhpc.lowrank_ffn_gate_up_fwd(X, A[:, :2 * r].contiguous(), Bs[0], Bs[1], save_H=True, workspace=ws)
         got.append([*Ys, H, dX, dA, *dBs, *gate_up])
     assert all(torch.equal(a, b) for a, b in zip(*got))
+
+
+@pytest.mark.parametrize("M,K,r,N", [
+    (1, 8, 8, 8),            # the smallest: one step of the reduction, most of it outside
+    (16, 1536, 40, 1544),    # whole 16-row block; a reduction at the limit of the uncut ones, and one beyond it
+    (17, 2056, 96, 520),     # one row beyond; slices that end inside a step
+    (33, 1032, 1024, 264),   # the largest rank of these launches; more rows than one block
+    (64, 4104, 72, 8456),    # all 64 tokens; wide outputs in 64-column tiles
+])
+def test_few_token_launches(M, K, r, N):
+    """At most 64 tokens: rank products whole and in slices, outputs on both column tiles and the weight gradients beside
+    them, against the oracle; each output has the same bits whatever else is asked for, and the header is left zero."""
+    import torch
+    fhpc = _fhpc()
+    X = Bf16.normal(31, (M, K)); A = Bf16.normal(32, (K, r), K ** -0.5)
+    B = Bf16.normal(33, (r, N), r ** -0.5); dY = Bf16.normal(34, (M, N))
+    Yr, Hr = oracle.lowrank_fwd(X.f64, A.f64, B.f64)
+    ref = (Yr,) + oracle.lowrank_bwd(X.f64, A.f64, B.f64, dY.f64)
+    Xd, Ad, Bd, dYd = X.cuda(), A.cuda(), B.cuda(), dY.cuda()
+    ws = torch.full((fhpc.workspace_bytes(fhpc.FHPC_OP_LOWRANK_BWD, M, K, r, N) + 4096,), 0xFF, dtype=torch.uint8, device="cuda")
+    ws[:16384] = 0                                                   # (the header; everything behind it is written before it is read)
+    guard = Guarded()
+    g = [guard.alloc(s, t) for s, t in (((M, N), torch.bfloat16), ((M, r), torch.bfloat16), ((M, K), torch.bfloat16),
+                                        ((K, r), torch.float32), ((r, N), torch.float32))]
+    Y, H = fhpc.lowrank_linear_fwd(Xd, Ad, Bd, Y=g[0], H_out=g[1], workspace=ws)
+    assert parity_err(from_device(H), Hr, TOL_BF16, "H") <= TOL_BF16
+    out = fhpc.lowrank_linear_bwd(Xd, Ad, Bd, dYd, H_saved=H, dX=g[2], dA=g[3], dB=g[4], workspace=ws)
+    _check_all("few %s" % ((M, K, r, N),), (Y,) + out, ref, TOL_BF16)
+    guard.check("few %s" % ((M, K, r, N),))
+    assert torch.equal(fhpc.lowrank_linear_fwd(Xd, Ad, Bd, workspace=ws), Y)
+    assert all(torch.equal(a, b) for a, b in zip(fhpc.lowrank_linear_bwd(Xd, Ad, Bd, dYd, workspace=ws), out))     # H recomputed
+    for i in range(3):
+        only = fhpc.lowrank_linear_bwd(Xd, Ad, Bd, dYd, H_saved=H, need_dX=i == 0, need_dA=i == 1, need_dB=i == 2, workspace=ws)
+        assert torch.equal(only[i], out[i])
+    assert int(ws[:16384].sum()) == 0
+
+
+def test_few_token_launches_replayed_from_a_graph():
+    import torch
+    fhpc = _fhpc()
+    M, K, r, N = 5, 4096, 64, 2048
+    A = Bf16.normal(41, (K, r), K ** -0.5).cuda(); B = Bf16.normal(42, (r, N), r ** -0.5).cuda()
+    X = [Bf16.normal(43 + i, (M, K)).cuda() for i in range(4)]
+    dY = [Bf16.normal(53 + i, (M, N)).cuda() for i in range(4)]
+    def step(x, dy):
+        Y, H = fhpc.lowrank_linear_fwd(x, A, B, save_H=True)
+        return (Y, *fhpc.lowrank_linear_bwd(x, A, B, dy, H_saved=H))
+    eager = [step(x, dy) for x, dy in zip(X, dY)]
+    xs, dys = X[0].clone(), dY[0].clone()
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        step(xs, dys)
+    torch.cuda.current_stream().wait_stream(side)
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        out = step(xs, dys)
+    for i in range(4):
+        xs.copy_(X[i]); dys.copy_(dY[i])
+        graph.replay()
+        torch.cuda.synchronize()
+        assert all(torch.equal(a, b) for a, b in zip(out, eager[i])), i
+        step(X[3], dY[3])                                            # other work on the eager workspace between the replays
