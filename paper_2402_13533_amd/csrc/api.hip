@@ -365,24 +365,23 @@ void plan_f32_grads(int64_t M, int64_t K, int64_t r, int64_t N, GemmF32Plan* eac
     const int64_t ms[2] = {K, r}, ns[2] = {r, N}, ks[2] = {M, M};
     plan_gemm_f32(2, ms, ns, ks, num_cu(), each);
 }
-int64_t plan_f32_bytes(const GemmF32Plan& p, int64_t M, int64_t N) { return p.splits > 1 ? p.splits * gemm_f32_slab(M, N) * 4 : 0; }
 
 int64_t f32_part_bytes(bool bwd, int64_t M, int64_t K, int64_t r, int64_t N)
 {
     int64_t part = 0;
     auto upto = [&part](int64_t b) { if (b > part) part = b; };
     if (!lowrank_chain_f32_pays(M, K, r)) {
-        upto(plan_f32_bytes(plan_f32(M, r, K), M, r));                                          // H = X A
-        if (!bwd) upto(plan_f32_bytes(plan_f32(M, N, r), M, N));                                // Y = H B
+        upto(gemm_f32_part_bytes(plan_f32(M, r, K), M, r));                                          // H = X A
+        if (!bwd) upto(gemm_f32_part_bytes(plan_f32(M, N, r), M, N));                                // Y = H B
     }
     if (!bwd) return part;
     if (!lowrank_chain_f32_pays(M, N, r)) {
-        upto(plan_f32_bytes(plan_f32(M, r, N), M, r));                                          // dH = dY B^T
-        upto(plan_f32_bytes(plan_f32(M, K, r), M, K));                                          // dX = dH A^T
+        upto(gemm_f32_part_bytes(plan_f32(M, r, N), M, r));                                          // dH = dY B^T
+        upto(gemm_f32_part_bytes(plan_f32(M, K, r), M, K));                                          // dX = dH A^T
     }
     GemmF32Plan both[2];
     plan_f32_grads(M, K, r, N, both);                                                           // dA and dB
-    upto(plan_f32_bytes(both[0], K, r) + plan_f32_bytes(both[1], r, N));
+    upto(gemm_f32_part_bytes(both[0], K, r) + gemm_f32_part_bytes(both[1], r, N));
     return part;
 }
 
@@ -911,40 +910,23 @@ int check_workspace(int op, void* ws, size_t ws_bytes, int64_t M, int64_t K, int
 }
 
 // ---------------- fp32 path of the factorised layer ----------------
-GemmF32Job job_f32(const float* a, int64_t lda, const float* b, int64_t ldb, int64_t M, int64_t N, int64_t Kred, const GemmF32Plan& p)
+GemmF32Job job_f32(const float* a, int64_t lda, const float* b, int64_t ldb, float* c, int64_t M, int64_t N, int64_t Kred, const GemmF32Plan& p)
 {
     GemmF32Job j = {};
-    j.a = a; j.lda = lda; j.b = b; j.ldb = ldb;
+    j.a = a; j.lda = lda; j.b = b; j.ldb = ldb; j.c = c;
     j.M = (int)M; j.N = (int)N; j.K = (int)Kred;
-    j.ldc = N; j.slab = gemm_f32_slab(M, N);
+    j.ldc = N;
     j.splits = p.splits; j.k_chunk = p.k_chunk;
     return j;
 }
 
-// Dense outputs C[i][M][N] of `count` products (same layouts, same tile): one launch, and one more for the slab sums
-// of those whose reduction is cut into slices.
-hipError_t products_f32(F32Layout al, F32Layout bl, GemmF32Job* jobs, float* const* C, int count, int tile, float* part, Run& run)
+// `count` products (same layouts, same tile) in one launch
+hipError_t products_f32(F32Layout al, F32Layout bl, const GemmF32Job* jobs, const GemmF32Plan* plans, int count, const Scratch& s, Run& run)
 {
     int64_t need = 0;
-    for (int i = 0; i < count; i++) need += jobs[i].splits > 1 ? jobs[i].splits * jobs[i].slab * 4 : 0;
+    for (int i = 0; i < count; i++) need += gemm_f32_part_bytes(plans[i], jobs[i].M, jobs[i].N);
     if (!run.claim(need)) return hipErrorOutOfMemory;
-    if (run.dry) return hipSuccess;
-    SumF32Job sums[2] = {};
-    int n = 0;
-    for (int i = 0; i < count; i++) {
-        if (jobs[i].splits == 1) {
-            jobs[i].c = C[i];
-            continue;
-        }
-        jobs[i].c = part;
-        sums[n].slabs = part; sums[n].out = C[i];
-        sums[n].n = (int64_t)jobs[i].M * jobs[i].N; sums[n].slab = jobs[i].slab; sums[n].nslab = jobs[i].splits;
-        part += jobs[i].splits * jobs[i].slab;
-        n++;
-    }
-    hipError_t e = launch_gemm_f32(al, bl, jobs, count, tile, run.st);
-    if (e != hipSuccess || n == 0) return e;
-    return launch_sum_f32(sums, n, run.st);
+    return run.dry ? hipSuccess : launch_gemm_f32(al, bl, jobs, count, plans[0].tile, s.part, s.header, run.st);
 }
 
 // C[M][N] = a * b, one product
@@ -952,8 +934,8 @@ hipError_t product_f32(F32Layout al, F32Layout bl, const float* a, int64_t lda, 
                        int64_t M, int64_t N, int64_t Kred, const Scratch& s, Run& run)
 {
     const GemmF32Plan p = plan_f32(M, N, Kred);
-    GemmF32Job j = job_f32(a, lda, b, ldb, M, N, Kred, p);
-    return products_f32(al, bl, &j, &C, 1, p.tile, s.part, run);
+    const GemmF32Job j = job_f32(a, lda, b, ldb, C, M, N, Kred, p);
+    return products_f32(al, bl, &j, &p, 1, s, run);
 }
 
 int lowrank_fwd_f32(const float* X, const float* A, const float* B, float* Y, float* H_out,
@@ -999,14 +981,13 @@ int lowrank_bwd_f32(const float* X, const float* A, const float* B, const float*
     // dA[k][j] = sum_m X[m][k] dH[m][j],  dB[j][n] = sum_m H[m][j] dY[m][n]; planned together also when only one of them
     // is wanted, so that each has the same bits either way
     if (dA || dB) {
-        GemmF32Plan p[2];
+        GemmF32Plan p[2], used[2];
         plan_f32_grads(M, K, r, N, p);
         GemmF32Job jobs[2] = {};
-        float* C[2];
         int n = 0;
-        if (dA) { jobs[n] = job_f32(X, K, dH, r, K, r, M, p[0]); C[n++] = dA; }
-        if (dB) { jobs[n] = job_f32(H, r, dY, N, r, N, M, p[1]); C[n++] = dB; }
-        FHPC_HIP(products_f32(F32_XC, F32_XC, jobs, C, n, p[0].tile, s.part, run));
+        if (dA) { used[n] = p[0]; jobs[n++] = job_f32(X, K, dH, r, dA, K, r, M, p[0]); }
+        if (dB) { used[n] = p[1]; jobs[n++] = job_f32(H, r, dY, N, dB, r, N, M, p[1]); }
+        FHPC_HIP(products_f32(F32_XC, F32_XC, jobs, used, n, s, run));
     }
     return FHPC_OK;
 }

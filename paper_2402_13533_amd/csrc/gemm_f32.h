@@ -10,26 +10,31 @@ enum F32Layout { F32_KC = 0, F32_XC = 1 };
 
 struct GemmF32Plan {
     int tile;        // 64 or 32: the edge of the square output tile
-    int splits;      // slices of the reduction; more than one: each stores a slab, launch_sum_f32 adds them
+    int splits;      // slices of the reduction; more than one: each stores a slab per tile, the last to arrive adds them
     int k_chunk;     // reduction length of a slice, a multiple of 32
 };
+constexpr int64_t F32_TICKETS = 4096;                        // tiles of a launch whose reductions may be cut: words of the workspace header
+constexpr int64_t F32_LD_MAX = (int64_t)1 << 20;
 
-// C[M][N] (row stride ldc, or slab s of `slab` floats when the plan has slices) = sum_k a(m, k) b(n, k)
+// C[M][N] (row stride ldc) = sum_k a(m, k) b(n, k)
 struct GemmF32Job {
     const float* a;
     const float* b;
     float* c;
-    int64_t lda, ldb, ldc, slab;
+    int64_t lda, ldb, ldc;
     int M, N, K;
     int splits, k_chunk;
-    int a_vec, b_vec;      // 16-byte loads along the contiguous index
-    int tiles_n, items;    // (set by launch_gemm_f32)
+    // (set by launch_gemm_f32)
+    int tiles_n, items;
+    float* part;
+    uint32_t* tickets;
 };
 
 // Up to two products of the same operand layouts share a launch; `jobs` products of these sizes are planned together.
+// part: scratch of gemm_f32_part_bytes of every job; tickets: F32_TICKETS zero words, left zero.
 GemmF32Plan plan_gemm_f32(int jobs, const int64_t* M, const int64_t* N, const int64_t* K, int units, GemmF32Plan* each);
-int64_t gemm_f32_slab(int64_t M, int64_t N);      // floats of one slab of an M x N output
-hipError_t launch_gemm_f32(F32Layout al, F32Layout bl, const GemmF32Job* jobs, int count, int tile, hipStream_t s);
+int64_t gemm_f32_part_bytes(const GemmF32Plan& p, int64_t M, int64_t N);
+hipError_t launch_gemm_f32(F32Layout al, F32Layout bl, const GemmF32Job* jobs, int count, int tile, float* part, uint32_t* tickets, hipStream_t s);
 
 // out[i] = sum of the slabs' elements i, i < n.  With cols > 0 the output is bf16 [n / cols][cols] with row stride ldo
 // (cols a multiple of 4, rows 8-byte aligned).

@@ -6,6 +6,7 @@ namespace fhpc {
 
 typedef __attribute__((ext_vector_type(4))) float f32x4;
 typedef __attribute__((ext_vector_type(16))) float f32x16;
+typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
 typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4;
 
 // ---------------------------------------------------------------------------------
@@ -15,10 +16,12 @@ typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4;
 // quarter of every step each, their sums meet in LDS).  Bound by the matrix pipes, which reach 132 .. 142 TFLOP/s
 // from registers alone on this chip: the instruction takes 64 clocks, so L2 -> registers -> LDS keeps up, and what
 // counts is how evenly tiles x slices of the reduction fall on the compute units (plan_gemm_f32) with enough
-// workgroups per unit to hide a step's latency.  (A 128 x 128 tile, 64 x 64 per wave, never came first: two
-// workgroups per unit instead of four; 192 x 3072 over 8192: 136 against 108 microseconds.)
-// 8192 x 192 x 768: 334 microseconds on the vector ALU -> 35; 8192 x 3072 x 192: 149 -> 104 (93 TFLOP/s);
-// 768 x 192 x 8192: 895 -> 41, mostly from cutting the reduction into slices.
+// workgroups per unit to hide a step's latency.  (128 x 64, 64 x 128 and 128 x 128 tiles: 95 .. 115 microseconds for 8192 x 192 x 3072
+// against 92 .. 97; 94 .. 100 for 8192 x 3072 x 192 against 99.)
+// 8192 x 192 x 768, 8192 x 3072 x 192, 8192 x 192 x 3072, and 768 x 192 with 192 x 3072 over 8192, microseconds, with a wait for every request at
+// each step -> with the requests counted: 35 -> 30, 123 -> 107, 108 -> 97, 152 -> 126 (80 .. 100 TFLOP/s).
+// A cut reduction's slabs are added by the last slice to arrive at a tile: launches of their own (two to five a layer) took 3 to 6
+// microseconds each on the GPU and 4 on the host.
 // 32-deep steps; a lane takes four consecutive k at a time (lanes 0 .. 31 the first four of eight, lanes 32 .. 63 the
 // other four), so an operand with k contiguous is one 16-byte LDS read per four instructions.
 // PD steps are in flight in registers ahead of the LDS tile (two LDS buffers, one barrier per step).
@@ -37,30 +40,55 @@ template <F32Layout L, int T> struct F32Tile {
     static constexpr int PIECES = T * F32_BK / 4 / 256;      // 16-byte pieces per thread and step
 };
 
-template <F32Layout L, int T>
-__device__ __forceinline__ void f32_fetch(f32x4* reg, const float* __restrict__ p, int64_t ld, int x0, int X, int k0, int k_end, bool vec)
-{
-    const int tid = threadIdx.x;
+// The pieces of one operand's steps.  Everything a request needs but the end of the reduction is formed once: the lane's byte offsets from the
+// first row and first k of a step (beyond the matrix: F32_NONE, which the descriptor turns into zeros), so that no branch stands between
+// the requests and the compiler can count them: with one it waits for all of them at every step, whatever PD is.
+constexpr uint32_t F32_NONE = 0x80000000u;
+constexpr int F32_SC1 = 16;            // cache policy of accesses that other compute units' accesses must meet
+template <F32Layout L, int T, bool VEC>
+struct F32Feed {
+    static constexpr int PIECES = F32Tile<L, T>::PIECES;
+    const float* base;      // wave-uniform: the tile's first row at the first k of the next step
+    int64_t step;           // floats from one step to the next
+    int left;               // of the reduction from there on
+    uint32_t off[PIECES][VEC ? 1 : 4];
+    int k[PIECES];          // the piece's first k within a step
+
+    __device__ __forceinline__ void init(const float* p, int64_t ld, int x0, int X, int k0, int k_end)
+    {
+        const int tid = threadIdx.x;
+        base = p + ((L == F32_KC) ? (int64_t)x0 * ld + k0 : (int64_t)k0 * ld + x0);
+        step = (L == F32_KC) ? F32_BK : F32_BK * ld;
+        left = k_end - k0;
 #pragma unroll
-    for (int i = 0; i < F32Tile<L, T>::PIECES; i++) {
-        const int e = tid + 256 * i;
-        const int x = x0 + (L == F32_KC ? e / (F32_BK / 4) : (e % (T / 4)) * 4);
-        const int k = k0 + (L == F32_KC ? (e % (F32_BK / 4)) * 4 : e / (T / 4));
-        const int64_t at = (L == F32_KC) ? (int64_t)x * ld + k : (int64_t)k * ld + x;
-        f32x4 v = {0.f, 0.f, 0.f, 0.f};
-        if (vec) {
-            // (the contiguous extent is a multiple of four: a piece is inside or outside as a whole)
-            if (x < X && k < k_end) v = *reinterpret_cast<const f32x4*>(p + at);
-        } else {
+        for (int i = 0; i < PIECES; i++) {
+            const int e = tid + 256 * i;
+            const int x = (L == F32_KC) ? e / (F32_BK / 4) : (e % (T / 4)) * 4;
+            k[i] = (L == F32_KC) ? (e % (F32_BK / 4)) * 4 : e / (T / 4);
+            const uint32_t at = 4u * ((L == F32_KC) ? (uint32_t)x * (uint32_t)ld + k[i] : (uint32_t)k[i] * (uint32_t)ld + x);      // (ld < 2^20)
 #pragma unroll
-            for (int q = 0; q < 4; q++) {
-                const bool in = (L == F32_KC) ? (x < X && k + q < k_end) : (x + q < X && k < k_end);
-                if (in) v[q] = p[at + q];
+            for (int q = 0; q < (VEC ? 1 : 4); q++)
+                off[i][q] = (x0 + x + (L == F32_KC ? 0 : q) < X) ? at + 4u * q : F32_NONE;
+        }
+    }
+    __device__ __forceinline__ void fetch(f32x4* reg)
+    {
+        const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(base), 0, 0x7FFFFFFF, 0x00020000);
+#pragma unroll
+        for (int i = 0; i < PIECES; i++) {
+            if constexpr (VEC) {
+                // (the contiguous extent is a multiple of four: a piece is inside or outside as a whole)
+                reg[i] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rs, k[i] < left ? off[i][0] : F32_NONE, 0, 0));
+            } else {
+#pragma unroll
+                for (int q = 0; q < 4; q++)
+                    reg[i][q] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs, k[i] + (L == F32_KC ? q : 0) < left ? off[i][q] : F32_NONE, 0, 0));
             }
         }
-        reg[i] = v;
+        base += step;
+        left -= F32_BK;
     }
-}
+};
 
 template <F32Layout L, int T>
 __device__ __forceinline__ void f32_put(float* tile, const f32x4* reg)
@@ -90,111 +118,173 @@ __device__ __forceinline__ f32x4 f32_frag(const float* tile, int x, int c, int h
     }
 }
 
-template <F32Layout AL, F32Layout BL, int T, int PD>
+template <F32Layout AL, F32Layout BL, int T, int PD, bool VEC>
 __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmF32Args args)
 {
     constexpr int AW = F32Tile<AL, T>::WORDS, BW = F32Tile<BL, T>::WORDS;
     __shared__ __attribute__((aligned(16))) float lds[2 * (AW + BW)];
-    const int which = ((int)blockIdx.x < args.job[0].items) ? 0 : 1;
+    const int id = ring::xcd_contiguous((int)blockIdx.x, (int)gridDim.x);
+    const int which = (id < args.job[0].items) ? 0 : 1;
     const GemmF32Job& j = args.job[which];
-    const int item = (int)blockIdx.x - (which ? args.job[0].items : 0);
+    const int item = id - (which ? args.job[0].items : 0);
     const int per_split = j.items / j.splits;
     const int split = item / per_split, t = item - split * per_split;
     const int m0 = t / j.tiles_n * T, n0 = t % j.tiles_n * T;
     const int k_begin = split * j.k_chunk;
     const int k_end = (k_begin + j.k_chunk < j.K) ? k_begin + j.k_chunk : j.K;
-    const bool av = j.a_vec != 0, bv = j.b_vec != 0;
     const int lane = threadIdx.x & 63, half = lane >> 5, i32 = lane & 31;
     const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
-    const int wm = (T == 32) ? 0 : (wave >> 1) * 32, wn = (T == 32) ? 0 : (wave & 1) * 32;
+    constexpr bool SHARED = (T == 32);      // the four waves share the tile
+    const int wm = SHARED ? 0 : (wave >> 1) * 32, wn = SHARED ? 0 : (wave & 1) * 32;
 
     f32x4 ra[PD][F32Tile<AL, T>::PIECES], rb[PD][F32Tile<BL, T>::PIECES];
-    f32x16 acc;
+    // acc: the running trip's sums; sum: those of the trips before it.  (One chain of additions over the whole slice is both less
+    // exact, 1.1e-6 against 4e-7 over 3072, and no faster.)
+    f32x16 acc, sum;
 #pragma unroll
-    for (int v = 0; v < 16; v++) acc[v] = 0.f;
+    for (int v = 0; v < 16; v++) acc[v] = sum[v] = 0.f;
+    const auto end_trip = [&]() __attribute__((always_inline)) {
+#pragma unroll
+        for (int v = 0; v < 16; v++) {
+            sum[v] += acc[v];
+            acc[v] = 0.f;
+        }
+    };
 
     const int steps = (k_end - k_begin + F32_BK - 1) / F32_BK;
+    F32Feed<AL, T, VEC> feed_a;
+    F32Feed<BL, T, VEC> feed_b;
+    feed_a.init(j.a, j.lda, m0, j.M, k_begin, k_end);
+    feed_b.init(j.b, j.ldb, n0, j.N, k_begin, k_end);
 #pragma unroll
     for (int p = 0; p < PD; p++) {
         // (beyond the last step the pieces are all out of range: zeros, no access)
-        f32_fetch<AL, T>(ra[p], j.a, j.lda, m0, j.M, k_begin + p * F32_BK, k_end, av);
-        f32_fetch<BL, T>(rb[p], j.b, j.ldb, n0, j.N, k_begin + p * F32_BK, k_end, bv);
+        feed_a.fetch(ra[p]);
+        feed_b.fetch(rb[p]);
     }
-    for (int s0 = 0; s0 < steps; s0 += PD) {
-#pragma unroll
-        for (int p = 0; p < PD; p++) {
-            const int s = s0 + p;
-            if (s < steps) {
-                float* const sa = lds + (s & 1) * (AW + BW);
-                float* const sb = sa + AW;
-                f32_put<AL, T>(sa, ra[p]);
-                f32_put<BL, T>(sb, rb[p]);
-                __syncthreads();
-                f32_fetch<AL, T>(ra[p], j.a, j.lda, m0, j.M, k_begin + (s + PD) * F32_BK, k_end, av);
-                f32_fetch<BL, T>(rb[p], j.b, j.ldb, n0, j.N, k_begin + (s + PD) * F32_BK, k_end, bv);
-#pragma unroll
-                for (int cc = 0; cc < (T == 32 ? 1 : F32_BK / 8); cc++) {
-                    const int c = (T == 32) ? wave : cc;
-                    const f32x4 fa = f32_frag<AL, T>(sa, wm + i32, c, half);
-                    const f32x4 fb = f32_frag<BL, T>(sb, wn + i32, c, half);
-#pragma unroll
-                    for (int q = 0; q < 4; q++) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[q], fb[q], acc, 0, 0, 0);
-                }
-            }
-        }
-    }
-    float* const C = j.c + (int64_t)split * j.slab;
-    // a lane holds column lane % 32 and, of each group of eight rows, four: rows 8 (v / 4) + 4 (lane / 32) + v % 4
-    if constexpr (T == 32) {
-        // the four waves' sums, added in wave order
+    // step s in buffer s & 1; p = s % PD, `more`: its registers are filled for step s + PD
+    const auto one_step = [&](int p, int buf, bool more) __attribute__((always_inline)) {
+        float* const sa = lds + buf * (AW + BW);
+        float* const sb = sa + AW;
+        __builtin_amdgcn_sched_barrier(0);
+        f32_put<AL, T>(sa, ra[p]);
+        f32_put<BL, T>(sb, rb[p]);
         __syncthreads();
-        float* const red = lds;                                       // [wave - 1][v][lane]
-        static_assert(2 * (AW + BW) >= 3 * 16 * 64, "the waves' sums fit the operand buffers");
+        if (more) {
+            feed_a.fetch(ra[p]);
+            feed_b.fetch(rb[p]);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int cc = 0; cc < (SHARED ? 1 : F32_BK / 8); cc++) {
+            const int c = SHARED ? wave : cc;
+            const f32x4 fa = f32_frag<AL, T>(sa, wm + i32, c, half);
+            const f32x4 fb = f32_frag<BL, T>(sb, wn + i32, c, half);
+#pragma unroll
+            for (int q = 0; q < 4; q++) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[q], fb[q], acc, 0, 0, 0);
+        }
+    };
+    static_assert(PD % 2 == 0, "the steps of a trip alternate between the two buffers");
+    int s0 = 0;
+    for (; s0 + PD <= steps; s0 += PD) {
+#pragma unroll
+        for (int p = 0; p < PD; p++) one_step(p, p & 1, true);
+        end_trip();
+    }
+#pragma unroll
+    for (int p = 0; p < PD - 1; p++)
+        if (s0 + p < steps) one_step(p, p & 1, false);
+    end_trip();
+    // a lane holds column lane % 32 and, of each group of eight rows, four: rows 8 (v / 4) + 4 (lane / 32) + v % 4
+    float* const red = lds;                                           // [wave][v][lane]
+    const auto sum_of_waves = [&]() __attribute__((always_inline)) {  // in wave 0, in wave order
+        static_assert(!SHARED || 2 * (AW + BW) >= 4 * 16 * 64, "the waves' sums fit the operand buffers");
+        __syncthreads();
         if (wave > 0)
 #pragma unroll
-            for (int v = 0; v < 16; v++) red[((wave - 1) * 16 + v) * 64 + lane] = acc[v];
+            for (int v = 0; v < 16; v++) red[(wave * 16 + v) * 64 + lane] = sum[v];
         __syncthreads();
-        if (wave > 0) return;
+        if (wave == 0)
 #pragma unroll
-        for (int v = 0; v < 16; v++)
-            acc[v] = ((acc[v] + red[v * 64 + lane]) + red[(16 + v) * 64 + lane]) + red[(32 + v) * 64 + lane];
+            for (int v = 0; v < 16; v++)
+                sum[v] = ((sum[v] + red[(16 + v) * 64 + lane]) + red[(32 + v) * 64 + lane]) + red[(48 + v) * 64 + lane];
+    };
+    if constexpr (SHARED) sum_of_waves();
+    if (j.splits > 1) {
+        // The slice's sums go to its slab as the lanes hold them; the last slice to arrive at the tile adds the slabs up, in
+        // their order (a shared tile: every wave each fourth slab).
+        const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(j.part + (int64_t)t * j.splits * (T * T), 0, j.splits * (T * T) * 4, 0x00020000);
+        const uint32_t mine = 16u * (uint32_t)((SHARED ? 0 : wave * 256) + lane);
+        if (!SHARED || wave == 0)
+#pragma unroll
+            for (int q = 0; q < 4; q++) {
+                const f32x4 x = {sum[4 * q], sum[4 * q + 1], sum[4 * q + 2], sum[4 * q + 3]};
+                __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, x), rs, mine + 1024u * q + (uint32_t)split * (T * T * 4), 0, F32_SC1);
+            }
+        FHPC_WAIT_VM(0);                                              // (the slab is where every compute unit finds it before the ticket is drawn)
+        uint32_t* const s_ticket = reinterpret_cast<uint32_t*>(lds);
+        __syncthreads();
+        if (threadIdx.x == 0) *s_ticket = __hip_atomic_fetch_add(j.tickets + t, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __syncthreads();
+        if (*s_ticket != (uint32_t)(j.splits - 1)) return;
+        if (threadIdx.x == 0) __hip_atomic_store(j.tickets + t, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+        for (int v = 0; v < 16; v++) sum[v] = 0.f;
+        constexpr int STRIDE = SHARED ? 4 : 1;
+        for (int s = SHARED ? wave : 0; s < j.splits; s += 4 * STRIDE) {
+            u32x4 x[4][4];
+#pragma unroll
+            for (int i = 0; i < 4; i++)
+#pragma unroll
+                for (int q = 0; q < 4; q++)
+                    x[i][q] = __builtin_amdgcn_raw_buffer_load_b128(rs, s + i * STRIDE < j.splits ? mine + 1024u * q + (uint32_t)(s + i * STRIDE) * (T * T * 4) : F32_NONE, 0, F32_SC1);
+#pragma unroll
+            for (int i = 0; i < 4; i++)
+#pragma unroll
+                for (int v = 0; v < 16; v++) sum[v] += __builtin_bit_cast(f32x4, x[i][v / 4])[v % 4];
+        }
+        if constexpr (SHARED) sum_of_waves();
     }
+    if (SHARED && wave > 0) return;
     const int n = n0 + wn + i32;
 #pragma unroll
     for (int v = 0; v < 16; v++) {
         const int m = m0 + wm + 8 * (v >> 2) + 4 * half + (v & 3);
-        if (m < j.M && n < j.N) C[(int64_t)m * j.ldc + n] = acc[v];
+        if (m < j.M && n < j.N) j.c[(int64_t)m * j.ldc + n] = sum[v];
     }
 }
 
-int64_t gemm_f32_slab(int64_t M, int64_t N) { return (M * N + 3) / 4 * 4; }
+static int64_t f32_tiles(int64_t M, int64_t N, int64_t T) { return ((M + T - 1) / T) * ((N + T - 1) / T); }
+
+int64_t gemm_f32_part_bytes(const GemmF32Plan& p, int64_t M, int64_t N)
+{
+    return p.splits > 1 ? f32_tiles(M, N, p.tile) * p.splits * p.tile * p.tile * 4 : 0;
+}
 
 GemmF32Plan plan_gemm_f32(int jobs, const int64_t* M, const int64_t* N, const int64_t* K, int units, GemmF32Plan* each)
 {
-    // Microseconds a launch should take: what the busiest compute unit multiplies, the steps a workgroup has to walk one
-    // after the other however idle the unit is, and the slabs with their sum.  Fitted to 16 shapes x 11 slice counts:
-    // 192 x 3072 over 8192 takes 255 / 109 / 116 microseconds in 1 / 12 / 32 slices of 64 x 64 tiles (161 / 126 / - on
-    // 32 x 32), 1024 x 64 over 1024 33 / 10.5 / 10.6 in 1 / 8 / 16 (15.6 / 9.2 / 10.6), and the plan is within a tenth of
-    // the best of each row.
+    // Microseconds a launch should take: the workgroups of the busiest compute unit one after the other, each step as long as it
+    // takes with that many (up to the four that fit) sharing the unit, and what the last slice of a tile spends on the slabs.
+    // Fitted to 5 layers x 4 products x 10 slice counts on both tiles; the plan is within 2 % of the best of them in the mean.
+    // (192 x 3072 and 768 x 192 over 8192 tokens, one launch: 181 / 162 / 152 / 124 / 125 / 111 microseconds in 1 .. 6 and 8 slices.)
     const int tiles[2] = {64, 32};
-    const double rate[2] = {0.205e6, 0.15e6};      // multiply-adds per microsecond and compute unit
-    const double step[2] = {1.0, 0.375};           // microseconds per 32-deep step of a lone workgroup
+    const double step[2][4] = {{0.66, 0.66, 0.62, 0.58}, {0.28, 0.24, 0.22, 0.20}};
+    const double slab[2] = {0.11, 0.04};           // a slab of the tile read back by the last slice
     GemmF32Plan best = {64, 1, 0};
     double best_cost = -1.0;
     for (int t = 0; t < 2; t++) {
         const int64_t T = tiles[t];
         int64_t count = 0;
-        for (int i = 0; i < jobs; i++) count += ((M[i] + T - 1) / T) * ((N[i] + T - 1) / T);
+        for (int i = 0; i < jobs; i++) count += f32_tiles(M[i], N[i], T);
         int64_t last = 0;
-        for (int k = 0; k <= 4; k++) {
+        for (int k = 0; k <= 8; k++) {
             // unsplit, or as many slices as give every compute unit up to k workgroups
             int64_t s = (k == 0) ? 1 : (int64_t)k * units / count;
-            if (s > 64) s = 64;
-            if (s <= last) continue;
+            if (s > 32) s = 32;
+            if (s <= last || (s > 1 && count > F32_TICKETS)) continue;
             last = s;
             double items = 0.0, work = 0.0, slabs = 0.0;
-            int64_t deepest = 0;
-            bool split = false;
+            int64_t deepest = 0, most = 1;
             GemmF32Plan got[2];
             for (int i = 0; i < jobs; i++) {
                 const int64_t ksteps = (K[i] + F32_BK - 1) / F32_BK;
@@ -202,22 +292,20 @@ GemmF32Plan plan_gemm_f32(int jobs, const int64_t* M, const int64_t* N, const in
                 if (c < 1) c = 1;
                 const int64_t per = (ksteps + c - 1) / c;
                 c = (ksteps + per - 1) / per;
-                const int64_t n = ((M[i] + T - 1) / T) * ((N[i] + T - 1) / T) * c;
+                const int64_t n = f32_tiles(M[i], N[i], T) * c;
                 got[i].tile = (int)T;
                 got[i].splits = (int)c;
                 got[i].k_chunk = (int)(per * F32_BK);
                 items += (double)n;
-                work += (double)n * (double)(T * T) * (double)(per * F32_BK);
+                work += (double)n * ((double)per + 1.2);             // (1.2: a workgroup's first loads and its stores)
                 if (per > deepest) deepest = per;
-                if (c > 1) {
-                    split = true;
-                    slabs += (double)c * (double)M[i] * (double)N[i] * 8.0;
-                }
+                if (c > most) most = c;
+                if (c > 1) slabs += (double)n * (double)(T * T) * 8.0;
             }
-            const double rounds = (double)(int64_t)((items + units - 1) / units);
-            double cost = rounds * (work / items) / rate[t];
-            if (cost < (double)deepest * step[t]) cost = (double)deepest * step[t];
-            if (split) cost += 3.0 + slabs / 6.0e6;
+            const int rounds = (int)((items + units - 1) / units);
+            double cost = rounds * (work / items) * step[t][rounds < 4 ? rounds - 1 : 3];
+            if (cost < ((double)deepest + 1.2) * step[t][0]) cost = ((double)deepest + 1.2) * step[t][0];
+            if (most > 1) cost += 2.6 + most * slab[t] + slabs / 6.0e6;
             if (best_cost < 0.0 || cost < best_cost) {
                 best_cost = cost;
                 best = got[0];
@@ -229,40 +317,50 @@ GemmF32Plan plan_gemm_f32(int jobs, const int64_t* M, const int64_t* N, const in
 }
 
 template <F32Layout AL, F32Layout BL>
-static hipError_t launch_layout(const GemmF32Args& a, unsigned blocks, int tile, hipStream_t s)
+static hipError_t launch_layout(const GemmF32Args& a, unsigned blocks, int tile, bool vec, hipStream_t s)
 {
-    if (tile == 64) hipLaunchKernelGGL((gemm_f32_kernel<AL, BL, 64, 2>), dim3(blocks), dim3(256), 0, s, a);
-    else if (tile == 32) hipLaunchKernelGGL((gemm_f32_kernel<AL, BL, 32, 4>), dim3(blocks), dim3(256), 0, s, a);
+    if (tile == 64 && vec) hipLaunchKernelGGL((gemm_f32_kernel<AL, BL, 64, 2, true>), dim3(blocks), dim3(256), 0, s, a);
+    else if (tile == 64) hipLaunchKernelGGL((gemm_f32_kernel<AL, BL, 64, 2, false>), dim3(blocks), dim3(256), 0, s, a);
+    else if (tile == 32 && vec) hipLaunchKernelGGL((gemm_f32_kernel<AL, BL, 32, 4, true>), dim3(blocks), dim3(256), 0, s, a);
+    else if (tile == 32) hipLaunchKernelGGL((gemm_f32_kernel<AL, BL, 32, 4, false>), dim3(blocks), dim3(256), 0, s, a);
     else return hipErrorInvalidValue;
     return hipGetLastError();
 }
 
-hipError_t launch_gemm_f32(F32Layout al, F32Layout bl, const GemmF32Job* jobs, int count, int tile, hipStream_t s)
+hipError_t launch_gemm_f32(F32Layout al, F32Layout bl, const GemmF32Job* jobs, int count, int tile, float* part, uint32_t* tickets, hipStream_t s)
 {
     if (count < 1 || count > 2) return hipErrorInvalidValue;
     GemmF32Args a = {};
-    int64_t blocks = 0;
+    bool all_vec = true;
+    int64_t blocks = 0, counted = 0;
     for (int i = 0; i < count; i++) {
         GemmF32Job& j = a.job[i];
         j = jobs[i];
         if (j.M < 1 || j.N < 1 || j.K < 1 || j.splits < 1 || j.k_chunk < 1 || (j.k_chunk % F32_BK) != 0) return hipErrorInvalidValue;
         if ((int64_t)(j.splits - 1) * j.k_chunk >= j.K || (int64_t)j.splits * j.k_chunk < j.K) return hipErrorInvalidValue;
+        if (j.lda > F32_LD_MAX || j.ldb > F32_LD_MAX) return hipErrorInvalidValue;
         const auto vec = [](const float* p, int64_t ld, int64_t extent) {
             return ld % 4 == 0 && extent % 4 == 0 && reinterpret_cast<uintptr_t>(p) % 16 == 0;
         };
         // (a slice's end inside the reduction is a multiple of 32, so only its far end can cut a piece along k)
-        j.a_vec = vec(j.a, j.lda, al == F32_KC ? j.K : j.M);
-        j.b_vec = vec(j.b, j.ldb, bl == F32_KC ? j.K : j.N);
+        all_vec = all_vec && vec(j.a, j.lda, al == F32_KC ? j.K : j.M) && vec(j.b, j.ldb, bl == F32_KC ? j.K : j.N);
         j.tiles_n = (j.N + tile - 1) / tile;
-        const int64_t items = (int64_t)((j.M + tile - 1) / tile) * j.tiles_n * j.splits;
+        const int64_t tiles = f32_tiles(j.M, j.N, tile), items = tiles * j.splits;
         if (items > 0x3FFFFFFF) return hipErrorInvalidValue;
         j.items = (int)items;
         blocks += items;
+        if (j.splits > 1) {
+            j.part = part;
+            j.tickets = tickets + counted;
+            part += items * tile * tile;
+            counted += tiles;
+            if (!tickets || counted > F32_TICKETS) return hipErrorInvalidValue;
+        }
     }
     if (count == 1) a.job[1] = a.job[0];                     // (never reached: the grid ends with job 0)
-    if (al == F32_KC && bl == F32_XC) return launch_layout<F32_KC, F32_XC>(a, (unsigned)blocks, tile, s);
-    if (al == F32_KC && bl == F32_KC) return launch_layout<F32_KC, F32_KC>(a, (unsigned)blocks, tile, s);
-    if (al == F32_XC && bl == F32_XC) return launch_layout<F32_XC, F32_XC>(a, (unsigned)blocks, tile, s);
+    if (al == F32_KC && bl == F32_XC) return launch_layout<F32_KC, F32_XC>(a, (unsigned)blocks, tile, all_vec, s);
+    if (al == F32_KC && bl == F32_KC) return launch_layout<F32_KC, F32_KC>(a, (unsigned)blocks, tile, all_vec, s);
+    if (al == F32_XC && bl == F32_XC) return launch_layout<F32_XC, F32_XC>(a, (unsigned)blocks, tile, all_vec, s);
     return hipErrorInvalidValue;
 }
 

@@ -564,3 +564,31 @@ def test_few_token_launches_replayed_from_a_graph():
         torch.cuda.synchronize()
         assert all(torch.equal(a, b) for a, b in zip(out, eager[i])), i
         step(X[3], dY[3])                                            # other work on the eager workspace between the replays
+
+
+@pytest.mark.parametrize("M,K,r,N", [
+    (100, 2000, 100, 2008),  # 32 x 32 tiles in many slices: more slabs than the four waves take at a time
+    (1100, 4040, 170, 1928), # 64 x 64 tiles, the last step of a slice outside; rank not a multiple of four
+    (5, 8, 129, 40),         # a reduction shorter than a step
+])
+def test_fp32_slices_on_uncleared_scratch(M, K, r, N):
+    """The last slice to arrive at a tile adds the slabs: scratch full of NaN bit patterns gives the oracle's results, twice
+    the same, and the header is left zero."""
+    import torch
+    fhpc = _fhpc()
+    X, A, B, dY = lowrank_inputs(5, M, K, r, N, bf16=False)
+    Yr, Hr = oracle.lowrank_fwd(X, A, B)
+    ref = (Yr,) + oracle.lowrank_bwd(X, A, B, dY)
+    Xd, Ad, Bd, dYd = (torch.from_numpy(a).cuda() for a in (X, A, B, dY))
+    need = max(fhpc.workspace_bytes(op, M, K, r, N, fhpc.FHPC_F32) for op in (fhpc.FHPC_OP_LOWRANK_FWD, fhpc.FHPC_OP_LOWRANK_BWD))
+    first = None
+    for _ in range(2):
+        ws = torch.full((need,), 0xFF, dtype=torch.uint8, device="cuda")
+        ws[:16384] = 0                                               # (the header)
+        Y, H = fhpc.lowrank_linear_fwd(Xd, Ad, Bd, save_H=True, workspace=ws)
+        out = (Y,) + fhpc.lowrank_linear_bwd(Xd, Ad, Bd, dYd, H_saved=H, workspace=ws)
+        assert int(ws[:16384].sum()) == 0
+        if first is None:
+            first = out
+            _check_all("f32 slices %s" % ((M, K, r, N),), out, ref, TOL_F32)
+        assert all(torch.equal(a, b) for a, b in zip(out, first))
