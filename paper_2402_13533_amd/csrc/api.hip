@@ -188,7 +188,37 @@ SplitPlan plan_split_on(int tile, int64_t M, int64_t N, int64_t Kred, int g = 1)
     return sp;
 }
 
-// `rows32`: 32-row tiles whatever M is (the only fp32-output shape of the products X A, H B, dY B^T, dH A^T)
+// A product on 64 x 64 tiles (left operand with the reduction contiguous: X A, H B, dY B^T, dH A^T), whole or in slices of four steps at
+// least.  A 64-deep step takes 0.32 microseconds where a compute unit has one workgroup and 0.265 per workgroup where it has
+// more (1024 x 512 from 4096 in 2 slices 12.8, 2048 x 512 in 2 19.3, 4096 x 512 whole 32.4), and slabs are written and read at 4 TB/s by a launch more.
+SplitPlan plan_small(int64_t M, int64_t N, int64_t Kred)
+{
+    const int64_t ksteps = (Kred + 63) / 64, tiles = tile_count(TILE_64x64, M, N), most = ksteps / 4 < 64 ? ksteps / 4 : 64, units = num_cu();
+    double best = -1.0;
+    int64_t per = ksteps;
+    // whole, or as many slices as make full rounds of one to four workgroups per compute unit
+    for (int64_t each = 0; each <= 4; each++) {
+        int64_t s = each * units / tiles;
+        if (s > most) s = most;
+        if (s < 1) s = 1;
+        if (each > 0 && s == 1) continue;
+        const int64_t deep = (ksteps + s - 1) / s, n = (ksteps + deep - 1) / deep, load = (tiles * n + units - 1) / units;
+        double cost = (double)(load * deep) * (load == 1 ? 0.32 : 0.265);
+        if (n > 1) cost += 2.5 + (double)n * (double)(M * N) * 8.0 / 4.0e6;
+        if (best < 0.0 || cost < best) {
+            best = cost;
+            per = deep;
+        }
+        if (s == most) break;
+    }
+    SplitPlan sp;
+    sp.tile = TILE_64x64;
+    sp.k_chunk = (int)(per * 64);
+    sp.splits = (int)((ksteps + per - 1) / per);
+    return sp;
+}
+
+// `rows32`: 32-row tiles whatever M is (short_split_pays)
 SplitPlan plan_split(int64_t M, int64_t N, int64_t Kred, bool rows32 = false, int g = 1)
 {
     int tile;
@@ -210,35 +240,31 @@ SplitPlan plan_split(int64_t M, int64_t N, int64_t Kred, bool rows32 = false, in
 }
 
 // Bytes of partial-sum slabs for an M x N (leading dimension ldc) product reduced over Kred.
-int64_t split_bytes(int64_t M, int64_t N, int64_t ldc, int64_t Kred, bool rows32 = false)
+int64_t slab_bytes(const SplitPlan& sp, int64_t M, int64_t ldc) { return sp.splits > 1 ? (int64_t)sp.splits * M * ldc * 4 : 0; }
+int64_t split_bytes(int64_t M, int64_t N, int64_t ldc, int64_t Kred) { return slab_bytes(plan_split(M, N, Kred), M, ldc); }
+
+// A bf16 product M x Nout whose plain launch would put tiles on at most half of the compute units (or of few rows) runs on 64 x 64
+// tiles.  Measured, microseconds with the slab sum where there is one, against the best of the larger tiles: 4096 x 512 from 4096 32.4 / 38.0,
+// 1500 x 768 from 1600 15.8 / 20.4, 8192 x 64 from 4096 17.9 / 23.2; with twice the tiles (4096 x 1024) the larger ones are ahead.
+// (Outputs at most 32 wide: see rank_product.)
+bool small_pays(int64_t M, int64_t Nout)
 {
-    const SplitPlan sp = plan_split(M, N, Kred, rows32);
-    return sp.splits > 1 ? (int64_t)sp.splits * M * ldc * 4 : 0;
+    return Nout > 32 && (M <= 32 || 2 * tile_count(TILE_128x128, M, Nout) <= num_cu());
 }
 
-// A bf16 product M x Nout whose plain launch would put tiles on fewer than half of the compute units,
-// while its reduction is long, is bound by streaming the long operand through those few units: it runs
-// as a split reduction on 32-row tiles instead, as many slices as fill the chip, and the slab sum
-// rounds to bf16.  Measured on one factorised layer 4096 -> 512 -> 4096, forward: 64 tokens 52 -> 28
-// microseconds, 256 tokens 53 -> 30, 1024 tokens 54 -> 47; 11008 -> 1024 -> 4096 at 64 tokens 125 -> 30.
-// (Outputs at most 32 wide have their own split shape, see rank_product.)
-bool split_pays(int64_t M, int64_t Nout, int64_t Kred)
+// Few outputs of a reduction of at most 512, eight steps, go out in slices on 32-row tiles; larger outputs lose more to the slab
+// sum than the slices save (forward, microseconds, slices / whole on 128 x 128 tiles: 4096 -> 512 -> 4096 at 64 / 300 tokens 24 / 21, 31 / 24,
+// 2048 -> 256 -> 2048 at 600 26 / 19; but X A at 695 tokens, 416 -> 48, 17 / 19, at 386, 504 -> 112, 18 / 19).  The two are even at 32 K
+// outputs, 128 K on narrow ones, and half as much again beyond 384.
+bool short_split_pays(int64_t M, int64_t Nout, int64_t Kred)
 {
-    if (Nout <= 32) return false;
-    if (M > 32) {
-        const int64_t tiles = ((M + 127) / 128) * ((Nout + 127) / 128);
-        if (2 * tiles > num_cu() || Kred < 256) return false;
-        // at most 512 deep, eight steps, the slices save less than their slab sum costs once the output is large enough (forward,
-        // microseconds, slices / whole: 4096 -> 512 -> 4096 at 64 / 300 tokens 24 / 21, 31 / 24, 2048 -> 256 -> 2048 at 600 26 / 19;
-        // but X A at 695 tokens, 416 -> 48, 17 / 19, at 386, 504 -> 112, 18 / 19).  The two are even at 32 K outputs, 128 K on
-        // narrow ones, whose 128-wide tiles are mostly outside, and half as much again beyond 384.
-        if (Kred <= 512 && 2 * M * Nout >= (int64_t)(Nout > 256 ? 32768 : 131072) * (Kred > 384 ? 3 : 2)) return false;
-    }
+    if (Kred > 512 || !small_pays(M, Nout)) return false;
+    if (M > 32 && (Kred < 256 || 2 * M * Nout >= (int64_t)(Nout > 256 ? 32768 : 131072) * (Kred > 384 ? 3 : 2))) return false;
     return plan_split(M, Nout, Kred, true).splits > 1;
 }
 
 // From 256 tokens on, an output that gives at most a quarter of the compute units a 256 x 128 tile, with a
-// reduction of 1024 or more, takes the large request-fed tiles for its slices instead (slices of at least
+// reduction beyond 6144 (4096 x 512 from 4096 32.4 microseconds on 64 x 64 tiles, 38.0 on these; per step of the reduction 0.47 against 0.35), takes the large request-fed tiles for its slices instead (slices of at least
 // 512): one factorised layer 4096 -> 512 -> 4096 at 2048 tokens, forward 55 -> 43 microseconds and backward
 // 107 -> 96 against the 32-row tiles; at 4096 tokens, where X A is 64 tiles in 4 slices, 69 -> 56 and
 // 136 -> 125 against 128 unsplit tiles of 128 x 128.  At 8192 tokens (128 tiles) the slices and their slab
@@ -259,7 +285,7 @@ SplitPlan plan_large_split(int64_t M, int64_t Nout, int64_t Kred)
 
 bool large_split_pays(int64_t M, int64_t Nout, int64_t Kred)
 {
-    if (M < 256 || Nout <= 128 || Kred < 1024) return false;
+    if (M < 256 || Nout <= 128 || Kred <= 6144) return false;
     if (4 * tile_count(TILE_256x128, M, Nout) > num_cu()) return false;
     const SplitPlan sp = plan_large_split(M, Nout, Kred);
     // (with fewer workgroups than half the compute units the 32-row tiles do better)
@@ -269,7 +295,8 @@ bool large_split_pays(int64_t M, int64_t Nout, int64_t Kred)
 int64_t product_part_bytes(int64_t M, int64_t Nout, int64_t Kred)
 {
     if (large_split_pays(M, Nout, Kred)) return (int64_t)plan_large_split(M, Nout, Kred).splits * M * Nout * 4;
-    return split_pays(M, Nout, Kred) ? split_bytes(M, Nout, Nout, Kred, true) : 0;
+    if (short_split_pays(M, Nout, Kred)) return slab_bytes(plan_split(M, Nout, Kred, true), M, Nout);
+    return small_pays(M, Nout) ? slab_bytes(plan_small(M, Nout, Kred), M, Nout) : 0;
 }
 
 // The products of the finetuning and blend layers that dequantise the frozen weight in their load path
@@ -488,8 +515,8 @@ Scratch carve(Carver& c, int op, int64_t M, int64_t K, int64_t r, int64_t N, int
     int64_t part = 0;
     auto upto = [&part](int64_t b) { if (b > part) part = b; };
     if (rp <= 32) {
-        upto(split_bytes(M, rp, rp, K));               // H  = X A
-        if (bwd) upto(split_bytes(M, rp, rp, N));      // dH = dY B^T
+        upto(slab_bytes(plan_small(M, rp, K), M, rp));               // H  = X A
+        if (bwd) upto(slab_bytes(plan_small(M, rp, N), M, rp));      // dH = dY B^T
     } else {
         upto(product_part_bytes(M, rp, K));
         if (bwd) upto(product_part_bytes(M, rp, N));
@@ -609,7 +636,7 @@ GemmOperand operand(const void* p, int64_t ld, const void* scales = nullptr, int
 
 // C[M,N] bf16 = A(KC or via a_mode) * B, whole reduction in one workgroup per tile.
 hipError_t gemm_plain(int a_mode, int b_mode, GemmOperand a, GemmOperand b, void* C, int64_t ldc,
-                      int64_t M, int64_t N, int64_t Kred, Run& run, float alpha = 1.f)
+                      int64_t M, int64_t N, int64_t Kred, Run& run, float alpha = 1.f, int tile = -1)
 {
     if (run.dry) return hipSuccess;
     hipStream_t st = run.st;
@@ -617,7 +644,7 @@ hipError_t gemm_plain(int a_mode, int b_mode, GemmOperand a, GemmOperand b, void
     g.a = a; g.b = b; g.c = C; g.ldc = ldc;
     g.M = (int)M; g.N = (int)N; g.K = (int)Kred; g.K2 = 0;
     g.alpha = alpha; g.mid_scale = 1.f; g.splits = 1; g.k_chunk = (int)round_up(Kred, 64);
-    return launch_gemm_bf16(a_mode, b_mode, OP_NONE, OUT_BF16, pick_tile(M, N, false), g, st);
+    return launch_gemm_bf16(a_mode, b_mode, OP_NONE, OUT_BF16, tile < 0 ? pick_tile(M, N, false) : tile, g, st);
 }
 
 // C[M,N] fp32 (ldc) = alpha * A * B with the reduction split across workgroups: every
@@ -627,11 +654,10 @@ hipError_t gemm_plain(int a_mode, int b_mode, GemmOperand a, GemmOperand b, void
 // left alone: *wrote_bf16 tells the caller which happened.
 hipError_t gemm_split_f32(int a_mode, int b_mode, GemmOperand a, GemmOperand b, float* C, int64_t ldc,
                           int64_t M, int64_t N, int64_t Kred, float alpha, float* part, Run& run,
-                          void* bf16_out = nullptr, bool* wrote_bf16 = nullptr, bool rows32 = false,
-                          const SplitPlan* plan = nullptr)
+                          void* bf16_out = nullptr, bool* wrote_bf16 = nullptr, const SplitPlan* plan = nullptr)
 {
     if (wrote_bf16) *wrote_bf16 = false;
-    const SplitPlan sp = plan ? *plan : plan_split(M, N, Kred, rows32);
+    const SplitPlan sp = plan ? *plan : plan_split(M, N, Kred);
     if (!run.claim(sp.splits > 1 ? (int64_t)sp.splits * M * ldc * 4 : 0)) return hipErrorOutOfMemory;
     if (run.dry) {
         if (wrote_bf16) *wrote_bf16 = (sp.splits > 1 && bf16_out);
@@ -659,27 +685,30 @@ hipError_t gemm_split_f32(int a_mode, int b_mode, GemmOperand a, GemmOperand b, 
     return launch_sum_slabs(part, M * ldc, sp.splits, C, false, st);
 }
 
-// P[M][Nout] (bf16, row stride ldp) = L * R, L with k contiguous: the plain launch, or the split reduction on
-// 32-row tiles when that pays (split_pays) and P is dense.
+// P[M][Nout] (bf16, row stride ldp) = L * R, L with k contiguous: the plain launch, the split reduction on large tiles (large_split_pays),
+// or 64 x 64 tiles (small_pays), whole or, where P is dense, in slices (32-row ones: short_split_pays).
 hipError_t product_bf16(int b_mode, GemmOperand a, GemmOperand b, void* P, int64_t ldp, int64_t Nout,
                         int64_t M, int64_t Kred, float* part, Run& run)
 {
-    const bool large = large_split_pays(M, Nout, Kred);
-    if (ldp == Nout && (large || split_pays(M, Nout, Kred))) {
+    const bool small = small_pays(M, Nout);
+    if (ldp == Nout) {
+        SplitPlan sp;
+        sp.splits = 1;
+        if (large_split_pays(M, Nout, Kred)) sp = plan_large_split(M, Nout, Kred);
+        else if (short_split_pays(M, Nout, Kred)) sp = plan_split(M, Nout, Kred, true);
+        else if (small) sp = plan_small(M, Nout, Kred);
         bool done = false;
-        // more than one slice (checked by both rules), so the slab sum writes P and no fp32 output is touched
-        const SplitPlan lp = large ? plan_large_split(M, Nout, Kred) : SplitPlan();
-        return gemm_split_f32(OP_KC, b_mode, a, b, nullptr, Nout, M, Nout, Kred, 1.f, part, run, P, &done, !large,
-                              large ? &lp : nullptr);
+        // (with more than one slice the slab sum writes P and no fp32 output is touched)
+        if (sp.splits > 1) return gemm_split_f32(OP_KC, b_mode, a, b, nullptr, Nout, M, Nout, Kred, 1.f, part, run, P, &done, &sp);
     }
-    return gemm_plain(OP_KC, b_mode, a, b, P, ldp, M, Nout, Kred, run);
+    return gemm_plain(OP_KC, b_mode, a, b, P, ldp, M, Nout, Kred, run, 1.f, small ? TILE_64x64 : -1);
 }
 
 // Whether a dense bf16 product M x Nout runs as one plain launch of the 256 x 256 request-fed kernel, the one
 // whose epilogue can apply the FFN's SiLU gate to the tile it has just produced (GemmArgs::gate).
 static bool gate_rides(int64_t M, int64_t Nout, int64_t Kred)
 {
-    if (large_split_pays(M, Nout, Kred) || split_pays(M, Nout, Kred)) return false;
+    if (large_split_pays(M, Nout, Kred) || small_pays(M, Nout)) return false;
     return pick_tile(M, Nout, false) == TILE_256x256;
 }
 
@@ -715,7 +744,9 @@ hipError_t rank_product(int b_mode, GemmOperand a, GemmOperand b, void* P, int64
     }
     if (rp <= 32) {
         bool done = false;
-        hipError_t e = gemm_split_f32(OP_KC, b_mode, a, b, Pf, rp, M, rp, Kred, 1.f, part, run, P, &done);
+        const SplitPlan sp = plan_small(M, rp, Kred);
+        if (sp.splits == 1) return gemm_plain(OP_KC, b_mode, a, b, P, rp, M, rp, Kred, run, 1.f, TILE_64x64);
+        hipError_t e = gemm_split_f32(OP_KC, b_mode, a, b, Pf, rp, M, rp, Kred, 1.f, part, run, P, &done, &sp);
         if (e != hipSuccess || done || run.dry) return e;
         return launch_compact_f32(Pf, rp, P, rp, M, rp, 1.f, true, run.st);
     }
@@ -1285,13 +1316,13 @@ static SharedScratch carve_shared(Carver& c, bool bwd, int64_t M, int64_t K, int
     if (r <= 32) s.Pf = static_cast<float*>(c.take(M * (R <= 32 ? R : r) * 4));
     int64_t part = 0;
     auto upto = [&part](int64_t b) { if (b > part) part = b; };
-    upto(R <= 32 ? split_bytes(M, R, R, K) : product_part_bytes(M, R, K));      // H_all = X A_all
+    upto(R <= 32 ? slab_bytes(plan_small(M, R, K), M, R) : product_part_bytes(M, R, K));      // H_all = X A_all
     if (!bwd) upto(product_part_bytes(M, N, r));       // Y_i = H_i B_i
     if (bwd) {
         upto(product_part_bytes(M, K, R));             // dX = dH_all A_all^T
         // dH_i = dY_i B_i^T: at most 32 wide it splits its reduction; wider, it is a column block of dH_all and
         // runs unsplit, except for g = 1, where the block is the whole (dense) matrix and may take the 32-row split
-        if (r <= 32) upto(split_bytes(M, r, r, N));
+        if (r <= 32) upto(slab_bytes(plan_small(M, r, N), M, r));
         else if (g == 1) upto(product_part_bytes(M, r, N));
         if (g > 1) upto(grouped_dh_bytes(M, r, N, g));  // dH_i in one launch in slices
         upto(joint_part_bytes(M, K, r, N, g));         // dA_all and the dB_i in one launch, or
@@ -1331,7 +1362,8 @@ static hipError_t narrow_product(int b_mode, GemmOperand a, GemmOperand b, void*
                                  float* Pf, float* part, int64_t M, int64_t Kred, Run& run)
 {
     if (r > 32) return product_bf16(b_mode, a, b, P, ldp, r, M, Kred, part, run);
-    hipError_t e = gemm_split_f32(OP_KC, b_mode, a, b, Pf, r, M, r, Kred, 1.f, part, run);
+    const SplitPlan sp = plan_small(M, r, Kred);
+    hipError_t e = gemm_split_f32(OP_KC, b_mode, a, b, Pf, r, M, r, Kred, 1.f, part, run, nullptr, nullptr, &sp);
     if (e != hipSuccess || run.dry) return e;
     return launch_compact_f32(Pf, r, P, ldp, M, r, 1.f, true, run.st);
 }
@@ -1364,7 +1396,7 @@ static int grouped_tile(int b_mode, int64_t M, int64_t Nout, int64_t Kred, int g
 static bool groupable_bf16(int b_mode, int64_t M, int64_t Nout, int64_t ldp, int64_t Kred, int g)
 {
     if (g < 2 || g > GEMM_MAX_GROUPS) return false;
-    if (ldp == Nout && (large_split_pays(M, Nout, Kred) || split_pays(M, Nout, Kred))) return false;
+    if (ldp == Nout && (large_split_pays(M, Nout, Kred) || (small_pays(M, Nout) && (M <= 32 || Kred > 512)) || short_split_pays(M, Nout, Kred))) return false;
     return gemm_pp_supports(OP_KC, b_mode, OP_NONE, OUT_BF16, grouped_tile(b_mode, M, Nout, Kred, g));
 }
 
@@ -2238,7 +2270,7 @@ int fhpc_gemm_bf16(const void* A, int64_t lda, int a_mode, const void* B, int64_
     if (M < 1 || N < 1 || K < 1 || (K % 8) || (N % 8) || splits < 1) return FHPC_ERR_SHAPE;
     if ((a_mode != OP_KC && a_mode != OP_XC) || (b_mode != OP_KC && b_mode != OP_XC)) return FHPC_ERR_DTYPE;
     if (a_mode == OP_XC && (M % 8)) return FHPC_ERR_SHAPE;
-    if (M * K * 2 >= kMaxBytes || N * K * 2 >= kMaxBytes || tile < 0 || tile >= TILE_COUNT) return FHPC_ERR_UNSUPPORTED;
+    if (M * K * 2 >= kMaxBytes || N * K * 2 >= kMaxBytes || tile < 0 || tile > TILE_32x256) return FHPC_ERR_UNSUPPORTED;
     if (!aligned(A, 16) || !aligned(B, 16) || !aligned(C, 16)) return FHPC_ERR_ALIGN;
     GemmArgs g = {};
     g.a = operand(A, lda);

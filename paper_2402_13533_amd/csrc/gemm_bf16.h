@@ -37,7 +37,8 @@ enum : int {
     TILE_128x128 = 3,  // 2 x 2 waves of 64 x 64
     TILE_256x32 = 4,   // 4 x 1 waves of 64 x 32   (rank-r outputs: H, dH, dA)
     TILE_32x256 = 5,   // 1 x 4 waves of 32 x 64   (dB)
-    TILE_COUNT = 6
+    TILE_64x64 = 6,    // 2 x 2 waves of 32 x 32   (KC x KC and KC x XC outputs with few large tiles)
+    TILE_COUNT = 7
 };
 
 constexpr int GEMM_MAX_GROUPS = 8;

@@ -698,7 +698,7 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void gemm_bf16_kernel(GemmAr
     // ---- epilogue: lane holds C[m][n .. n+3] for 4 groups of columns per 32x32 block
     const float alpha = p.alpha;
     const int l32 = lane & 31, hi = lane >> 5;
-    if constexpr (OUT_MODE == OUT_BF16 && BM >= 128 && BN >= 128) {
+    if constexpr (OUT_MODE == OUT_BF16 && BM >= 64 && BN >= 64) {
         // bf16 output: the tile goes through LDS (free after the last barrier of the main loop)
         // as [BM][BN] with the 16-byte chunks of a row XOR-swizzled by the row, so that the
         // global stores are whole 16-byte chunks running along rows (full cache lines).
@@ -808,9 +808,20 @@ static hipError_t launch_skinny(int tile, const GemmArgs& a, hipStream_t s)
     }
 }
 
+// Small outputs: 64 x 64 on four waves, 32 KB of LDS, so that several workgroups share a compute unit and one multiplies while another
+// waits for its tile.  Bound by the operand tiles coming through the L2 (an output of n columns reads its left operand n / 64 times) and
+// by the steps' latency.  Against 32 x 256 tiles, which read the right operand M / 32 times (slabs not counted, microseconds): 1000 x 384
+// from 6400 21.9 -> 13.7, 1000 x 64 from 8192 14.2 -> 6.5, 3000 x 64 from 4096 24.1 -> 8.0, 128 x 512 from 4096 6.4 -> 4.7; against 256 x 32
+// tiles: 300 x 16 from 4096 5.1 -> 3.6, 4096 x 16 from 5120 10.9 -> 9.2.  64 x 128, 64 x 256 and 128 x 128 tiles lie between or behind.
+template <int BMODE, int OUT>
+static hipError_t launch_small(const GemmArgs& a, hipStream_t s)
+{
+    return launch_one<64, 64, 2, 2, OP_KC, BMODE, OP_NONE, OUT, 2, false>(a, s);
+}
+
 void gemm_tile_extent(int tile, int* bm, int* bn)
 {
-    static const int ext[TILE_COUNT][2] = {{256, 256}, {128, 256}, {256, 128}, {128, 128}, {256, 32}, {32, 256}};
+    static const int ext[TILE_COUNT][2] = {{256, 256}, {128, 256}, {256, 128}, {128, 128}, {256, 32}, {32, 256}, {64, 64}};
     *bm = ext[tile][0];
     *bn = ext[tile][1];
 }
@@ -827,6 +838,12 @@ hipError_t launch_gemm_bf16(int a_mode, int b_mode, int b2_mode, int out_mode, i
     if (args.groups > 1) return hipErrorInvalidValue;           // grouped products: the request-fed kernels only
     if (args.n_split > 0) return hipErrorInvalidValue;          // a second output: the request-fed kernels only
     if (args.gate != 0) return hipErrorInvalidValue;           // the gate epilogue: the request-fed kernels only
+    if (tile == TILE_64x64) {
+        if (a_mode != OP_KC || b2_mode != OP_NONE) return hipErrorInvalidValue;
+        if (b_mode == OP_KC) return out_mode == OUT_BF16 ? launch_small<OP_KC, OUT_BF16>(args, stream) : launch_small<OP_KC, OUT_F32>(args, stream);
+        if (b_mode == OP_XC) return out_mode == OUT_BF16 ? launch_small<OP_XC, OUT_BF16>(args, stream) : launch_small<OP_XC, OUT_F32>(args, stream);
+        return hipErrorInvalidValue;
+    }
     const bool skinny = (tile == TILE_256x32 || tile == TILE_32x256);
 #define FHPC_CASE(AM, BMODE, B2, OUT)                                                         \
     if (a_mode == AM && b_mode == BMODE && b2_mode == B2 && out_mode == OUT && !skinny)       \

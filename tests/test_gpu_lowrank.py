@@ -592,3 +592,35 @@ def test_fp32_slices_on_uncleared_scratch(M, K, r, N):
             first = out
             _check_all("f32 slices %s" % ((M, K, r, N),), out, ref, TOL_F32)
         assert all(torch.equal(a, b) for a, b in zip(out, first))
+
+
+@pytest.mark.parametrize("M,K,r,N", [
+    (65, 264, 40, 72),        # one row and a part of a tile beyond 64; everything whole
+    (127, 776, 64, 712),      # whole rank products, a rank of one tile exactly
+    (128, 4104, 72, 568),     # many slices, the last one short; nine of 64 columns of the second tile
+    (300, 2056, 16, 520),     # at most 32 wide: most of the tile outside
+    (1000, 1600, 376, 1544),  # two workgroups and more per compute unit
+    (2100, 1032, 264, 264),   # slices and whole products beside each other, a ragged last tile in both directions
+    (8200, 520, 64, 1288),    # whole over many tokens
+])
+def test_small_tile_products(M, K, r, N):
+    """Outputs with few large tiles run on 64 x 64 ones, whole or in slices: against the oracle, inside their buffers, from scratch
+    that nobody cleared, and with the same bits whether H is saved or formed again."""
+    import torch
+    fhpc = _fhpc()
+    X = Bf16.normal(61, (M, K)); A = Bf16.normal(62, (K, r), K ** -0.5)
+    B = Bf16.normal(63, (r, N), r ** -0.5); dY = Bf16.normal(64, (M, N))
+    Yr, Hr = oracle.lowrank_fwd(X.f64, A.f64, B.f64)
+    ref = (Yr,) + oracle.lowrank_bwd(X.f64, A.f64, B.f64, dY.f64)
+    Xd, Ad, Bd, dYd = X.cuda(), A.cuda(), B.cuda(), dY.cuda()
+    ws = torch.full((fhpc.workspace_bytes(fhpc.FHPC_OP_LOWRANK_BWD, M, K, r, N) + 4096,), 0xFF, dtype=torch.uint8, device="cuda")
+    ws[:16384] = 0
+    guard = Guarded()
+    g = [guard.alloc(s, t) for s, t in (((M, N), torch.bfloat16), ((M, r), torch.bfloat16), ((M, K), torch.bfloat16),
+                                        ((K, r), torch.float32), ((r, N), torch.float32))]
+    Y, H = fhpc.lowrank_linear_fwd(Xd, Ad, Bd, Y=g[0], H_out=g[1])
+    assert parity_err(from_device(H), Hr, TOL_BF16, "H") <= TOL_BF16
+    out = fhpc.lowrank_linear_bwd(Xd, Ad, Bd, dYd, H_saved=H, dX=g[2], dA=g[3], dB=g[4], workspace=ws)
+    _check_all("small tiles %s" % ((M, K, r, N),), (Y,) + out, ref, TOL_BF16)
+    guard.check("small tiles %s" % ((M, K, r, N),))
+    assert all(torch.equal(a, b) for a, b in zip(fhpc.lowrank_linear_bwd(Xd, Ad, Bd, dYd, workspace=ws), out))
