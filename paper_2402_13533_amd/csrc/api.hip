@@ -308,7 +308,7 @@ int64_t product_part_bytes(int64_t M, int64_t Nout, int64_t Kred)
 // most 128 tiles of 256 x 256 (one workgroup per compute unit) takes those.  Measured on a 4-bit
 // 5120 x 5120 weight: 65 tokens 76 -> 34 microseconds forward and 96 -> 49 backward, 256 tokens 86 -> 47 and
 // 101 -> 63, 1024 tokens (80 tiles of 256 x 256, 3 slices) 107 -> 91 and 133 -> 108.
-SplitPlan plan_fused_split(int64_t M, int64_t Nout, int64_t Kred)
+SplitPlan plan_fused_large(int64_t M, int64_t Nout, int64_t Kred)
 {
     SplitPlan sp;
     sp.tile = TILE_128x128;
@@ -338,6 +338,31 @@ SplitPlan plan_fused_split(int64_t M, int64_t Nout, int64_t Kred)
     return sp;
 }
 
+// Up to 384 tokens tiles of 64 x 128 compute fewer rows that do not exist and need half the slices for as many workgroups, as long as
+// three slices of them fit two to a compute unit and the reduction is at most 5120; more tiles are ahead with 128 rows, which dequantise the
+// weight less often, and longer reductions with more slices.  Whole call of the forward in microseconds, 128 / 64 rows: 8-bit 4096 x 4096 at 300
+// tokens 40.7 / 37.9, at 100 28.0 / 25.3, 5120 x 4096 at 250 38.4 / 33.7, 2048 x 2048 at 200 23.0 / 20.4, 4-bit 2816 x 5120 at 150 33.6 / 30.1;
+// 4-bit 11008 x 4096 at 65 39.6 / 44.5, 8-bit 11008 x 4096 at 500 (256 tiles) 74.9 / 87.
+SplitPlan plan_fused_split(int64_t M, int64_t Nout, int64_t Kred)
+{
+    const int64_t units = num_cu(), tiles = tile_count(TILE_64x128, M, Nout), ksteps = (Kred + 63) / 64;
+    if (M <= 384 && Kred <= 5120 && 3 * tiles <= 2 * units) {
+        int64_t s = 2 * units / tiles < 4 ? 2 * units / tiles : 4;
+        if (s < units / tiles) s = units / tiles;
+        if (s > ksteps / 8) s = ksteps / 8;
+        if (s > 16) s = 16;
+        if (s >= 2) {
+            const int64_t per = (ksteps + s - 1) / s;
+            SplitPlan sp;
+            sp.tile = TILE_64x128;
+            sp.k_chunk = (int)(per * 64);
+            sp.splits = (int)((ksteps + per - 1) / per);
+            return sp;
+        }
+    }
+    return plan_fused_large(M, Nout, Kred);
+}
+
 int64_t fused_part_bytes(int64_t M, int64_t Nout, int64_t Kred)
 {
     const SplitPlan sp = plan_fused_split(M, Nout, Kred);
@@ -348,7 +373,7 @@ int64_t fused_part_bytes(int64_t M, int64_t Nout, int64_t Kred)
 // launch fills over its rounds, times the per-flop standing of that tile shape (see pick_tile).
 static double dequant_route_fill(int64_t M, int64_t Nout, int64_t Kred)
 {
-    const SplitPlan sp = plan_fused_split(M, Nout, Kred);
+    const SplitPlan sp = plan_fused_large(M, Nout, Kred);
     if (sp.splits > 1) {
         const bool small = (sp.tile == TILE_128x128);
         return (double)(tile_count(sp.tile, M, Nout) * sp.splits) / (double)((small ? 2 : 1) * num_cu());

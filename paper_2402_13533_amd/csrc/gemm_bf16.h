@@ -38,7 +38,8 @@ enum : int {
     TILE_256x32 = 4,   // 4 x 1 waves of 64 x 32   (rank-r outputs: H, dH, dA)
     TILE_32x256 = 5,   // 1 x 4 waves of 32 x 64   (dB)
     TILE_64x64 = 6,    // 2 x 2 waves of 32 x 32   (KC x KC and KC x XC outputs with few large tiles)
-    TILE_COUNT = 7
+    TILE_64x128 = 7,   // 2 x 2 waves of 32 x 64   (products with a rank-r phase, a few hundred rows, fp32 slabs)
+    TILE_COUNT = 8
 };
 
 constexpr int GEMM_MAX_GROUPS = 8;

@@ -794,8 +794,13 @@ static hipError_t launch_tile(int tile, const GemmArgs& a, hipStream_t s)
         case TILE_128x256: return launch_one<128, 256, 2, 4, AM, BMODE, B2, OUT, 2, true>(a, s);
         case TILE_256x128: return launch_one<256, 128, 4, 2, AM, BMODE, B2, OUT, 2, true>(a, s);
         case TILE_128x128: return launch_one<128, 128, 2, 2, AM, BMODE, B2, OUT, PF, false>(a, s);
-        default: return hipErrorInvalidValue;
+        case TILE_64x128:
+            // (48 KB of LDS and half the accumulators: two staging sets fit beside them for every operand kind)
+            if constexpr (AM == OP_KC && B2 != OP_NONE && OUT == OUT_F32) return launch_one<64, 128, 2, 2, AM, BMODE, B2, OUT, 2, false>(a, s);
+            break;
+        default: break;
     }
+    return hipErrorInvalidValue;
 }
 
 template <int AM, int BMODE, int OUT>
@@ -821,7 +826,7 @@ static hipError_t launch_small(const GemmArgs& a, hipStream_t s)
 
 void gemm_tile_extent(int tile, int* bm, int* bn)
 {
-    static const int ext[TILE_COUNT][2] = {{256, 256}, {128, 256}, {256, 128}, {128, 128}, {256, 32}, {32, 256}, {64, 64}};
+    static const int ext[TILE_COUNT][2] = {{256, 256}, {128, 256}, {256, 128}, {128, 128}, {256, 32}, {32, 256}, {64, 64}, {64, 128}};
     *bm = ext[tile][0];
     *bn = ext[tile][1];
 }

@@ -826,3 +826,25 @@ def test_premerged_weight(scheme, M):
             assert torch.equal(a, b)
     with pytest.raises(fhpc.FhpcError):          # the blend layer does not take a merged weight
         fhpc.qlinear_blend_fwd(Xd, Wm, None, fhpc.FHPC_W_MERGED, Ad, Bd, 0.5)
+
+
+@pytest.mark.parametrize("q", [4, 8])
+@pytest.mark.parametrize("M,K,r,N", [
+    (66, 1088, 16, 520),      # two rows beyond one block, slices of unequal depth, nine of 64 columns of a tile
+    (129, 2048, 40, 1032),    # one row beyond two blocks; a rank beyond 32
+    (384, 1024, 8, 2112),     # the last row count of these tiles; two slices
+])
+def test_dequantising_products_on_64_row_tiles(q, M, K, r, N):
+    import torch
+    import paper_2402_13533_amd as fhpc
+    from paper_2402_13533_amd import synth
+    W = synth.normal(71, (K, N), 0.02)
+    Wq, sc = oracle.quantize_int4_block(W, 64) if q == 4 else oracle.quantize_int8_perchannel(W)
+    Wd = oracle.dequant(Wq, sc, q, 64)
+    X = Bf16.normal(72, (M, K)); A = Bf16.normal(73, (K, r), K ** -0.5)
+    B = Bf16.normal(74, (r, N), 0.01); dY = Bf16.normal(75, (M, N))
+    w = (X.cuda(), torch.from_numpy(Wq).cuda(), f16_bits_cuda(sc), q, A.cuda(), B.cuda(), 2.0)
+    got = (fhpc.qlinear_lowrank_fwd(*w), *fhpc.qlinear_lowrank_bwd(*w, dY.cuda()))
+    ref = (oracle.qlinear_lowrank_fwd(X.f64, Wd, A.f64, B.f64, 2.0)[0],) + oracle.qlinear_lowrank_bwd(X.f64, Wd, A.f64, B.f64, 2.0, dY.f64)
+    for name, g, rf in zip(("Y", "dX", "dA", "dB"), got, ref):
+        assert parity_err(from_device(g), rf, TOL_BF16, name) <= TOL_BF16
