@@ -758,7 +758,7 @@ static hipError_t gemm_gated(int b_mode, GemmOperand a, GemmOperand b, void* P, 
 static bool tall_skinny_pays(int64_t M) { return M >= 8 * (int64_t)num_cu(); }
 
 // Rank-r product P[M][rp] (bf16) = L * R where the output is only rp <= 32 wide:
-// split the long reduction, accumulate in fp32, then round once to bf16.
+// 64 x 64 tiles, most of their columns outside, in slices of the long reduction; summed in fp32, rounded once to bf16.
 hipError_t rank_product(int b_mode, GemmOperand a, GemmOperand b, void* P, int64_t rp, float* Pf, float* part,
                         int64_t M, int64_t Kred, Run& run)
 {
