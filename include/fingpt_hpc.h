@@ -13,10 +13,12 @@
  *    device memory.  Scratch comes from `workspace` (device pointer, 256-byte
  *    aligned, size from fhpc_workspace_bytes); too small => FHPC_ERR_WORKSPACE
  *    and nothing is launched.  Every workspace layout begins with a header of
- *    FHPC_WORKSPACE_HEADER_BYTES that holds arrival counters of the weight-streaming
- *    launches (a launch's last workgroup to reach a block of outputs finishes it).  The
- *    header must be ZERO when a buffer is first handed to the library (clear the buffer
- *    once after allocating it); every call leaves the header zero again, so a buffer
+ *    FHPC_WORKSPACE_HEADER_BYTES that holds arrival counters (the last workgroup of a launch to
+ *    reach a block of outputs finishes it): of the weight-streaming launches, of the factorised
+ *    layer with at most 64 tokens, and of every fp32 product whose reduction is cut into slices.
+ *    The header must be ZERO when a buffer is first handed to the library (clear the buffer
+ *    once after allocating it: in memory that a graph capture allocates, the graph itself has
+ *    to clear it, before its first call); every call leaves the header zero again, so a buffer
  *    can be reused from call to call, by any entry point, without clearing, also under
  *    HIP graph replay.  The rest of a workspace may hold anything.
  *  - `hip_stream` is a hipStream_t passed as void* (NULL = the default stream).
@@ -366,6 +368,10 @@ int fhpc_probe_read_rows(const void* W, int64_t N, int64_t row_bytes, int workgr
 enum { FHPC_PLAN_SHARED_FWD = 16, FHPC_PLAN_SHARED_BWD = 17, FHPC_PLAN_FFN_GATE_UP = 18, FHPC_PLAN_FFN_DOWN_BWD = 19 };
 int fhpc_plan_slab_bytes(int call, int64_t M, int64_t K, int64_t r, int64_t N, int dtype, int qscheme, int g,
                          int outputs, float base_scale, int64_t* planned, int64_t* reserved);
+
+/* Id of the capture that `hip_stream` takes part in (unique among captures of the process), 0 when it takes part in
+ * none: for a binding that keeps scratch per graph.  Host-only. */
+int fhpc_capture_id(void* hip_stream, uint64_t* id);
 
 /* Library version (major * 100 + minor). */
 int fhpc_version(void);

@@ -19,13 +19,15 @@ FHPC_W_MERGED = 17        # qlinear_lowrank_fwd/bwd only: Wq is the bf16 [K,N] w
 FHPC_OP_LOWRANK_FWD, FHPC_OP_LOWRANK_BWD, FHPC_OP_QLINEAR_FWD, FHPC_OP_QLINEAR_BWD, FHPC_OP_MERGE, FHPC_OP_DECOMPOSE = 0, 1, 2, 3, 4, 5
 FHPC_PLAN_SHARED_FWD, FHPC_PLAN_SHARED_BWD, FHPC_PLAN_FFN_GATE_UP, FHPC_PLAN_FFN_DOWN_BWD = 16, 17, 18, 19
 
+FHPC_WORKSPACE_HEADER_BYTES = 16384
+
 EXPORTS = [
     "lowrank_linear_fwd", "lowrank_linear_bwd", "qlinear_lowrank_fwd", "qlinear_lowrank_bwd", "qlinear_blend_fwd", "qlinear_blend_bwd", "lowrank_merge", "lowrank_decompose", "qlinear_lowrank_fwd_shared_x", "fhpc_workspace_bytes_shared_x",
     "lowrank_linear_fwd_shared_x", "lowrank_linear_bwd_shared_x", "fhpc_workspace_bytes_lowrank_shared_x",
     "lowrank_ffn_gate_up_fwd", "lowrank_ffn_down_bwd",
     "fhpc_workspace_bytes", "swiglu_fwd", "swiglu_bwd", "qweight_quantize", "qweight_unpack",
     "qweight_dequant", "fhpc_add", "fhpc_gemm_bf16", "fhpc_profile_start", "fhpc_profile_stop", "fhpc_profile_get",
-    "fhpc_status_string", "fhpc_version", "fhpc_plan_slab_bytes", "qlinear_lowrank_fwd_noalloc", "fhpc_probe_mfma", "fhpc_probe_copy", "fhpc_probe_read_rows",
+    "fhpc_status_string", "fhpc_version", "fhpc_plan_slab_bytes", "fhpc_capture_id", "qlinear_lowrank_fwd_noalloc", "fhpc_probe_mfma", "fhpc_probe_copy", "fhpc_probe_read_rows",
 ]
 
 _lib = None
@@ -88,6 +90,7 @@ def load_library():
     lib.fhpc_profile_get.argtypes = [i32, C.c_char_p, i32, C.POINTER(C.c_float), C.POINTER(C.c_double),
                                      C.POINTER(C.c_double)]
     lib.fhpc_plan_slab_bytes.argtypes = [i32, i64, i64, i64, i64, i32, i32, i32, i32, f32, C.POINTER(i64), C.POINTER(i64)]
+    lib.fhpc_capture_id.argtypes = [vp, C.POINTER(C.c_uint64)]
     lib.fhpc_probe_mfma.argtypes = [vp, i32, i32, vp, C.POINTER(C.c_double), vp]
     lib.fhpc_probe_copy.argtypes = [vp, vp, i64, vp]
     lib.fhpc_probe_read_rows.argtypes = [vp, i64, i64, i32, vp, vp]
@@ -224,12 +227,14 @@ def _check(t, name, shape=None, dtype=None):
         raise TypeError("%s has dtype %s, expected %s" % (name, t.dtype, dtype))
 
 
-_workspaces = {}
+_workspaces = {}              # (device, stream) -> the tensor its eager calls share
+_capture_workspaces = {}      # (device, stream) -> (capture id, the tensor that capture's calls share)
 
 
 def get_workspace(nbytes: int, device):
     """A cached byte tensor of at least nbytes (grown on demand), one per device and stream: calls that share a
-    workspace must be ordered on one stream."""
+    workspace must be ordered on one stream.  While the stream is being captured into a graph: a tensor of that
+    graph's own, whose header the graph itself clears."""
     torch = _torch()
     if not isinstance(device, torch.device):
         device = torch.device(device)
@@ -238,7 +243,12 @@ def get_workspace(nbytes: int, device):
         index = torch.cuda.current_device()
         device = torch.device("cuda", index)
     # (the device itself is the key, so that only GPUs are ever found: its type, a quarter of a microsecond to ask for, is looked at on a miss)
-    key = (device, None if index is None else _raw_stream(index))
+    stream = None if index is None else _raw_stream(index)
+    key = (device, stream)
+    if stream and torch.cuda.is_current_stream_capturing():        # (the default stream, 0, cannot be captured)
+        return _capture_workspace(int(nbytes), device, key)
+    if _capture_workspaces:
+        _capture_workspaces.clear()      # (their graphs keep the memory; one still being captured takes another tensor and clears that)
     ws = _workspaces.get(key)
     if ws is None or ws.numel() < nbytes:
         if device.type != "cuda":
@@ -247,6 +257,33 @@ def get_workspace(nbytes: int, device):
         ws = torch.zeros(max(int(nbytes), 256), dtype=torch.uint8, device=device)
         _workspaces[key] = ws
     return ws
+
+
+def _capture_workspace(nbytes, device, key):
+    """The workspace of a capture.  Work recorded while capturing runs at the replays only, in whatever order the program
+    replays its graphs, and the memory that a capture allocates belongs to the graph's pool: neither a header that
+    another graph cleared nor a tensor that eager calls replace by a larger one will do.  The capture's first call
+    allocates and records the clearing; its later calls find the tensor by the capture's id."""
+    torch = _torch()
+    if device.type != "cuda":
+        raise ValueError("a workspace is device memory, not %s" % device)
+    now = _capture_id(key[1])
+    held, ws = _capture_workspaces.get(key, (None, None))
+    if held != now or ws.numel() < nbytes:
+        _capture_workspaces.pop(key, None)
+        ws = torch.empty(max(nbytes, FHPC_WORKSPACE_HEADER_BYTES), dtype=torch.uint8, device=device)
+        ws[:FHPC_WORKSPACE_HEADER_BYTES].zero_()
+        _capture_workspaces[key] = (now, ws)
+    return ws
+
+
+def _capture_id(stream: int) -> int:
+    """Id of the capture that the stream takes part in, 0 for none."""
+    out = C.c_uint64(0)
+    rc = load_library().fhpc_capture_id(stream, C.byref(out))
+    if rc:
+        raise FhpcError(rc, "fhpc_capture_id")
+    return int(out.value)
 
 
 def _ws(op, M, K, r, N, dtype, qscheme, device, workspace):

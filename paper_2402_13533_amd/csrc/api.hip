@@ -2319,6 +2319,17 @@ int fhpc_gemm_bf16(const void* A, int64_t lda, int a_mode, const void* B, int64_
     return FHPC_OK;
 }
 
+int fhpc_capture_id(void* hip_stream, uint64_t* id)
+{
+    if (!id) return FHPC_ERR_NULL;
+    *id = 0;
+    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+    unsigned long long now = 0;
+    if (hipStreamGetCaptureInfo(static_cast<hipStream_t>(hip_stream), &status, &now) != hipSuccess) return FHPC_ERR_HIP;
+    if (status == hipStreamCaptureStatusActive) *id = now;
+    return FHPC_OK;
+}
+
 int fhpc_plan_slab_bytes(int call, int64_t M, int64_t K, int64_t r, int64_t N, int dtype, int qscheme, int g,
                          int outputs, float base_scale, int64_t* planned, int64_t* reserved)
 {

@@ -624,3 +624,36 @@ def test_small_tile_products(M, K, r, N):
     _check_all("small tiles %s" % ((M, K, r, N),), (Y,) + out, ref, TOL_BF16)
     guard.check("small tiles %s" % ((M, K, r, N),))
     assert all(torch.equal(a, b) for a, b in zip(fhpc.lowrank_linear_bwd(Xd, Ad, Bd, dYd, workspace=ws), out))
+
+
+def test_graphs_in_one_pool_replayed_in_any_order():
+    """Calls without a workspace, captured: each graph clears the arrival counters it uses, so that neither the order of the replays
+    nor what another graph of the pool left in the memory changes a result."""
+    import torch
+    fhpc = _fhpc()
+    def layer(i, M, K, r, N, t):
+        X, A, B, dY = (torch.from_numpy(a).to(t).cuda() for a in lowrank_inputs(i, M, K, r, N, bf16=False))
+        def step():
+            Y, H = fhpc.lowrank_linear_fwd(X, A, B, save_H=True)
+            return (Y, *fhpc.lowrank_linear_bwd(X, A, B, dY, H_saved=H))
+        return step
+    steps = [layer(1, 5, 4096, 64, 2048, torch.bfloat16), layer(2, 300, 2048, 64, 520, torch.float32), layer(3, 40, 2056, 96, 4104, torch.bfloat16)]
+    eager = [[t.clone() for t in s()] for s in steps]
+    torch.cuda.synchronize()
+    fill = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(fill):
+        for n in (1 << 14, 1 << 19, 1 << 21, 1 << 25):
+            torch.empty(n, dtype=torch.uint8, device="cuda").fill_(0xFF)        # freed: the other graphs' memory
+    graphs, outs = [], []
+    for s in steps:
+        graphs.append(torch.cuda.CUDAGraph())
+        with torch.cuda.graph(graphs[-1], pool=fill.pool()):
+            outs.append(s())
+    assert all(type(t) is torch.Tensor for t in fhpc._workspaces.values()) and len(fhpc._capture_workspaces) <= 1
+    for i in (2, 1, 0, 1, 2, 0):
+        fill.replay()
+        graphs[i].replay()
+        torch.cuda.synchronize()
+        assert all(torch.equal(a, b) for a, b in zip(outs[i], eager[i])), i
+        assert all(torch.equal(a, b) for a, b in zip(steps[0](), eager[0])), i      # eager work between the replays
+    assert not fhpc._capture_workspaces
