@@ -118,15 +118,12 @@ __device__ __forceinline__ f32x4 f32_frag(const float* tile, int x, int c, int h
     }
 }
 
-template <F32Layout AL, F32Layout BL, int T, int PD, bool VEC>
-__global__ __launch_bounds__(256) void gemm_f32_kernel(GemmF32Args args)
+template <F32Layout AL, F32Layout BL, int T> constexpr int f32_lds() { return 2 * (F32Tile<AL, T>::WORDS + F32Tile<BL, T>::WORDS); }
+
+template <F32Layout AL, F32Layout BL, int T, int PD, bool VEC_A, bool VEC_B>
+__device__ __forceinline__ void gemm_f32_body(const GemmF32Job& j, int item, float* lds)
 {
     constexpr int AW = F32Tile<AL, T>::WORDS, BW = F32Tile<BL, T>::WORDS;
-    __shared__ __attribute__((aligned(16))) float lds[2 * (AW + BW)];
-    const int id = ring::xcd_contiguous((int)blockIdx.x, (int)gridDim.x);
-    const int which = (id < args.job[0].items) ? 0 : 1;
-    const GemmF32Job& j = args.job[which];
-    const int item = id - (which ? args.job[0].items : 0);
     const int per_split = j.items / j.splits;
     const int split = item / per_split, t = item - split * per_split;
     const int m0 = t / j.tiles_n * T, n0 = t % j.tiles_n * T;
@@ -152,8 +149,8 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmF32Args args)
     };
 
     const int steps = (k_end - k_begin + F32_BK - 1) / F32_BK;
-    F32Feed<AL, T, VEC> feed_a;
-    F32Feed<BL, T, VEC> feed_b;
+    F32Feed<AL, T, VEC_A> feed_a;
+    F32Feed<BL, T, VEC_B> feed_b;
     feed_a.init(j.a, j.lda, m0, j.M, k_begin, k_end);
     feed_b.init(j.b, j.ldb, n0, j.N, k_begin, k_end);
 #pragma unroll
@@ -254,6 +251,25 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmF32Args args)
     }
 }
 
+// Which operands take 16-byte loads: bit 0 and 1 a and b of job 0, bit 2 and 3 of job 1.  An operand can where its rows start 16-byte
+// aligned and its contiguous extent is a multiple of four, so with other ranks X, dY and B still do.  768 -> 191 -> 3072 at 8192 tokens,
+// forward / backward in microseconds: every load by four bytes 193 / 300, this choice 157 / 246 (rank 192: 129 / 225).
+constexpr unsigned F32_VEC_A = 5, F32_VEC_B = 10;
+template <F32Layout AL, F32Layout BL, int T, int PD, unsigned VEC>
+__global__ __launch_bounds__(256) void gemm_f32_kernel(GemmF32Args args)
+{
+    __shared__ __attribute__((aligned(16))) float lds[f32_lds<AL, BL, T>()];
+    const int id = ring::xcd_contiguous((int)blockIdx.x, (int)gridDim.x);
+    const int which = (id < args.job[0].items) ? 0 : 1;
+    const int item = id - (which ? args.job[0].items : 0);
+    if constexpr ((VEC & 3) == VEC >> 2) {
+        gemm_f32_body<AL, BL, T, PD, (VEC & 1) != 0, (VEC & 2) != 0>(args.job[which], item, lds);
+    } else {
+        if (which == 0) gemm_f32_body<AL, BL, T, PD, (VEC & 1) != 0, (VEC & 2) != 0>(args.job[0], item, lds);
+        else gemm_f32_body<AL, BL, T, PD, (VEC & 4) != 0, (VEC & 8) != 0>(args.job[1], item, lds);
+    }
+}
+
 static int64_t f32_tiles(int64_t M, int64_t N, int64_t T) { return ((M + T - 1) / T) * ((N + T - 1) / T); }
 
 int64_t gemm_f32_part_bytes(const GemmF32Plan& p, int64_t M, int64_t N)
@@ -316,22 +332,31 @@ GemmF32Plan plan_gemm_f32(int jobs, const int64_t* M, const int64_t* N, const in
     return best;
 }
 
-template <F32Layout AL, F32Layout BL>
-static hipError_t launch_layout(const GemmF32Args& a, unsigned blocks, int tile, bool vec, hipStream_t s)
+template <F32Layout AL, F32Layout BL, unsigned VEC>
+static hipError_t launch_tile(const GemmF32Args& a, unsigned blocks, int tile, hipStream_t s)
 {
-    if (tile == 64 && vec) hipLaunchKernelGGL((gemm_f32_kernel<AL, BL, 64, 2, true>), dim3(blocks), dim3(256), 0, s, a);
-    else if (tile == 64) hipLaunchKernelGGL((gemm_f32_kernel<AL, BL, 64, 2, false>), dim3(blocks), dim3(256), 0, s, a);
-    else if (tile == 32 && vec) hipLaunchKernelGGL((gemm_f32_kernel<AL, BL, 32, 4, true>), dim3(blocks), dim3(256), 0, s, a);
-    else if (tile == 32) hipLaunchKernelGGL((gemm_f32_kernel<AL, BL, 32, 4, false>), dim3(blocks), dim3(256), 0, s, a);
+    if (tile == 64) hipLaunchKernelGGL((gemm_f32_kernel<AL, BL, 64, 2, VEC>), dim3(blocks), dim3(256), 0, s, a);
+    else if (tile == 32) hipLaunchKernelGGL((gemm_f32_kernel<AL, BL, 32, 4, VEC>), dim3(blocks), dim3(256), 0, s, a);
     else return hipErrorInvalidValue;
     return hipGetLastError();
+}
+
+template <F32Layout AL, F32Layout BL>
+static hipError_t launch_layout(const GemmF32Args& a, unsigned blocks, int tile, unsigned vec, hipStream_t s)
+{
+    // dA = X^T dH beside dB = H^T dY, at a rank that is not a multiple of four
+    if constexpr (AL == F32_XC && BL == F32_XC)
+        if (vec == ((F32_VEC_A & 3) | (F32_VEC_B & 12))) return launch_tile<AL, BL, (F32_VEC_A & 3) | (F32_VEC_B & 12)>(a, blocks, tile, s);
+    const bool va = (vec & F32_VEC_A) == F32_VEC_A, vb = (vec & F32_VEC_B) == F32_VEC_B;
+    if (va) return vb ? launch_tile<AL, BL, F32_VEC_A | F32_VEC_B>(a, blocks, tile, s) : launch_tile<AL, BL, F32_VEC_A>(a, blocks, tile, s);
+    return vb ? launch_tile<AL, BL, F32_VEC_B>(a, blocks, tile, s) : launch_tile<AL, BL, 0>(a, blocks, tile, s);
 }
 
 hipError_t launch_gemm_f32(F32Layout al, F32Layout bl, const GemmF32Job* jobs, int count, int tile, float* part, uint32_t* tickets, hipStream_t s)
 {
     if (count < 1 || count > 2) return hipErrorInvalidValue;
     GemmF32Args a = {};
-    bool all_vec = true;
+    unsigned vec_bits = 0;
     int64_t blocks = 0, counted = 0;
     for (int i = 0; i < count; i++) {
         GemmF32Job& j = a.job[i];
@@ -343,7 +368,8 @@ hipError_t launch_gemm_f32(F32Layout al, F32Layout bl, const GemmF32Job* jobs, i
             return ld % 4 == 0 && extent % 4 == 0 && reinterpret_cast<uintptr_t>(p) % 16 == 0;
         };
         // (a slice's end inside the reduction is a multiple of 32, so only its far end can cut a piece along k)
-        all_vec = all_vec && vec(j.a, j.lda, al == F32_KC ? j.K : j.M) && vec(j.b, j.ldb, bl == F32_KC ? j.K : j.N);
+        if (vec(j.a, j.lda, al == F32_KC ? j.K : j.M)) vec_bits |= F32_VEC_A & (count == 1 ? 15 : 3 << 2 * i);
+        if (vec(j.b, j.ldb, bl == F32_KC ? j.K : j.N)) vec_bits |= F32_VEC_B & (count == 1 ? 15 : 3 << 2 * i);
         j.tiles_n = (j.N + tile - 1) / tile;
         const int64_t tiles = f32_tiles(j.M, j.N, tile), items = tiles * j.splits;
         if (items > 0x3FFFFFFF) return hipErrorInvalidValue;
@@ -358,9 +384,9 @@ hipError_t launch_gemm_f32(F32Layout al, F32Layout bl, const GemmF32Job* jobs, i
         }
     }
     if (count == 1) a.job[1] = a.job[0];                     // (never reached: the grid ends with job 0)
-    if (al == F32_KC && bl == F32_XC) return launch_layout<F32_KC, F32_XC>(a, (unsigned)blocks, tile, all_vec, s);
-    if (al == F32_KC && bl == F32_KC) return launch_layout<F32_KC, F32_KC>(a, (unsigned)blocks, tile, all_vec, s);
-    if (al == F32_XC && bl == F32_XC) return launch_layout<F32_XC, F32_XC>(a, (unsigned)blocks, tile, all_vec, s);
+    if (al == F32_KC && bl == F32_XC) return launch_layout<F32_KC, F32_XC>(a, (unsigned)blocks, tile, vec_bits, s);
+    if (al == F32_KC && bl == F32_KC) return launch_layout<F32_KC, F32_KC>(a, (unsigned)blocks, tile, vec_bits, s);
+    if (al == F32_XC && bl == F32_XC) return launch_layout<F32_XC, F32_XC>(a, (unsigned)blocks, tile, vec_bits, s);
     return hipErrorInvalidValue;
 }
 

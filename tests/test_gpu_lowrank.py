@@ -657,3 +657,27 @@ def test_graphs_in_one_pool_replayed_in_any_order():
         assert all(torch.equal(a, b) for a, b in zip(outs[i], eager[i])), i
         assert all(torch.equal(a, b) for a, b in zip(steps[0](), eager[0])), i      # eager work between the replays
     assert not fhpc._capture_workspaces
+
+
+@pytest.mark.parametrize("M,K,r,N", [
+    (2050, 776, 131, 1032),   # 64 x 64 tiles; the last step of the reduction over the rank holds three
+    (70, 264, 45, 136),       # 32 x 32 tiles
+    (1000, 1600, 66, 2056),   # rows of the rank 8-byte aligned
+])
+def test_fp32_ranks_that_are_not_a_multiple_of_four(M, K, r, N):
+    """X, dY and B by 16 bytes beside A, H and dH by four, in every product alone and in the launch that carries both weight gradients."""
+    import torch
+    fhpc = _fhpc()
+    X, A, B, dY = lowrank_inputs(6, M, K, r, N, bf16=False)
+    Yr, Hr = oracle.lowrank_fwd(X, A, B)
+    Xd, Ad, Bd, dYd = (torch.from_numpy(a).cuda() for a in (X, A, B, dY))
+    guard = Guarded()
+    g = [guard.alloc(s, torch.float32) for s in ((M, N), (M, r), (M, K), (K, r), (r, N))]
+    Y, H = fhpc.lowrank_linear_fwd(Xd, Ad, Bd, Y=g[0], H_out=g[1])
+    out = fhpc.lowrank_linear_bwd(Xd, Ad, Bd, dYd, H_saved=H, dX=g[2], dA=g[3], dB=g[4])
+    _check_all("f32 rank %s" % ((M, K, r, N),), (Y,) + out, (Yr,) + oracle.lowrank_bwd(X, A, B, dY), TOL_F32)
+    assert parity_err(from_device(H), Hr, TOL_F32, "H") <= TOL_F32
+    guard.check("f32 rank %s" % ((M, K, r, N),))
+    for i in range(3):
+        only = fhpc.lowrank_linear_bwd(Xd, Ad, Bd, dYd, H_saved=H, need_dX=i == 0, need_dA=i == 1, need_dB=i == 2)
+        assert torch.equal(only[i], out[i])
