@@ -1416,6 +1416,8 @@ static inline void* bf16_col(const void* p, int64_t col)
 // three against two: 121 / 117 / 143 (5 x 13715 x 168 from 800), 151 / 150 / 155 (3 x 11893 x 400 from 800), 178 /
 // 184 / 208 (5 x 14572 x 144 from 1408), 208 / 224 / 213 (3 x 10795 x 416 from 1688), attention of 16384 x 512 from 4096 1677 / 1699.
 // Of 750 forward shapes of 2 .. 8 products at 2 .. 16384 tokens, g launches are ahead of this by more than the noise (5 %) on two.
+// Not grouped: outputs whose reduction is cut, or long enough to be (three 64 x 64 launches / grouped, forward at 16 tokens, 4096 -> r -> 4096: r = 64
+// 16.0 / 14.4).
 static int grouped_tile(int b_mode, int64_t M, int64_t Nout, int64_t Kred, int g)
 {
     const int64_t large = (tile_count(TILE_256x256, M, Nout) * g + num_cu() - 1) / num_cu();
@@ -1426,7 +1428,7 @@ static int grouped_tile(int b_mode, int64_t M, int64_t Nout, int64_t Kred, int g
 static bool groupable_bf16(int b_mode, int64_t M, int64_t Nout, int64_t ldp, int64_t Kred, int g)
 {
     if (g < 2 || g > GEMM_MAX_GROUPS) return false;
-    if (ldp == Nout && (large_split_pays(M, Nout, Kred) || (small_pays(M, Nout) && (M <= 32 || Kred > 512)) || short_split_pays(M, Nout, Kred))) return false;
+    if (ldp == Nout && (large_split_pays(M, Nout, Kred) || (small_pays(M, Nout) && Kred > 512) || short_split_pays(M, Nout, Kred))) return false;
     return gemm_pp_supports(OP_KC, b_mode, OP_NONE, OUT_BF16, grouped_tile(b_mode, M, Nout, Kred, g));
 }
 

@@ -681,3 +681,17 @@ def test_fp32_ranks_that_are_not_a_multiple_of_four(M, K, r, N):
     for i in range(3):
         only = fhpc.lowrank_linear_bwd(Xd, Ad, Bd, dYd, H_saved=H, need_dX=i == 0, need_dA=i == 1, need_dB=i == 2)
         assert torch.equal(only[i], out[i])
+
+
+@pytest.mark.parametrize("M,r", [(1, 8), (13, 64), (32, 40), (33, 64)])
+def test_shared_x_outputs_of_few_tokens_share_a_launch(M, r):
+    import torch
+    fhpc = _fhpc()
+    K, N, g = 520, 776, 3
+    X = Bf16.normal(71, (M, K)); A = [Bf16.normal(72 + i, (K, r), K ** -0.5) for i in range(g)]; B = [Bf16.normal(82 + i, (r, N), r ** -0.5) for i in range(g)]
+    args = (X.cuda(), torch.cat([a.cuda() for a in A], 1).contiguous(), [b.cuda() for b in B])
+    fhpc.profile_start(64)
+    Ys = fhpc.lowrank_linear_fwd_shared_x(*args)
+    assert sum(name.startswith("gemm") for name, *_ in fhpc.profile_stop()) == 2          # X A_all, and the outputs
+    for Y, a, b in zip(Ys, A, B):
+        assert parity_err(from_device(Y), oracle.lowrank_fwd(X.f64, a.f64, b.f64)[0], TOL_BF16, "Y") <= TOL_BF16
