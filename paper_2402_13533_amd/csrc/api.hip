@@ -191,7 +191,7 @@ SplitPlan plan_split_on(int tile, int64_t M, int64_t N, int64_t Kred, int g = 1)
 // A product on 64 x 64 tiles (left operand with the reduction contiguous: X A, H B, dY B^T, dH A^T), whole or in slices of four steps at
 // least.  A 64-deep step takes 0.32 microseconds where a compute unit has one workgroup and 0.265 per workgroup where it has
 // more (1024 x 512 from 4096 in 2 slices 12.8, 2048 x 512 in 2 19.3, 4096 x 512 whole 32.4), and slabs are written and read at 4 TB/s by a launch more.
-SplitPlan plan_small(int64_t M, int64_t N, int64_t Kred)
+SplitPlan plan_small(int64_t M, int64_t N, int64_t Kred, double* microseconds = nullptr)
 {
     const int64_t ksteps = (Kred + 63) / 64, tiles = tile_count(TILE_64x64, M, N), most = ksteps / 4 < 64 ? ksteps / 4 : 64, units = num_cu();
     double best = -1.0;
@@ -215,6 +215,7 @@ SplitPlan plan_small(int64_t M, int64_t N, int64_t Kred)
     sp.tile = TILE_64x64;
     sp.k_chunk = (int)(per * 64);
     sp.splits = (int)((ksteps + per - 1) / per);
+    if (microseconds) *microseconds = best;
     return sp;
 }
 
@@ -263,12 +264,8 @@ bool short_split_pays(int64_t M, int64_t Nout, int64_t Kred)
     return plan_split(M, Nout, Kred, true).splits > 1;
 }
 
-// From 256 tokens on, an output that gives at most a quarter of the compute units a 256 x 128 tile, with a
-// reduction beyond 6144 (4096 x 512 from 4096 32.4 microseconds on 64 x 64 tiles, 38.0 on these; per step of the reduction 0.47 against 0.35), takes the large request-fed tiles for its slices instead (slices of at least
-// 512): one factorised layer 4096 -> 512 -> 4096 at 2048 tokens, forward 55 -> 43 microseconds and backward
-// 107 -> 96 against the 32-row tiles; at 4096 tokens, where X A is 64 tiles in 4 slices, 69 -> 56 and
-// 136 -> 125 against 128 unsplit tiles of 128 x 128.  At 8192 tokens (128 tiles) the slices and their slab
-// sum take longer than the small tiles do: 54 + 8 against 57 microseconds.
+// From 256 tokens on, an output that gives at most a quarter of the compute units a 256 x 128 tile can take the large request-fed tiles
+// for slices of at least 512 of a long reduction.
 SplitPlan plan_large_split(int64_t M, int64_t Nout, int64_t Kred)
 {
     SplitPlan sp = plan_split(M, Nout, Kred);
@@ -283,13 +280,22 @@ SplitPlan plan_large_split(int64_t M, int64_t Nout, int64_t Kred)
     return sp;
 }
 
+// They pay where they should take less time than 64 x 64 tiles.  A step of a 256 x 256 tile takes 1.5 microseconds and one of a 256 x 128 tile
+// 1.0, a round 4.5 beside its steps (ramp, slab sum's launch), and slabs are written and read at 6.2 TB/s (fitted to 172 products).  Factorised layer's forward in
+// microseconds, on these / on 64 x 64 tiles: 3500 tokens 4096 -> 256 56.3 / 53.7, 5120 -> 384 41.0 / 46.9, 6144 -> 512 54.2 / 61.4, 11008 -> 512 90 / 130;
+// 2000 tokens 4096 -> 512 44.6 / 41.3, 6144 -> 512 38.8 / 41.9; 1000 tokens 6144 -> 512 30.5 / 28.6, 8192 -> 512 39.4 / 38.3, 13824 -> 1024 61 / 80.
+// Below a reduction of 3584 none was ahead.
 bool large_split_pays(int64_t M, int64_t Nout, int64_t Kred)
 {
-    if (M < 256 || Nout <= 128 || Kred <= 6144) return false;
-    if (4 * tile_count(TILE_256x128, M, Nout) > num_cu()) return false;
+    const int64_t units = num_cu();
+    if (M < 256 || Nout <= 128 || Kred < 3584 || 4 * tile_count(TILE_256x128, M, Nout) > units) return false;
     const SplitPlan sp = plan_large_split(M, Nout, Kred);
-    // (with fewer workgroups than half the compute units the 32-row tiles do better)
-    return sp.splits > 1 && 2 * sp.splits * tile_count(sp.tile, M, Nout) >= num_cu();
+    const int64_t groups = sp.splits * tile_count(sp.tile, M, Nout);
+    if (sp.splits < 2 || 2 * groups < units) return false;
+    double small;
+    plan_small(M, Nout, Kred, &small);
+    const double round = sp.k_chunk / 64 * (sp.tile == TILE_256x256 ? 1.5 : 1.0) + 4.5;
+    return (double)((groups + units - 1) / units) * round + (double)sp.splits * (double)(M * Nout) * 8.0 / 6.2e6 < small;
 }
 
 int64_t product_part_bytes(int64_t M, int64_t Nout, int64_t Kred)
@@ -345,7 +351,7 @@ SplitPlan plan_fused_large(int64_t M, int64_t Nout, int64_t Kred)
 // at 100 28.0 / 25.3, 5120 x 4096 at 250 38.4 / 33.7, 2048 x 2048 at 200 23.0 / 20.4, 4-bit 2816 x 5120 at 150 33.6 / 30.1; dense (blend)
 // 3072 x 4096 at 256 32.5 / 28.7; but 4-bit 11008 x 4096 at 65 39.6 / 44.5, 8-bit 11008 x 4096 at 500 74.9 / 87, 8-bit 5120 x 5120 at 65
 // 27.0 / 30.0, 3264 x 4736 at 75 28.4 / 31.2, dense 4096 x 4096 at 65 23.0 / 25.2, 2816 x 4672 at 73 25.6 / 30.3, 3840 x 5120 at 205 37.4 / 41.0, 1088 x 4352 at 216 (272
-// workgroups) 23.8 / 25.9.  Of 540 products drawn from 65 .. 384 x 1024 .. 5120 x 1024 .. 5120 the choice is at most 4 % behind 128 rows.
+// workgroups) 23.8 / 25.9.  Of 540 products drawn from 65 .. 384 x 1024 .. 5120 x 1024 .. 5120 the choice is at most 5 % behind 128 rows.
 SplitPlan plan_fused_split(int64_t M, int64_t Nout, int64_t Kred)
 {
     const int64_t units = num_cu(), rows = (M + 63) / 64, tiles = tile_count(TILE_64x128, M, Nout), ksteps = (Kred + 63) / 64;

@@ -128,3 +128,10 @@ def test_rows_of_dequantising_tiles(M, K, N, slices):
     """The slices of the dequantising product tell its tile (what either takes stands at the rule)."""
     for scheme in (fhpc.FHPC_Q_INT8_PER_CHANNEL, fhpc.FHPC_W_BF16):
         assert _assert_fits(fhpc.FHPC_OP_QLINEAR_FWD, "qlinear_fwd", M=M, K=K, r=16, N=N, qscheme=scheme) == slices * M * N * 4
+
+
+@pytest.mark.parametrize("M,K,r,sliced", [(3500, 6144, 512, True), (3500, 5120, 384, True), (2000, 6144, 512, True), (1645, 4040, 648, True),
+                                          (2600, 3584, 384, False), (2000, 4096, 512, False), (1000, 4096, 1000, False)])
+def test_slices_of_long_reductions(M, K, r, sliced):
+    """H = X A where 64 x 64 tiles fill the chip by themselves: whole on those, or on large tiles in slices (what either takes stands at the rule)."""
+    assert (_assert_fits(fhpc.FHPC_OP_LOWRANK_FWD, "forward", M=M, K=K, r=r, N=1600, outputs=1) > 0) == sliced
