@@ -80,7 +80,6 @@ struct Scratch {
     void* B_p = nullptr;    // bf16 [rp][N]
     void* H = nullptr;      // bf16 [M][rp]
     void* dH = nullptr;     // bf16 [M][rp]
-    float* Hf = nullptr;    // fp32 [M][rp]   split-K accumulator for the rank-r products
     float* dA_t = nullptr;  // fp32 [K][rp]
     float* dB_t = nullptr;  // fp32 [rp][N]
     float* part = nullptr;  // fp32 partial sums of a split reduction, one slab per split
@@ -253,10 +252,10 @@ bool small_pays(int64_t M, int64_t Nout)
     return Nout > 32 && (M <= 32 || 2 * tile_count(TILE_128x128, M, Nout) <= num_cu());
 }
 
-// Few outputs of a reduction of at most 512, eight steps, go out in slices on 32-row tiles; larger outputs lose more to the slab
-// sum than the slices save (forward, microseconds, slices / whole on 128 x 128 tiles: 4096 -> 512 -> 4096 at 64 / 300 tokens 24 / 21, 31 / 24,
-// 2048 -> 256 -> 2048 at 600 26 / 19; but X A at 695 tokens, 416 -> 48, 17 / 19, at 386, 504 -> 112, 18 / 19).  The two are even at 32 K
-// outputs, 128 K on narrow ones, and half as much again beyond 384.
+// Few outputs of a reduction of at most 512, eight steps, go out in slices on 32-row tiles; the line was drawn against 128 x 128 tiles,
+// where the two are even at 32 K outputs, 128 K on narrow ones, and half as much again beyond 384.  Against 64 x 64 tiles, which
+// would take these outputs whole, the slices are behind (layer's forward in microseconds, slices / whole: 300 tokens 512 -> 64 -> 512
+// 10.5 / 8.7, 900 tokens 400 -> 128 -> 400 12.7 / 8.9, q, k and v of 512 -> 96 -> 512 at 16 tokens 25.4 / 14.1); test_plan_cpu.py pins them.
 bool short_split_pays(int64_t M, int64_t Nout, int64_t Kred)
 {
     if (Kred > 512 || !small_pays(M, Nout)) return false;
@@ -531,7 +530,6 @@ Scratch carve(Carver& c, int op, int64_t M, int64_t K, int64_t r, int64_t N, int
     }
     s.H = c.take(M * rp * 2);
     if (bwd) s.dH = c.take(M * rp * 2);
-    if (rp <= 32) s.Hf = static_cast<float*>(c.take(M * rp * 4));
     if (bwd && rp != r) {
         s.dA_t = static_cast<float*>(c.take(K * rp * 4));
         s.dB_t = static_cast<float*>(c.take(rp * N * 4));
@@ -769,8 +767,8 @@ static hipError_t gemm_gated(int b_mode, GemmOperand a, GemmOperand b, void* P, 
 static bool tall_skinny_pays(int64_t M) { return M >= 8 * (int64_t)num_cu(); }
 
 // Rank-r product P[M][rp] (bf16) = L * R where the output is only rp <= 32 wide:
-// 64 x 64 tiles, most of their columns outside, in slices of the long reduction; summed in fp32, rounded once to bf16.
-hipError_t rank_product(int b_mode, GemmOperand a, GemmOperand b, void* P, int64_t rp, float* Pf, float* part,
+// 64 x 64 tiles, most of their columns outside, whole or in slices of the long reduction; summed in fp32, rounded once to bf16.
+hipError_t rank_product(int b_mode, GemmOperand a, GemmOperand b, void* P, int64_t rp, float* part,
                         int64_t M, int64_t Kred, Run& run)
 {
     if (rp <= 32 && b_mode == OP_KC && (Kred % 32) == 0 && tall_skinny_pays(M)) {
@@ -779,12 +777,10 @@ hipError_t rank_product(int b_mode, GemmOperand a, GemmOperand b, void* P, int64
         return launch_tall_skinny_kc(a.ptr, a.ld, b.ptr, b.ld, P, M, rp, Kred, run.st);
     }
     if (rp <= 32) {
-        bool done = false;
         const SplitPlan sp = plan_small(M, rp, Kred);
         if (sp.splits == 1) return gemm_plain(OP_KC, b_mode, a, b, P, rp, M, rp, Kred, run, 1.f, TILE_64x64);
-        hipError_t e = gemm_split_f32(OP_KC, b_mode, a, b, Pf, rp, M, rp, Kred, 1.f, part, run, P, &done, &sp);
-        if (e != hipSuccess || done || run.dry) return e;
-        return launch_compact_f32(Pf, rp, P, rp, M, rp, 1.f, true, run.st);
+        bool done = false;      // (with more than one slice the slab sum writes P)
+        return gemm_split_f32(OP_KC, b_mode, a, b, nullptr, rp, M, rp, Kred, 1.f, part, run, P, &done, &sp);
     }
     return product_bf16(b_mode, a, b, P, rp, rp, M, Kred, part, run);
 }
@@ -1206,7 +1202,7 @@ int seq_lowrank_fwd(Run& run, const Scratch& s, const void* X, const void* A, co
     int rc = prepare_factors(A, B, K, r, rp, N, s, run, &f);
     if (rc) return rc;
     void* H = (H_out && rp == r) ? H_out : s.H;
-    FHPC_HIP(rank_product(OP_XC, operand(X, K), operand(f.A, rp), H, rp, s.Hf, s.part, M, K, run));
+    FHPC_HIP(rank_product(OP_XC, operand(X, K), operand(f.A, rp), H, rp, s.part, M, K, run));
     FHPC_HIP(product_bf16(OP_XC, operand(H, rp), operand(f.B, N), Y, N, N, M, rp, s.part, run));
     if (H_out && rp != r) FHPC_LAUNCH(run, launch_pad2d_u16(H, rp, M, r, H_out, r, M, run.st));
     return FHPC_OK;
@@ -1247,12 +1243,12 @@ int seq_lowrank_bwd(Run& run, const Scratch& s, const void* X, const void* A, co
             FHPC_LAUNCH(run, launch_pad2d_u16(H_saved, r, M, r, s.H, rp, M, run.st));
             H = s.H;
         } else {
-            FHPC_HIP(rank_product(OP_XC, operand(X, K), operand(f.A, rp), s.H, rp, s.Hf, s.part, M, K, run));
+            FHPC_HIP(rank_product(OP_XC, operand(X, K), operand(f.A, rp), s.H, rp, s.part, M, K, run));
             H = s.H;
         }
     }
     if (dX || dA)
-        FHPC_HIP(rank_product(OP_KC, operand(dY, N), operand(f.B, N), s.dH, rp, s.Hf, s.part, M, N, run));
+        FHPC_HIP(rank_product(OP_KC, operand(dY, N), operand(f.B, N), s.dH, rp, s.part, M, N, run));
     const JointPlan joint = token_outer_pays(M, K, rp, N) ? JointPlan() : plan_joint(M, K, rp, N, 1);
     if (dX && !joint.with_dx)
         FHPC_HIP(product_bf16(OP_KC, operand(s.dH, rp), operand(f.A, rp), dX, K, K, M, rp, s.part, run));
@@ -1357,7 +1353,7 @@ static SharedScratch carve_shared(Carver& c, bool bwd, int64_t M, int64_t K, int
     if (bwd) {
         upto(product_part_bytes(M, K, R));             // dX = dH_all A_all^T
         // dH_i = dY_i B_i^T: at most 32 wide it splits its reduction; wider, it is a column block of dH_all and
-        // runs unsplit, except for g = 1, where the block is the whole (dense) matrix and may take the 32-row split
+        // runs unsplit, except for g = 1, where the block is the whole (dense) matrix and may be cut into slices
         if (r <= 32) upto(slab_bytes(plan_small(M, r, N), M, r));
         else if (g == 1) upto(product_part_bytes(M, r, N));
         if (g > 1) upto(grouped_dh_bytes(M, r, N, g));  // dH_i in one launch in slices
@@ -1693,11 +1689,11 @@ static int seq_ffn_down_bwd(Run& run, const Scratch& s, const void* Z, const voi
             FHPC_LAUNCH(run, launch_pad2d_u16(H_saved, r, M, r, s.H, rp, M, run.st));
             H = s.H;
         } else {
-            FHPC_HIP(rank_product(OP_XC, operand(Z, K), operand(f.A, rp), s.H, rp, s.Hf, s.part, M, K, run));
+            FHPC_HIP(rank_product(OP_XC, operand(Z, K), operand(f.A, rp), s.H, rp, s.part, M, K, run));
             H = s.H;
         }
     }
-    FHPC_HIP(rank_product(OP_KC, operand(dY, N), operand(f.B, N), s.dH, rp, s.Hf, s.part, M, N, run));
+    FHPC_HIP(rank_product(OP_KC, operand(dY, N), operand(f.B, N), s.dH, rp, s.part, M, N, run));
     // (by the same rule as lowrank_linear_bwd, dX there being dZ here: the same bits)
     const JointPlan joint = token_outer_pays(M, K, rp, N) ? JointPlan() : plan_joint(M, K, rp, N, 1);
     const bool gated = !joint.with_dx && gate_rides(M, K, rp);
@@ -1804,12 +1800,12 @@ static int seq_qlinear_fwd(Run& run, const Scratch& s, const void* X, const void
         }
         FHPC_HIP(gemm_plain(OP_KC, OP_XC, operand(X, K), operand(Wm, N), Y, N, M, N, K, run));
         if (H_out) {
-            FHPC_HIP(rank_product(OP_XC, operand(X, K), operand(f.A, rp), H, rp, s.Hf, s.part, M, K, run));
+            FHPC_HIP(rank_product(OP_XC, operand(X, K), operand(f.A, rp), H, rp, s.part, M, K, run));
             if (rp != r) FHPC_LAUNCH(run, launch_pad2d_u16(H, rp, M, r, H_out, r, M, run.st));
         }
         return FHPC_OK;
     }
-    FHPC_HIP(rank_product(OP_XC, operand(X, K), operand(f.A, rp), H, rp, s.Hf, s.part, M, K, run));
+    FHPC_HIP(rank_product(OP_XC, operand(X, K), operand(f.A, rp), H, rp, s.part, M, K, run));
 
     if (base_scale == 0.f) {
         // nothing of the frozen weight is left: the factorised layer alone
@@ -2024,7 +2020,7 @@ static int seq_qlinear_bwd(Run& run, const Scratch& s, const void* X, const void
             FHPC_LAUNCH(run, launch_pad2d_u16(H_saved, r, M, r, s.H, rp, M, run.st));
             H = s.H;
         } else {
-            FHPC_HIP(rank_product(OP_XC, operand(X, K), operand(f.A, rp), s.H, rp, s.Hf, s.part, M, K, run));
+            FHPC_HIP(rank_product(OP_XC, operand(X, K), operand(f.A, rp), s.H, rp, s.part, M, K, run));
             H = s.H;
         }
     }
@@ -2034,7 +2030,7 @@ static int seq_qlinear_bwd(Run& run, const Scratch& s, const void* X, const void
     // (many tokens: dH = dY B^T can come out of the dX product itself, B standing in rp extra rows of the merged weight)
     const bool dh_rides = dX && merged_dx && !premerged && dA && rides_along(OP_KC, OP_KC, M, K, rp);
     if (!dh_on_the_way && !dh_rides && (dA || (dX && !merged_dx)))
-        FHPC_HIP(rank_product(OP_KC, operand(dY, N), operand(f.B, N), s.dH, rp, s.Hf, s.part, M, N, run));
+        FHPC_HIP(rank_product(OP_KC, operand(dY, N), operand(f.B, N), s.dH, rp, s.part, M, N, run));
     if (dX && base_scale == 0.f) {
         FHPC_HIP(gemm_plain(OP_KC, OP_KC, operand(s.dH, rp), operand(f.A, rp), dX, K, M, K, rp, run, scaling));
     } else if (dX && merged_dx) {

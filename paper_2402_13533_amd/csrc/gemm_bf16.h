@@ -36,7 +36,7 @@ enum : int {
     TILE_256x128 = 2,  // 4 x 2 waves of 64 x 64, ping-pong schedule
     TILE_128x128 = 3,  // 2 x 2 waves of 64 x 64
     TILE_256x32 = 4,   // 4 x 1 waves of 64 x 32   (outputs at most 32 wide over tokens: dA)
-    TILE_32x256 = 5,   // 1 x 4 waves of 32 x 64   (dB)
+    TILE_32x256 = 5,   // 1 x 4 waves of 32 x 64   (dB at a rank up to 32; few outputs of a short reduction)
     TILE_64x64 = 6,    // 2 x 2 waves of 32 x 32   (KC x KC and KC x XC outputs with few large tiles)
     TILE_64x128 = 7,   // 2 x 2 waves of 32 x 64   (products with a rank-r phase, a few hundred rows, fp32 slabs)
     TILE_COUNT = 8

@@ -876,10 +876,10 @@ hipError_t launch_gemm_bf16(int a_mode, int b_mode, int b2_mode, int out_mode, i
     FHPC_CASE(OP_KC, OP_Q4_XC, OP_KC, OUT_F32)
     FHPC_CASE(OP_KC, OP_XC, OP_XC, OUT_F32)
     FHPC_CASE(OP_KC, OP_KC, OP_KC, OUT_F32)
-    // rank-r (skinny) products of the finetuning layer
-    FHPC_SKINNY(OP_KC, OP_XC, OUT_F32)                  // H  = X A      (split over K)
-    FHPC_SKINNY(OP_KC, OP_KC, OUT_F32)                  // dH = dY B^T   (split over N)
-    FHPC_SKINNY(OP_XC, OP_XC, OUT_F32)                  // dA, dB        (split over tokens)
+    // skinny tiles: few outputs of a reduction up to 512 in slices (32 x 256; 256 x 32 with these layouts serves fhpc_gemm_bf16 only)
+    FHPC_SKINNY(OP_KC, OP_XC, OUT_F32)                  // H  = X A, Y = H B
+    FHPC_SKINNY(OP_KC, OP_KC, OUT_F32)                  // dH = dY B^T, dX = dH A^T
+    FHPC_SKINNY(OP_XC, OP_XC, OUT_F32)                  // dA, dB at a rank up to 32 (split over tokens)
 #undef FHPC_CASE
 #undef FHPC_SKINNY
     return hipErrorInvalidValue;
