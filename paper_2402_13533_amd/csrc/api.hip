@@ -84,6 +84,7 @@ struct Scratch {
     float* dB_t = nullptr;  // fp32 [rp][N]
     float* part = nullptr;  // fp32 partial sums of a split reduction, one slab per split
     int64_t part_bytes = 0; // what is reserved behind `part`
+    int64_t rank_room = (int64_t)1 << 62;   // what the slabs of H = X A may take of it
     void* Wm = nullptr;     // bf16 [K][N]    base_scale * deq(W) + scaling * A B, many tokens (see many_tokens)
     float* sk_part = nullptr;   // weight-streaming forward (few tokens): slabs of M x N
     float* sk_hpart = nullptr;  //                                        partial sums of X A
@@ -190,9 +191,13 @@ SplitPlan plan_split_on(int tile, int64_t M, int64_t N, int64_t Kred, int g = 1)
 // A product on 64 x 64 tiles (left operand with the reduction contiguous: X A, H B, dY B^T, dH A^T), whole or in slices of four steps at
 // least.  A 64-deep step takes 0.32 microseconds where a compute unit has one workgroup and 0.265 per workgroup where it has
 // more (1024 x 512 from 4096 in 2 slices 12.8, 2048 x 512 in 2 19.3, 4096 x 512 whole 32.4), and slabs are written and read at 4 TB/s by a launch more.
-SplitPlan plan_small(int64_t M, int64_t N, int64_t Kred, double* microseconds = nullptr)
+// `room`: bytes the slabs may take.
+constexpr int64_t ROOM_ANY = (int64_t)1 << 62;
+SplitPlan plan_small(int64_t M, int64_t N, int64_t Kred, int64_t room = ROOM_ANY, double* microseconds = nullptr)
 {
-    const int64_t ksteps = (Kred + 63) / 64, tiles = tile_count(TILE_64x64, M, N), most = ksteps / 4 < 64 ? ksteps / 4 : 64, units = num_cu();
+    const int64_t ksteps = (Kred + 63) / 64, tiles = tile_count(TILE_64x64, M, N), units = num_cu(), fit = room / (M * N * 4);
+    int64_t most = ksteps / 4 < 64 ? ksteps / 4 : 64;
+    if (most > fit) most = fit;
     double best = -1.0;
     int64_t per = ksteps;
     // whole, or as many slices as make full rounds of one to four workgroups per compute unit
@@ -292,16 +297,21 @@ bool large_split_pays(int64_t M, int64_t Nout, int64_t Kred)
     const int64_t groups = sp.splits * tile_count(sp.tile, M, Nout);
     if (sp.splits < 2 || 2 * groups < units) return false;
     double small;
-    plan_small(M, Nout, Kred, &small);
+    plan_small(M, Nout, Kred, ROOM_ANY, &small);
     const double round = sp.k_chunk / 64 * (sp.tile == TILE_256x256 ? 1.5 : 1.0) + 4.5;
     return (double)((groups + units - 1) / units) * round + (double)sp.splits * (double)(M * Nout) * 8.0 / 6.2e6 < small;
 }
 
-int64_t product_part_bytes(int64_t M, int64_t Nout, int64_t Kred)
+int64_t product_part_bytes(int64_t M, int64_t Nout, int64_t Kred, int64_t room = ROOM_ANY)
 {
     if (large_split_pays(M, Nout, Kred)) return (int64_t)plan_large_split(M, Nout, Kred).splits * M * Nout * 4;
     if (short_split_pays(M, Nout, Kred)) return slab_bytes(plan_split(M, Nout, Kred, true), M, Nout);
-    return small_pays(M, Nout) ? slab_bytes(plan_small(M, Nout, Kred), M, Nout) : 0;
+    return small_pays(M, Nout) ? slab_bytes(plan_small(M, Nout, Kred, room), M, Nout) : 0;
+}
+// a rank product (rank_product)
+int64_t rank_part_bytes(int64_t M, int64_t rp, int64_t Kred, int64_t room = ROOM_ANY)
+{
+    return rp <= 32 ? slab_bytes(plan_small(M, rp, Kred, room), M, rp) : product_part_bytes(M, rp, Kred, room);
 }
 
 // The products of the finetuning and blend layers that dequantise the frozen weight in their load path
@@ -548,13 +558,12 @@ Scratch carve(Carver& c, int op, int64_t M, int64_t K, int64_t r, int64_t N, int
     // split reductions of this entry point run one after another and share the slabs
     int64_t part = 0;
     auto upto = [&part](int64_t b) { if (b > part) part = b; };
-    if (rp <= 32) {
-        upto(slab_bytes(plan_small(M, rp, K), M, rp));               // H  = X A
-        if (bwd) upto(slab_bytes(plan_small(M, rp, N), M, rp));      // dH = dY B^T
-    } else {
-        upto(product_part_bytes(M, rp, K));
-        if (bwd) upto(product_part_bytes(M, rp, N));
-    }
+    // The quantised forward at sizes that the library's fixed array (qlinear_lowrank_fwd_noalloc) just holds: the slabs of H = X A take what
+    // is left of it.  The plan is the same with a workspace, so that both calls have the same bits.
+    const int64_t left = FHPC_NOALLOC_SCRATCH_BYTES - (int64_t)c.used;
+    if (op == FHPC_OP_QLINEAR_FWD && left >= 0 && rank_part_bytes(M, rp, K) > left) s.rank_room = left;
+    upto(rank_part_bytes(M, rp, K, s.rank_room));                    // H  = X A
+    if (bwd) upto(rank_part_bytes(M, rp, N));                        // dH = dY B^T
     if (op == FHPC_OP_QLINEAR_FWD) upto(fused_part_bytes(M, N, K));        // Y  = X deq(W) + s H B
     if (op == FHPC_OP_QLINEAR_BWD) upto(fused_part_bytes(M, K, N));        // dX = dY deq(W)^T + s dH A^T
     if (op == FHPC_OP_LOWRANK_FWD) upto(product_part_bytes(M, N, rp));     // Y  = H B
@@ -722,7 +731,7 @@ hipError_t gemm_split_f32(int a_mode, int b_mode, GemmOperand a, GemmOperand b, 
 // P[M][Nout] (bf16, row stride ldp) = L * R, L with k contiguous: the plain launch, the split reduction on large tiles (large_split_pays),
 // or 64 x 64 tiles (small_pays), whole or, where P is dense, in slices (32-row ones: short_split_pays).
 hipError_t product_bf16(int b_mode, GemmOperand a, GemmOperand b, void* P, int64_t ldp, int64_t Nout,
-                        int64_t M, int64_t Kred, float* part, Run& run)
+                        int64_t M, int64_t Kred, float* part, Run& run, int64_t room = ROOM_ANY)
 {
     const bool small = small_pays(M, Nout);
     if (ldp == Nout) {
@@ -730,7 +739,7 @@ hipError_t product_bf16(int b_mode, GemmOperand a, GemmOperand b, void* P, int64
         sp.splits = 1;
         if (large_split_pays(M, Nout, Kred)) sp = plan_large_split(M, Nout, Kred);
         else if (short_split_pays(M, Nout, Kred)) sp = plan_split(M, Nout, Kred, true);
-        else if (small) sp = plan_small(M, Nout, Kred);
+        else if (small) sp = plan_small(M, Nout, Kred, room);
         bool done = false;
         // (with more than one slice the slab sum writes P and no fp32 output is touched)
         if (sp.splits > 1) return gemm_split_f32(OP_KC, b_mode, a, b, nullptr, Nout, M, Nout, Kred, 1.f, part, run, P, &done, &sp);
@@ -769,7 +778,7 @@ static bool tall_skinny_pays(int64_t M) { return M >= 8 * (int64_t)num_cu(); }
 // Rank-r product P[M][rp] (bf16) = L * R where the output is only rp <= 32 wide:
 // 64 x 64 tiles, most of their columns outside, whole or in slices of the long reduction; summed in fp32, rounded once to bf16.
 hipError_t rank_product(int b_mode, GemmOperand a, GemmOperand b, void* P, int64_t rp, float* part,
-                        int64_t M, int64_t Kred, Run& run)
+                        int64_t M, int64_t Kred, Run& run, int64_t room = ROOM_ANY)
 {
     if (rp <= 32 && b_mode == OP_KC && (Kred % 32) == 0 && tall_skinny_pays(M)) {
         // many rows, both operands with the reduction contiguous (dH = dY B^T): one launch that owns the whole reduction
@@ -777,12 +786,12 @@ hipError_t rank_product(int b_mode, GemmOperand a, GemmOperand b, void* P, int64
         return launch_tall_skinny_kc(a.ptr, a.ld, b.ptr, b.ld, P, M, rp, Kred, run.st);
     }
     if (rp <= 32) {
-        const SplitPlan sp = plan_small(M, rp, Kred);
+        const SplitPlan sp = plan_small(M, rp, Kred, room);
         if (sp.splits == 1) return gemm_plain(OP_KC, b_mode, a, b, P, rp, M, rp, Kred, run, 1.f, TILE_64x64);
         bool done = false;      // (with more than one slice the slab sum writes P)
         return gemm_split_f32(OP_KC, b_mode, a, b, nullptr, rp, M, rp, Kred, 1.f, part, run, P, &done, &sp);
     }
-    return product_bf16(b_mode, a, b, P, rp, rp, M, Kred, part, run);
+    return product_bf16(b_mode, a, b, P, rp, rp, M, Kred, part, run, room);
 }
 
 // C[M][Nout] (bf16, dense) = g.alpha * (g.mid_scale * A2 B2 + A deq(B)): whole, or split over the reduction
@@ -1800,12 +1809,12 @@ static int seq_qlinear_fwd(Run& run, const Scratch& s, const void* X, const void
         }
         FHPC_HIP(gemm_plain(OP_KC, OP_XC, operand(X, K), operand(Wm, N), Y, N, M, N, K, run));
         if (H_out) {
-            FHPC_HIP(rank_product(OP_XC, operand(X, K), operand(f.A, rp), H, rp, s.part, M, K, run));
+            FHPC_HIP(rank_product(OP_XC, operand(X, K), operand(f.A, rp), H, rp, s.part, M, K, run, s.rank_room));
             if (rp != r) FHPC_LAUNCH(run, launch_pad2d_u16(H, rp, M, r, H_out, r, M, run.st));
         }
         return FHPC_OK;
     }
-    FHPC_HIP(rank_product(OP_XC, operand(X, K), operand(f.A, rp), H, rp, s.part, M, K, run));
+    FHPC_HIP(rank_product(OP_XC, operand(X, K), operand(f.A, rp), H, rp, s.part, M, K, run, s.rank_room));
 
     if (base_scale == 0.f) {
         // nothing of the frozen weight is left: the factorised layer alone

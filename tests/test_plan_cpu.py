@@ -135,3 +135,11 @@ def test_rows_of_dequantising_tiles(M, K, N, slices):
 def test_slices_of_long_reductions(M, K, r, sliced):
     """H = X A where 64 x 64 tiles fill the chip by themselves: whole on those, or on large tiles in slices (what either takes stands at the rule)."""
     assert (_assert_fits(fhpc.FHPC_OP_LOWRANK_FWD, "forward", M=M, K=K, r=r, N=1600, outputs=1) > 0) == sliced
+
+
+@pytest.mark.parametrize("M,K,r,N,scheme", [(2895, 1280, 64, 4808, 4), (1241, 20544, 128, 88, 8), (2751, 44544, 40, 8, 8), (1577, 21504, 128, 64, 8), (1770, 50560, 64, 8, 4), (1028, 45312, 64, 16, 4)])
+def test_slabs_of_the_rank_product_fit_the_fixed_scratch(M, K, r, N, scheme):
+    """Sizes whose other regions leave a part of the no-allocation entry point's array: the slabs of X A stay within it."""
+    assert fhpc.workspace_bytes(fhpc.FHPC_OP_QLINEAR_FWD, M, K, r, N, fhpc.FHPC_BF16, scheme) <= fhpc.FHPC_NOALLOC_SCRATCH_BYTES
+    for outputs in (0, 1):
+        _assert_fits(fhpc.FHPC_OP_QLINEAR_FWD, "qlinear_fwd", M=M, K=K, r=r, N=N, qscheme=scheme, outputs=outputs)

@@ -58,3 +58,14 @@ def test_sizes_beyond_the_fixed_scratch_are_refused():
     assert e.value.status == 5
     torch.cuda.synchronize()
     assert bool((Y == 7.0).all())               # nothing was launched
+
+
+def test_rank_product_that_takes_what_the_fixed_scratch_has_left():
+    import torch
+    import paper_2402_13533_amd as fhpc
+    M, K, r, N, scheme = 1028, 45312, 64, 16, 4          # the merged weight's rows leave room for fewer slabs of X A than its plan would take
+    args, Y_ref, H_ref = _case(fhpc, scheme, M, K, r, N, 70)
+    Y = torch.full((M, N), 7.0, dtype=torch.bfloat16, device="cuda")
+    H = torch.full((M, r), 7.0, dtype=torch.bfloat16, device="cuda")
+    fhpc.qlinear_lowrank_fwd_noalloc(*args, Y, H)
+    assert torch.equal(Y, Y_ref) and torch.equal(H, H_ref)
