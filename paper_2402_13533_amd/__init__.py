@@ -196,15 +196,31 @@ def _ptr(t):
 # numbers (ctypes converts them by the declared argument types) and to torch calls that build no Python objects: a
 # forward and backward pair of the 8-bit layer took 47 microseconds of host time otherwise, 33 this way.
 
+_raw = None      # (current device, its current stream's integer handle, is that stream being captured) as torch's own functions
+
+
+def _bind():
+    global _raw
+    torch = _torch()
+    c = torch._C
+    _raw = (getattr(c, "_cuda_getDevice", torch.cuda.current_device),
+            getattr(c, "_cuda_getCurrentRawStream", lambda index: int(torch.cuda.current_stream(index).cuda_stream)),
+            getattr(c, "_cuda_isCurrentStreamCapturing", torch.cuda.is_current_stream_capturing))
+    return _raw
+
+
 def _raw_stream(index: int) -> int:
     """The device's current stream as an integer handle."""
-    torch = _torch()
-    raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
-    return int(torch.cuda.current_stream(index).cuda_stream) if raw is None else raw(index)
+    return (_raw or _bind())[1](index)
+
+
+def _capturing() -> bool:
+    return (_raw or _bind())[2]()
 
 
 def _stream():
-    return _raw_stream(_torch().cuda.current_device())
+    device, stream, _ = _raw or _bind()
+    return stream(device())
 
 
 def _dtype_code(t) -> int:
@@ -245,7 +261,7 @@ def get_workspace(nbytes: int, device):
     # (the device itself is the key, so that only GPUs are ever found: its type, a quarter of a microsecond to ask for, is looked at on a miss)
     stream = None if index is None else _raw_stream(index)
     key = (device, stream)
-    if stream and torch.cuda.is_current_stream_capturing():        # (the default stream, 0, cannot be captured)
+    if stream and _capturing():                # (the default stream, 0, cannot be captured; asking takes 0.3 microseconds)
         return _capture_workspace(int(nbytes), device, key)
     if _capture_workspaces:
         _capture_workspaces.clear()      # (their graphs keep the memory; one still being captured takes another tensor and clears that)

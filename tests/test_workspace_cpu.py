@@ -15,7 +15,7 @@ def device(monkeypatch):
     monkeypatch.setattr(torch, "empty", lambda n, dtype, device: empty(n, dtype=dtype).fill_(0xFF))
     # work recorded while capturing has not run when the next graph is replayed: a cleared allocation is not clear
     monkeypatch.setattr(torch, "zeros", lambda n, dtype, device: empty(n, dtype=dtype).fill_(0xFF) if state["capture"] else zeros(n, dtype=dtype))
-    monkeypatch.setattr(torch.cuda, "is_current_stream_capturing", lambda: state["capture"] != 0)
+    monkeypatch.setattr(fhpc, "_capturing", lambda: state["capture"] != 0, raising=False)
     monkeypatch.setattr(fhpc, "_raw_stream", lambda index: state["stream"])
     monkeypatch.setattr(fhpc, "_capture_id", lambda stream: state["capture"], raising=False)
     monkeypatch.setattr(fhpc, "_workspaces", {})
