@@ -567,8 +567,11 @@ def test_few_token_launches_replayed_from_a_graph():
 
 
 @pytest.mark.parametrize("M,K,r,N", [
-    (100, 2000, 100, 2008),  # 32 x 32 tiles in many slices: more slabs than the four waves take at a time
-    (1100, 4040, 170, 1928), # 64 x 64 tiles, the last step of a slice outside; rank not a multiple of four
+    (100, 2000, 100, 2008),  # 32 x 32 tiles in 16 slices: as many slabs as the four waves take at a time
+    (20, 4096, 130, 4104),   # in 32 slices, twice as many
+    (1100, 4040, 170, 1928), # 64 x 64 tiles in four slices, the last step of the reduction outside; rank not a multiple of four
+    (595, 2688, 101, 608),   # in 12, three times what a wave takes at a time
+    (1098, 512, 119, 608),   # both weight gradients in seven, operands by 16 and by 4 bytes
     (5, 8, 129, 40),         # a reduction shorter than a step
 ])
 def test_fp32_slices_on_uncleared_scratch(M, K, r, N):
@@ -596,11 +599,11 @@ def test_fp32_slices_on_uncleared_scratch(M, K, r, N):
 
 @pytest.mark.parametrize("M,K,r,N", [
     (65, 264, 40, 72),        # one row and a part of a tile beyond 64; everything whole
-    (127, 776, 64, 712),      # whole rank products, a rank of one tile exactly
-    (128, 4104, 72, 568),     # many slices, the last one short; nine of 64 columns of the second tile
+    (127, 776, 64, 712),      # slices of a few steps, a rank of one tile exactly
+    (128, 4104, 72, 568),     # many slices, the last one short; eight of 64 columns of the second tile
     (300, 2056, 16, 520),     # at most 32 wide: most of the tile outside
-    (1000, 1600, 376, 1544),  # two workgroups and more per compute unit
-    (2100, 1032, 264, 264),   # slices and whole products beside each other, a ragged last tile in both directions
+    (1000, 1600, 376, 1544),  # outputs of two workgroups per compute unit
+    (2100, 1032, 264, 264),   # large and small tiles beside each other, a ragged last tile in both directions
     (8200, 520, 64, 1288),    # whole over many tokens
 ])
 def test_small_tile_products(M, K, r, N):
@@ -660,9 +663,9 @@ def test_graphs_in_one_pool_replayed_in_any_order():
 
 
 @pytest.mark.parametrize("M,K,r,N", [
-    (2050, 776, 131, 1032),   # 64 x 64 tiles; the last step of the reduction over the rank holds three
-    (70, 264, 45, 136),       # 32 x 32 tiles
-    (1000, 1600, 66, 2056),   # rows of the rank 8-byte aligned
+    (4100, 1032, 195, 776),   # both weight gradients on 64 x 64 tiles; the last step of the reduction over the rank holds three
+    (70, 264, 45, 136),       # 32 x 32 tiles, everything whole
+    (1000, 1600, 66, 2056),   # rows of the rank 8-byte aligned; 32 x 32 tiles in slices
 ])
 def test_fp32_ranks_that_are_not_a_multiple_of_four(M, K, r, N):
     """X, dY and B by 16 bytes beside A, H and dH by four, in every product alone and in the launch that carries both weight gradients."""

@@ -830,7 +830,7 @@ def test_premerged_weight(scheme, M):
 
 @pytest.mark.parametrize("q", [4, 8])
 @pytest.mark.parametrize("M,K,r,N", [
-    (66, 1088, 16, 520),      # two rows beyond one block, slices of unequal depth, nine of 64 columns of a tile
+    (66, 1088, 16, 520),      # two rows beyond one block, slices of unequal depth, eight of 128 columns of a tile
     (129, 2048, 40, 1032),    # one row beyond two blocks; a rank beyond 32
     (384, 1024, 8, 2112),     # the last row count of these tiles; two slices
 ])
