@@ -355,8 +355,8 @@ SplitPlan plan_fused_large(int64_t M, int64_t Nout, int64_t Kred)
 
 // Up to 384 tokens tiles of 64 x 128 compute fewer rows that do not exist and need fewer slices for as many workgroups.  128 rows are
 // ahead where they read the weight half as often and still fill the chip (65 to 128 tokens with more than a quarter of the units' tiles,
-// up to 96 on a long reduction three sixteenths; an even number of 64-row blocks with more than half of them), where a few workgroups
-// are left for a second round, and on reductions beyond 5120, which have slices enough.  Whole call of the forward in microseconds, 128 / 64 rows: 8-bit 4096 x 4096 at 300 tokens 40.7 / 37.9,
+// up to 96 on a long reduction three sixteenths; an even number of 64-row blocks with more than half of them), where with more than
+// one block a few workgroups are left for a second round, and on reductions beyond 5120, which have slices enough.  Whole call of the forward in microseconds, 128 / 64 rows: 8-bit 4096 x 4096 at 300 tokens 40.7 / 37.9,
 // at 100 28.0 / 25.3, 5120 x 4096 at 250 38.4 / 33.7, 2048 x 2048 at 200 23.0 / 20.4, 4-bit 2816 x 5120 at 150 33.6 / 30.1; dense (blend)
 // 3072 x 4096 at 256 32.5 / 28.7; but 4-bit 11008 x 4096 at 65 39.6 / 44.5, 8-bit 11008 x 4096 at 500 74.9 / 87, 8-bit 5120 x 5120 at 65
 // 27.0 / 30.0, 3264 x 4736 at 75 28.4 / 31.2, dense 4096 x 4096 at 65 23.0 / 25.2, 2816 x 4672 at 73 25.6 / 30.3, 3840 x 5120 at 205 37.4 / 41.0, 1088 x 4352 at 216 (272
@@ -364,7 +364,7 @@ SplitPlan plan_fused_large(int64_t M, int64_t Nout, int64_t Kred)
 SplitPlan plan_fused_split(int64_t M, int64_t Nout, int64_t Kred)
 {
     const int64_t units = num_cu(), rows = (M + 63) / 64, tiles = tile_count(TILE_64x128, M, Nout), ksteps = (Kred + 63) / 64;
-    const bool fits = M <= 96 && Kred > 3328 ? 16 * tiles <= 3 * units : M <= 128 ? 4 * tiles <= units : rows % 2 == 0 ? 2 * tiles <= units : 3 * tiles <= 2 * units;
+    const bool fits = rows % 2 == 1 ? 3 * tiles <= 2 * units : M <= 96 && Kred > 3328 ? 16 * tiles <= 3 * units : M <= 128 ? 4 * tiles <= units : 2 * tiles <= units;
     if (M <= 384 && Kred <= 5120 && fits) {
         int64_t s = 2 * units / tiles < 4 ? 2 * units / tiles : 4;
         if (s < units / tiles) s = units / tiles;
@@ -377,7 +377,7 @@ SplitPlan plan_fused_split(int64_t M, int64_t Nout, int64_t Kred)
             sp.k_chunk = (int)(per * 64);
             sp.splits = (int)((ksteps + per - 1) / per);
             const int64_t groups = tiles * sp.splits;
-            if (groups <= units || 4 * groups > 5 * units) return sp;
+            if (rows == 1 || groups <= units || 4 * groups > 5 * units) return sp;
         }
     }
     return plan_fused_large(M, Nout, Kred);

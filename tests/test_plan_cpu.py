@@ -121,12 +121,13 @@ def test_decompose_slabs_fit():
 
 @pytest.mark.parametrize("M,K,N,slices", [
     (300, 4096, 4096, 3), (150, 2816, 5120, 4), (100, 4096, 2048, 8),      # 64-row tiles
+    (13, 1728, 12096, 3),                                                  # one block of rows
     (83, 4864, 4224, 9), (75, 3264, 4736, 6), (205, 3840, 5120, 6),        # 128-row tiles, which read the weight half as often
     (213, 3520, 2560, 6),                                                  # (64 rows: a few workgroups more than units)
 ])
 def test_rows_of_dequantising_tiles(M, K, N, slices):
     """The slices of the dequantising product tell its tile (what either takes stands at the rule)."""
-    for scheme in (fhpc.FHPC_Q_INT8_PER_CHANNEL, fhpc.FHPC_W_BF16):
+    for scheme in (fhpc.FHPC_W_BF16,) if M <= 64 else (fhpc.FHPC_Q_INT8_PER_CHANNEL, fhpc.FHPC_W_BF16):
         assert _assert_fits(fhpc.FHPC_OP_QLINEAR_FWD, "qlinear_fwd", M=M, K=K, r=16, N=N, qscheme=scheme) == slices * M * N * 4
 
 
