@@ -72,6 +72,8 @@ struct Carver {
     }
 };
 
+constexpr int64_t ROOM_ANY = (int64_t)1 << 62;
+
 // Buffers an entry point may need, laid out identically by the measuring pass and the
 // real pass.
 struct Scratch {
@@ -84,7 +86,7 @@ struct Scratch {
     float* dB_t = nullptr;  // fp32 [rp][N]
     float* part = nullptr;  // fp32 partial sums of a split reduction, one slab per split
     int64_t part_bytes = 0; // what is reserved behind `part`
-    int64_t rank_room = (int64_t)1 << 62;   // what the slabs of H = X A may take of it
+    int64_t rank_room = ROOM_ANY;   // what the slabs of H = X A may take of it
     void* Wm = nullptr;     // bf16 [K][N]    base_scale * deq(W) + scaling * A B, many tokens (see many_tokens)
     float* sk_part = nullptr;   // weight-streaming forward (few tokens): slabs of M x N
     float* sk_hpart = nullptr;  //                                        partial sums of X A
@@ -192,7 +194,6 @@ SplitPlan plan_split_on(int tile, int64_t M, int64_t N, int64_t Kred, int g = 1)
 // least.  A 64-deep step takes 0.32 microseconds where a compute unit has one workgroup and 0.265 per workgroup where it has
 // more (1024 x 512 from 4096 in 2 slices 12.8, 2048 x 512 in 2 19.3, 4096 x 512 whole 32.4), and slabs are written and read at 4 TB/s by a launch more.
 // `room`: bytes the slabs may take.
-constexpr int64_t ROOM_ANY = (int64_t)1 << 62;
 SplitPlan plan_small(int64_t M, int64_t N, int64_t Kred, int64_t room = ROOM_ANY, double* microseconds = nullptr)
 {
     const int64_t ksteps = (Kred + 63) / 64, tiles = tile_count(TILE_64x64, M, N), units = num_cu(), fit = room / (M * N * 4);
