@@ -733,6 +733,63 @@ def test_fp32_products_in_three_parts(M, K, r, N):
         assert torch.equal(only[i], out[i])
 
 
+def _fp32_launches(fhpc, call):
+    """What `call` returns, and the names of the fp32 products it launched."""
+    fhpc.profile_start(64)
+    try:
+        out = call()
+    finally:
+        names = [name for name, *_ in fhpc.profile_stop()]
+    return out, [n for n in names if n.startswith("gemm_f32")]
+
+
+@pytest.mark.parametrize("where", ["X", "A", "B", "dY"])
+def test_fp32_subnormal_words_in_three_parts(where):
+    """Subnormal words beside words of about 1e30, every product on three-part operands: the results are ordinary numbers and made of
+    those words alone, in an input gradient, a forward output or H.  The words are exact in three parts, so each result has the accuracy of
+    a single product carried through two sums: 1e-6."""
+    import torch
+    fhpc = _fhpc()
+    M, K, r, N = 4100, 2008, 256, 1000
+    X, A, B, dY = lowrank_inputs(12, M, K, r, N, bf16=False)
+    # (multiples of 2^-149 = 1.4e-45; those of the first tile of rows below 2^-134, which bf16 rounds to zero)
+    sub = np.float32([1e-41, -3e-42, 2.2e-44, 4.5e-41, 1e-44, 9e-39, -4.6e-41, 1e-38])
+    rows = np.r_[300:305, 1000:1003]
+    if where == "X":                                                  # H = X A
+        X[:, 7], X[rows] = 0, 0
+        X[rows, 7] = sub
+        A[7] *= np.float32(1e30)
+    elif where == "dY":                                               # dH = dY B^T
+        dY[:, 5], dY[rows] = 0, 0
+        dY[rows, 5] = sub
+        B[:, 5] *= np.float32(1e30)
+    elif where == "A":
+        A[9], A[:, 3] = 0, 0
+        A[9, 3] = sub[0]
+        X[:, 9] *= np.float32(1e30)
+    else:                                                             # Y = H B
+        A[:, 3] *= np.float32(1e30)
+        B[3], B[:, 11] = 0, 0
+        B[3, 11] = sub[0]
+    d = [torch.from_numpy(t).cuda() for t in (X, A, B, dY)]
+    (Y, H), fwd = _fp32_launches(fhpc, lambda: fhpc.lowrank_linear_fwd(*d[:3], save_H=True))
+    (dX, dA, dB), bwd = _fp32_launches(fhpc, lambda: fhpc.lowrank_linear_bwd(*d, H_saved=H))
+    assert len(fwd) == 2 and len(bwd) == 3 and all(n.startswith("gemm_f32x3<") for n in fwd + bwd), (fwd, bwd)
+    X, A, B, dY = (t.astype(np.float64) for t in (X, A, B, dY))
+    if where == "X":
+        pairs = [(H[rows], X[rows] @ A), (Y[rows], X[rows] @ A @ B)]
+    elif where == "dY":
+        pairs = [(dX[rows], dY[rows] @ B.T @ A.T)]
+    elif where == "A":
+        pairs = [(H[:, 3:4], X @ A[:, 3:4])]
+    else:
+        pairs = [(Y[:, 11:12], X @ A @ B[:, 11:12])]
+    for got, ref in pairs:
+        got = from_device(got)
+        for g, f in zip(got, ref) if where in ("X", "dY") else [(got, ref)]:
+            assert np.linalg.norm(f) > 0 and np.linalg.norm(g - f) <= 1e-6 * np.linalg.norm(f), where
+
+
 def test_fp32_words_that_do_not_come_in_parts():
     """Tokens of about 1e-36 (their bf16 parts would lose all but a few bits), of infinities, of the largest finite words and of zeros
     beside ordinary ones in one tile: every token has the accuracy of its own magnitude and nothing else meets the infinities."""
