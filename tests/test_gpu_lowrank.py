@@ -790,6 +790,81 @@ def test_fp32_subnormal_words_in_three_parts(where):
             assert np.linalg.norm(f) > 0 and np.linalg.norm(g - f) <= 1e-6 * np.linalg.norm(f), where
 
 
+def _elementwise(got, ref, size, what):
+    """Non-finite where `ref` is, and each element within 4e-6 of `size`, the product of the operands' magnitudes: the sums of a launch round
+    some 60 times (24 in a trip, as many trips and slabs), 60 x 2^-24 = 3.6e-6; what falls below the normal numbers besides."""
+    got = from_device(got)
+    ok = np.isfinite(ref)
+    assert np.array_equal(got[~ok], ref[~ok], equal_nan=True), what
+    assert np.all(np.abs(got[ok] - ref[ok]) <= 4e-6 * size[ok] + 1e-40), what
+
+
+@pytest.mark.parametrize("M,K,r,N,tiles", [
+    (4100, 2008, 256, 1000, ["128s", "64", "128s", "128", "128s"]),       # H, Y, dH, dX, both weight gradients; s: in slices
+    (8192, 768, 192, 3072, ["64s", "128", "128s", "64", "128s"]),
+])
+@pytest.mark.parametrize("where", ["X", "A", "B", "dY", "X inf", "dY nan"])
+def test_fp32_tiles_formed_again(M, K, r, N, tiles, where):
+    """One word that does not come in three parts, 3.4e38 beside small ones so that results are finite, an infinity or a NaN: its tiles are formed
+    again on the fp32 instructions, whole, in slices beside other slabs, and in every layout; all elements of all outputs."""
+    import re
+    import torch
+    fhpc = _fhpc()
+    X, A, B, dY = lowrank_inputs(13, M, K, r, N, bf16=False)
+    top, f = np.float32(3.4e38), np.float32
+    if where == "X":
+        A[5] *= f(1e-20); dY[700] *= f(1e-20); X[700, 5] = top
+    elif where == "A":
+        X[:, 5] *= f(1e-30); B[3] *= f(1e-8); A[5, 3] = top
+    elif where == "B":
+        A[:, 3] *= f(1e-30); dY[:, 5] *= f(1e-30); B[3, 5] = top
+    elif where == "dY":
+        B[:, 5] *= f(1e-20); X[700] *= f(1e-18); dY[700, 5] = top
+    elif where == "X inf":
+        X[700, 5] = np.inf
+    else:
+        dY[700, 5] = np.nan
+    d = [torch.from_numpy(t).cuda() for t in (X, A, B, dY)]
+    (Y, H), fwd = _fp32_launches(fhpc, lambda: fhpc.lowrank_linear_fwd(*d[:3], save_H=True))
+    (dX, dA, dB), bwd = _fp32_launches(fhpc, lambda: fhpc.lowrank_linear_bwd(*d, H_saved=H))
+    ran = [re.match(r"gemm_f32x3<(\d+),a\d,b\d,v15,s(\d+)\+\d+>", n).groups() for n in fwd + bwd]
+    assert [t + ("s" if int(s) > 1 else "") for t, s in ran] == tiles, (fwd, bwd)
+    X, A, B, dY = (t.astype(np.float64) for t in (X, A, B, dY))
+    Hd = from_device(H)
+    with np.errstate(invalid="ignore"):
+        m = [np.abs(t) for t in (X, A, B, dY, Hd)]
+        dH, mH = dY @ B.T, m[3] @ m[2].T
+        _elementwise(H, X @ A, m[0] @ m[1], "H")
+        _elementwise(Y, Hd @ B, m[4] @ m[2], "Y")
+        _elementwise(dX, dH @ A.T, 2 * (mH @ m[1].T), "dX")
+        _elementwise(dA, X.T @ dH, 2 * (m[0].T @ mH), "dA")
+        _elementwise(dB, Hd.T @ dY, m[4].T @ m[3], "dB")
+
+
+def test_fp32_tiles_formed_again_take_their_time():
+    """Every tile formed twice, on both kinds of instruction, takes 2.3 times as long as once; word by word from memory it took 7.7 times as long."""
+    import torch
+    fhpc = _fhpc()
+    X, A, B, dY = (torch.from_numpy(t).cuda() for t in lowrank_inputs(14, 8192, 768, 192, 3072, bf16=False))
+
+    def shortest():
+        times = []
+        for _ in range(6):
+            e = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
+            e[0].record()
+            Y, H = fhpc.lowrank_linear_fwd(X, A, B, save_H=True)
+            fhpc.lowrank_linear_bwd(X, A, B, dY, H_saved=H)
+            e[1].record()
+            e[1].synchronize()
+            times.append(e[0].elapsed_time(e[1]))
+        return min(times)
+
+    plain = shortest()
+    X.view(-1)[::997] = float("nan")
+    dY.view(-1)[::997] = float("nan")
+    assert shortest() <= 4 * plain
+
+
 def test_fp32_words_that_do_not_come_in_parts():
     """Tokens of about 1e-36 (their bf16 parts would lose all but a few bits), of infinities, of the largest finite words and of zeros
     beside ordinary ones in one tile: every token has the accuracy of its own magnitude and nothing else meets the infinities."""
