@@ -841,6 +841,24 @@ def test_fp32_tiles_formed_again(M, K, r, N, tiles, where):
         _elementwise(dB, Hd.T @ dY, m[4].T @ m[3], "dB")
 
 
+def test_fp32_three_parts_are_as_exact_as_the_fp32_instructions():
+    """Relative errors no larger than those of the fp32 instructions' tiles for the same operands, 1.92 1.21 2.29 2.46 2.12e-7.  H, two slices of
+    six trips of 64 k: roundings of the variance of 4.5 (in trips) + 3.3 (trips) + 1 (slabs) final ones, .42 x 2^-24 each: 7.4e-8."""
+    import torch
+    fhpc = _fhpc()
+    d = [torch.from_numpy(t).cuda() for t in lowrank_inputs(15, 8192, 768, 192, 3072, bf16=False)]
+    (Y, H), fwd = _fp32_launches(fhpc, lambda: fhpc.lowrank_linear_fwd(*d[:3], save_H=True))
+    (dX, dA, dB), bwd = _fp32_launches(fhpc, lambda: fhpc.lowrank_linear_bwd(*d, H_saved=H))
+    assert all(n.startswith("gemm_f32x3<") for n in fwd + bwd), (fwd, bwd)
+    X, A, B, dY = (t.double() for t in d)
+    Hr, dHr = X @ A, dY @ B.T.contiguous()
+    for name, got, ref, most in (("Y", Y, Hr @ B, 1.92e-7), ("H", H, Hr, 1.0e-7), ("dX", dX, dHr @ A.T.contiguous(), 2.29e-7),
+                                 ("dA", dA, X.T.contiguous() @ dHr, 2.46e-7), ("dB", dB, Hr.T.contiguous() @ dY, 2.12e-7)):
+        err = float((got.double() - ref).norm() / ref.norm())
+        print(name, "rel %.3e" % err, flush=True)
+        assert err <= most, (name, err)
+
+
 def test_fp32_tiles_formed_again_take_their_time():
     """Every tile formed twice, on both kinds of instruction, takes 2.3 times as long as once; word by word from memory it took 7.7 times as long."""
     import torch
