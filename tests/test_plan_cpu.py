@@ -144,3 +144,18 @@ def test_slabs_of_the_rank_product_fit_the_fixed_scratch(M, K, r, N, scheme):
     assert fhpc.workspace_bytes(fhpc.FHPC_OP_QLINEAR_FWD, M, K, r, N, fhpc.FHPC_BF16, scheme) <= fhpc.FHPC_NOALLOC_SCRATCH_BYTES
     for outputs in (0, 1):
         _assert_fits(fhpc.FHPC_OP_QLINEAR_FWD, "qlinear_fwd", M=M, K=K, r=r, N=N, qscheme=scheme, outputs=outputs)
+
+
+def test_middle_fp32_layers_are_planned_as_quickly_as_small_ones():
+    """504 tokens are below the size from which three-part operands are priced at all, 520 above it, with the same plans: 1.0 times as long a
+    call, and 1.3 when every slice count of those tiles is priced first."""
+    import time
+    need = fhpc.load_library().fhpc_workspace_bytes
+    best = {504: 1.0, 520: 1.0}
+    for _ in range(30):
+        for M in best:
+            start = time.perf_counter()
+            for _ in range(1000):
+                need(fhpc.FHPC_OP_LOWRANK_BWD, M, 1024, 64, 1024, fhpc.FHPC_F32, 0)
+            best[M] = min(best[M], time.perf_counter() - start)
+    assert best[520] <= 1.15 * best[504], best
