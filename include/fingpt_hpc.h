@@ -76,7 +76,7 @@ enum {
     FHPC_ERR_SHAPE = 2,       /* non-positive size, K or N not a multiple of 8, K % block != 0 */
     FHPC_ERR_DTYPE = 3,       /* unknown dtype / qscheme */
     FHPC_ERR_ALIGN = 4,       /* a data pointer is not 16-byte aligned (workspace: 256) */
-    FHPC_ERR_WORKSPACE = 5,   /* workspace NULL or smaller than fhpc_workspace_bytes */
+    FHPC_ERR_WORKSPACE = 5,   /* workspace NULL or smaller than fhpc_workspace_bytes (f32: than what lowrank_linear_fwd says) */
     FHPC_ERR_UNSUPPORTED = 6, /* block != 64, matrix >= 2 GiB, ... */
     FHPC_ERR_HIP = 7          /* a HIP call or kernel launch failed */
 };
@@ -89,7 +89,14 @@ enum { FHPC_OP_LOWRANK_FWD = 0, FHPC_OP_LOWRANK_BWD = 1, FHPC_OP_QLINEAR_FWD = 2
  *   Y[M,N] = (X[M,K] * A[K,r]) * B[r,N].
  * X, A, B, Y have `dtype`.  H_out (M x r, `dtype`), if not NULL, receives H = X*A for
  * the backward pass.  bf16: fp32 accumulation, H rounded to bf16 between the two
- * products.  f32: plain fp32 arithmetic throughout. */
+ * products.  f32: fp32 words, products of their full 24 bits, fp32 sums.  Large products run on the bf16
+ * matrix instructions, each word as the sum of three bf16 parts: as exact as on the fp32 instructions (relative
+ * error about 2e-7 of an output), with fp32's range and special values: tiles that meet an infinity, a NaN, a word
+ * from 2^104 or a sum from 2^80 on are formed on the fp32 instructions (a layer all of whose tiles do takes 2.3
+ * times as long).  f32 workspace, forward and backward: fhpc_workspace_bytes is what the fastest kernels need; a
+ * smaller one that holds the partial sums of the fp32 instructions' kernels is accepted too and runs on those
+ * alone, so results (and an H formed again in the backward pass) may then differ in their last bits from
+ * those of the full size.  Below that: FHPC_ERR_WORKSPACE. */
 int lowrank_linear_fwd(const void* X, const void* A, const void* B, void* Y, void* H_out,
                        int64_t M, int64_t K, int64_t r, int64_t N, int dtype,
                        void* workspace, size_t workspace_bytes, void* hip_stream);

@@ -1,4 +1,5 @@
-// The fp32 products of the factorised layer, on the fp32 matrix instructions.  Internal; not part of the C ABI.
+// The fp32 products of the factorised layer, on the fp32 matrix instructions or, large ones, on the bf16 ones with operands in three parts.
+// Internal; not part of the C ABI.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
