@@ -700,13 +700,39 @@ def test_shared_x_outputs_of_few_tokens_share_a_launch(M, r):
         assert parity_err(from_device(Y), oracle.lowrank_fwd(X.f64, a.f64, b.f64)[0], TOL_BF16, "Y") <= TOL_BF16
 
 
-@pytest.mark.parametrize("M,K,r,N", [
-    (2050, 1032, 132, 4104),  # Y and dH on 128 x 128 tiles, whole and in slices, two rows and eight columns beyond; four ranks beyond
-    (4100, 2008, 256, 1000),  # everything on three-part operands; reductions that end inside a trip of 64
-    (8185, 776, 191, 3080),   # odd rank and token count: H, A and dH by four bytes, both weight gradients in slices
-    (520, 4096, 250, 4104),   # few rows: 64 x 64 tiles; rows of the rank 8-byte aligned
+def _fp32_launches(fhpc, call):
+    """What `call` returns, and the names of the fp32 products it launched."""
+    fhpc.profile_start(64)
+    try:
+        out = call()
+    finally:
+        names = [name for name, *_ in fhpc.profile_stop()]
+    return out, [n for n in names if n.startswith("gemm_f32")]
+
+
+def _fp32_tiles(names):
+    """Of each launch: "-" on the fp32 instructions; on three-part operands the tile's edge, "s" if in slices, and after a "/" the operands loaded
+    by 16 bytes (bits 0 and 1 a and b of the first product, 2 and 3 of the second) where not all are."""
+    import re
+    out = []
+    for n in names:
+        kind, tile, vec, s0, s1 = re.match(r"gemm_f32(x3)?<(\d+),a\d,b\d,v(\d+),s(\d+)\+(\d+)>", n).groups()
+        out.append(tile + "s" * (max(int(s0), int(s1)) > 1) + ("" if vec == "15" else "/" + vec) if kind else "-")
+    return out
+
+
+@pytest.mark.parametrize("M,K,r,N,tiles", [       # tiles of H, Y, dH, dX and both weight gradients
+    (2050, 1032, 132, 4104, ["-", "64", "64s", "-", "64s"]),             # two rows and eight columns beyond the tiles; four ranks beyond
+    (4100, 2008, 256, 1000, ["128s", "64", "128s", "128", "128s"]),      # everything on three-part operands; reductions that end inside a trip of 64
+    (8185, 776, 191, 3080, ["-", "128/10", "-", "-", "-"]),              # odd rank and token count
+    (520, 4096, 250, 4104, ["-", "-", "-", "-", "-"]),                   # few rows: all on the fp32 instructions
+    (4406, 1488, 40, 1664, ["64s", "128", "64s", "64", "64s"]),          # fewer ranks than a tile
+    (2689, 2808, 103, 264, ["128s/5", "-", "-", "128/0", "128s/9"]),     # words of the rank by four bytes: one operand, both, one of each product
+    (6366, 256, 228, 312, ["64", "64", "64", "64", "128s"]),             # short reductions, whole
+    (165, 4088, 232, 2760, ["-", "-", "-", "-", "64"]),                  # weight gradients over few tokens, whole
+    (5185, 256, 33, 2224, ["-", "128/10", "-", "-", "-"]),               # a reduction of 33
 ])
-def test_fp32_products_in_three_parts(M, K, r, N):
+def test_fp32_products_in_three_parts(M, K, r, N, tiles):
     """Large fp32 products multiply bf16 parts: as close to the oracle as fp32 sums are.  1e-6: a chain of 4104 fp32 additions of terms
     without order is off by sqrt(4104 / 3) 2^-24 = 2.2e-6 at most where every partial sum is as large as the last; sums of 64 apart,
     that is 4.6e-7 and three times that in the parts' roundings and the second product."""
@@ -721,9 +747,10 @@ def test_fp32_products_in_three_parts(M, K, r, N):
     ws = torch.full((max(fhpc.workspace_bytes(op, M, K, r, N, fhpc.FHPC_F32) for op in (fhpc.FHPC_OP_LOWRANK_FWD, fhpc.FHPC_OP_LOWRANK_BWD)),),
                     0xFF, dtype=torch.uint8, device="cuda")
     ws[:16384] = 0
-    Y, H = fhpc.lowrank_linear_fwd(Xd, Ad, Bd, Y=g[0], H_out=g[1], workspace=ws)
+    (Y, H), fwd = _fp32_launches(fhpc, lambda: fhpc.lowrank_linear_fwd(Xd, Ad, Bd, Y=g[0], H_out=g[1], workspace=ws))
     assert parity_err(from_device(H), Hr, 1e-6, "H") <= 1e-6
-    out = fhpc.lowrank_linear_bwd(Xd, Ad, Bd, dYd, H_saved=H, dX=g[2], dA=g[3], dB=g[4], workspace=ws)
+    out, bwd = _fp32_launches(fhpc, lambda: fhpc.lowrank_linear_bwd(Xd, Ad, Bd, dYd, H_saved=H, dX=g[2], dA=g[3], dB=g[4], workspace=ws))
+    assert _fp32_tiles(fwd + bwd) == tiles
     _check_all("f32 parts %s" % ((M, K, r, N),), (Y,) + out, ref, 1e-6)
     guard.check("f32 parts %s" % ((M, K, r, N),))
     again = fhpc.lowrank_linear_bwd(Xd, Ad, Bd, dYd)                  # H recomputed
@@ -731,16 +758,6 @@ def test_fp32_products_in_three_parts(M, K, r, N):
     for i in range(3):
         only = fhpc.lowrank_linear_bwd(Xd, Ad, Bd, dYd, H_saved=H, need_dX=i == 0, need_dA=i == 1, need_dB=i == 2)
         assert torch.equal(only[i], out[i])
-
-
-def _fp32_launches(fhpc, call):
-    """What `call` returns, and the names of the fp32 products it launched."""
-    fhpc.profile_start(64)
-    try:
-        out = call()
-    finally:
-        names = [name for name, *_ in fhpc.profile_stop()]
-    return out, [n for n in names if n.startswith("gemm_f32")]
 
 
 @pytest.mark.parametrize("where", ["X", "A", "B", "dY"])
@@ -802,12 +819,13 @@ def _elementwise(got, ref, size, what):
 @pytest.mark.parametrize("M,K,r,N,tiles", [
     (4100, 2008, 256, 1000, ["128s", "64", "128s", "128", "128s"]),       # H, Y, dH, dX, both weight gradients; s: in slices
     (8192, 768, 192, 3072, ["64s", "128", "128s", "64", "128s"]),
+    (4406, 1488, 40, 1664, ["64s", "128", "64s", "64", "64s"]),
+    (2689, 2808, 103, 264, ["128s/5", "-", "-", "128/0", "128s/9"]),
 ])
 @pytest.mark.parametrize("where", ["X", "A", "B", "dY", "X inf", "dY nan"])
 def test_fp32_tiles_formed_again(M, K, r, N, tiles, where):
     """One word that does not come in three parts, 3.4e38 beside small ones so that results are finite, an infinity or a NaN: its tiles are formed
     again on the fp32 instructions, whole, in slices beside other slabs, and in every layout; all elements of all outputs."""
-    import re
     import torch
     fhpc = _fhpc()
     X, A, B, dY = lowrank_inputs(13, M, K, r, N, bf16=False)
@@ -827,8 +845,7 @@ def test_fp32_tiles_formed_again(M, K, r, N, tiles, where):
     d = [torch.from_numpy(t).cuda() for t in (X, A, B, dY)]
     (Y, H), fwd = _fp32_launches(fhpc, lambda: fhpc.lowrank_linear_fwd(*d[:3], save_H=True))
     (dX, dA, dB), bwd = _fp32_launches(fhpc, lambda: fhpc.lowrank_linear_bwd(*d, H_saved=H))
-    ran = [re.match(r"gemm_f32x3<(\d+),a\d,b\d,v15,s(\d+)\+\d+>", n).groups() for n in fwd + bwd]
-    assert [t + ("s" if int(s) > 1 else "") for t, s in ran] == tiles, (fwd, bwd)
+    assert _fp32_tiles(fwd + bwd) == tiles
     X, A, B, dY = (t.astype(np.float64) for t in (X, A, B, dY))
     Hd = from_device(H)
     with np.errstate(invalid="ignore"):
@@ -884,8 +901,8 @@ def test_fp32_tiles_formed_again_take_their_time():
 
 
 def test_fp32_words_that_do_not_come_in_parts():
-    """Tokens of about 1e-36 (their bf16 parts would lose all but a few bits), of infinities, of the largest finite words and of zeros
-    beside ordinary ones in one tile: every token has the accuracy of its own magnitude and nothing else meets the infinities."""
+    """Tokens of about 1e-36, of infinities, of the largest finite words and of zeros beside ordinary ones in one tile of a layer whose Y runs on
+    three-part operands: every token has the accuracy of its own magnitude and nothing else meets the infinities."""
     import torch
     fhpc = _fhpc()
     M, K, r, N = 2048, 1024, 128, 4096
