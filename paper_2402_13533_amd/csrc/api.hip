@@ -1034,7 +1034,7 @@ int lowrank_bwd_f32(const float* X, const float* A, const float* B, const float*
 {
     const float* H = H_saved;
     if (!H && dB) {
-        // (the way the forward call forms it, so that saved and recomputed H have the same bits)
+        // (the way the forward call forms it, so that saved and recomputed H have the same bits, unless one of the calls is `tight`)
         float* Hw = static_cast<float*>(s.H);
         if (lowrank_chain_f32_pays(M, K, r))
             FHPC_LAUNCH(run, launch_lowrank_chain_f32(X, K, A, r, F32_XC, B, N, F32_XC, nullptr, N, Hw, (int)M, (int)K, (int)r, 0, num_cu(), run.st));

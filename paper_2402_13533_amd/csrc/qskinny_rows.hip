@@ -339,15 +339,16 @@ static bool rows_fit(int64_t M, int64_t K, int64_t r)
 
 }  // namespace skinny
 
-// Where it is the faster way (microseconds per call, replayed from a graph, one token, sliced kernel / this one):
-//   many channels, which are what the slabs cost: 5120 -> 15360 int4 23.2 / 19.8, 5120 -> 27648 41.8 / 28.9, 4096 -> 12288 int8
-//   22.4 / 20.3; with fewer the launch ahead costs as much: 5120 -> 10240 16.3 / 16.6, 5120 -> 5120 12.4 / 13.6;
-//   more than 16 ranks, where the sliced kernel's chunks of H are what it waits for: 4096 -> 4096 r = 32 16.5 / 11.9,
-//   r = 64 25.4 / 20.5;
-//   a short reduction, few chunks of H to form: 2048 -> 4096 11.2 / 9.2.
-// Over 838 calls it takes (1 .. 16 tokens, K 512 .. 8192, r 4 .. 64, both storages) it is 1.23 times faster on average; 28 are 4 .. 14 per
-// cent slower, where the sliced kernel's blocks happen to fill its one round (5 tokens, 4096 -> 2 x 12416 r 32 int8 30.7 / 34.6, 3 tokens, 4096
-// -> 2 x 11008 int4 19.7 / 21.1): no bound on tokens, ranks or that fill tells them apart without giving up more than it saves.
+// Where it is taken (microseconds a call, twelve calls on four weights replayed from a graph, one token, sliced kernel / this one):
+//   many channels, which are what the slabs cost: 5120 -> 15360 int4 19.7 / 15.2, 5120 -> 27648 41.9 / 25.5, 4096 -> 12288 int8
+//   20.9 / 16.3;
+//   more than 16 ranks, where the sliced kernel's chunks of H are what it waits for: 4096 -> 4096 r = 32 17.2 / 9.9,
+//   r = 64 22.7 / 15.0;
+//   a short reduction, few chunks of H to form: 2048 -> 4096 10.9 / 6.7.
+// Over 240 calls it takes (1 .. 16 tokens, K 512 .. 8192, r 4 .. 64, both storages, ten calls a replay) it is 1.08 .. 2 times faster, 1.56 on
+// average.  The line at 12288 channels dates from an H launch of 4.6 instead of 3.5 microseconds and lies high: with fewer channels a
+// call alone in its graph takes as long either way (5120 -> 10240 19.4 / 19.4, 5120 -> 5120 16.7 / 17.0; 5120 -> 11776 24.6 / 19.5), calls one
+// after another are faster here too (14.7 / 12.8, 12.1 / 10.7, 19.9 / 12.9).
 // The rest are its limits.
 bool qskinny_rows_pay(int64_t M, int64_t K, int64_t r, int64_t N_all, int num_cu)
 {
